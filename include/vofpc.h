@@ -147,19 +147,22 @@ vofpc_status vofpc_mesh_info(vofpc_mesh mesh, int64_t info[8]);
  * = the reconstruction kernel flavour used for class c (see
  * vofpc_mesh_set_tune); *bucketed = 1 when the cells spread over several
  * classes: then the reconstruction splits the mixed entries by class and
- * launches each class's kernel on its own entries (size buckets), else the
- * one class's kernel runs. */
+ * launches each class's kernel on its own entries (size buckets; classes 0
+ * and 2 with few cells ride with class 1 when all run group flavours), else
+ * the one class's kernel runs. */
 vofpc_status vofpc_mesh_classes(vofpc_mesh mesh, int64_t cells[4], int32_t tune[4], int32_t *bucketed);
 /* Reconstruction kernel flavours (tile shapes) per class:
  *   3, 4   one cell per wavefront (64 lanes over its loop positions), with
  *          the register budget of 3 or 4 waves per SIMD; 3 for every
  *          class, 4 for classes 0 to 2;
- *   10+G   a group of G lanes per cell (the lanes share the cell's edges and
- *          faces), 64/G cells per wavefront: G = 1, 2, 4 for class 0 when
+ *   10+G   a group of lanes per cell (the lanes share the cell's edges and
+ *          faces), several cells per wavefront: G = 1, 2, 4 for class 0 when
  *          its cells are at most hexahedra (8 vertices, 6 faces), else
- *          G = 2, 4; G = 4, 8, 16 for classes 1 and 2.
- * The learned form runs the network inside the reconstruction for every
- * flavour.  Results of all flavours agree within the parity tolerances. */
+ *          G = 2, 4; G = 4, 8, 16 for classes 1 and 2.  One build serves
+ *          every G of a class (4 lanes for class 0, 16 for the others).
+ * A mesh starts with the group flavour of every class that has one, 3 for the
+ * others.  The learned form runs the network inside the reconstruction for
+ * every flavour.  Results of all flavours agree within the parity tolerances. */
 #define VOFPC_FLAVOUR_WAVE3 3
 #define VOFPC_FLAVOUR_WAVE4 4
 #define VOFPC_FLAVOUR_GROUP(G) (10 + (G))
@@ -168,7 +171,7 @@ vofpc_status vofpc_mesh_classes(vofpc_mesh mesh, int64_t cells[4], int32_t tune[
  * cells is given a flavour that has no build for it. */
 vofpc_status vofpc_mesh_set_tune(vofpc_mesh mesh, const int32_t tune[4]);
 /* Class launches side by side (default on).  A bucketed reconstruction runs
- * the usual Voronoi class (1) and its bracket pass on the context's stream
+ * the usual Voronoi class (1) on the context's stream
  * and the other classes beside it on a second stream the context owns
  * (default priority), forked after the bucketing and joined before the call
  * returns, so one class's idle issue slots and tail are filled by another's
@@ -179,13 +182,13 @@ vofpc_status vofpc_ctx_overlap_classes(vofpc_ctx ctx, int32_t enable);
 /* Per-class kernel timing of the reconstruction (a measurement aid).  With
  * enable != 0, every later eager reconstruction on this context records a HIP
  * event pair around each class kernel it launches, on the stream the kernel
- * runs on, and around the class's bracket pass when the learned form runs
- * one (none while the stream is being captured); enable = 0 destroys the
+ * runs on (none while the stream is being captured); enable = 0 destroys the
  * events.
  * vofpc_ctx_class_ms waits for the latest call's events and writes to HOST
- * ms[8] the duration in milliseconds of each class kernel (ms[0..3]) and of
- * each bracket pass (ms[4..7]), -1 where none ran, then forgets them;
- * VOFPC_E_STATE when timing is off. */
+ * ms[8] the duration in milliseconds of each class kernel (ms[0..3]), -1 where
+ * none ran (a class that rides with class 1 is in ms[1]), then forgets them;
+ * ms[4..7], the bracket passes before the class kernels, are -1: the network
+ * runs inside them.  VOFPC_E_STATE when timing is off. */
 vofpc_status vofpc_ctx_time_classes(vofpc_ctx ctx, int32_t enable);
 vofpc_status vofpc_ctx_class_ms(vofpc_ctx ctx, float ms[8]);
 /* Copy the computed geometry into caller DEVICE buffers (any may be NULL):
@@ -247,7 +250,8 @@ typedef struct {
   double *d;          /* n . (x_P - c_int), positive when x_P is in the liquid */
   double *alpha_got;  /* V_liq(s)/V_P */
   int32_t *status;    /* VOFPC_CELL_* */
-  int32_t *iters;     /* volume evaluations spent */
+  int32_t *iters;     /* volume evaluations spent (4 or 16 isovalues cut side by side by a
+                       * group flavour count as 2 or 4, the halvings they stand for) */
   int64_t cap;
 } vofpc_interface;
 
@@ -264,8 +268,7 @@ typedef struct {
  * shrinks to two ulps first, the end nearer to alpha V_P is taken
  * (VOFPC_CELL_NO_ROOT when its residual exceeds 1e-10).  Guesses come from
  * regula falsi / inverse quadratic interpolation with bisection safeguards;
- * between two breakpoints of the cut topology several guesses are evaluated
- * at once.  Any isovalue in the stopping window is a valid result; the
+ * where the cells do not fill the chip several guesses are evaluated at once.  Any isovalue in the stopping window is a valid result; the
  * oracle's bisection may stop at another one of the same window.
  * hint_lo/hint_hi: DEVICE [cap] per mixed entry, read only when
  * opts->bracket is VOFPC_BRACKET_HINT (NaN entries: plain search, no flag):
@@ -282,8 +285,8 @@ vofpc_status vofpc_reconstruct(vofpc_ctx ctx, vofpc_mesh mesh, const double *alp
 
 /* Reconstruction with the bracket network run inside the same kernel: each
  * mixed cell's 32 inputs (as vofpc_features defines them) and the forward
- * pass (BF16 MFMA tiles of 16 cells in the group flavours, one FP32 row per
- * wavefront in the wavefront flavours) give the predicted isovalue
+ * pass (BF16 weights and activations, FP32 multiply-adds in one fixed order, so
+ * every flavour predicts the same bits) give the predicted isovalue
  * phi_min + clamp(u,0,1) W and the bracket around it of half-width
  * delta_scale W, checked as with VOFPC_BRACKET_HINT with the first cut at the
  * predicted isovalue.  opts->bracket must be

@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "vofpc_internal.h"
+#include "recon_common.h"
 
 namespace vofpc {
 
@@ -265,7 +266,9 @@ static vofpc_status setup_classes(vofpc_mesh M, const ClassStats &cs) {
   for (int c = 0; c < kClasses; ++c) {
     M->class_cells[c] = class_cnt[c];
     for (int t = 0; t < 4; ++t) M->class_max[c][t] = cmax[c][t];
-    M->tune[c] = 3;
+    // the group build of each class that has one (recon_common.h)
+    const int group = c == 0 ? 4 : 16;
+    M->tune[c] = class_cnt[c] > 0 && thin_available(c, group, cmax[c]) ? VOFPC_FLAVOUR_GROUP(group) : VOFPC_FLAVOUR_WAVE3;
     if (class_cnt[c] > 0) M->max_class = c;
     if (class_cnt[c] > 0) ++big;
   }

@@ -1173,12 +1173,13 @@ __global__ void bucket_zero_kernel(int32_t *c) {
   if (threadIdx.x < kClasses) c[threadIdx.x] = 0;
 }
 
-// Split the mixed entries into one list per class (order within a list is
-// the order of the claims; results do not depend on it).  Blocks of 1024
+// Split the mixed entries into one list per class, the classes in the bit set
+// `joined` into class 1's (order within a list is the order of the claims;
+// results do not depend on it).  Blocks of 1024
 // stride over the mixed entries; per tile of 1024 entries, one claim per
 // class on the list counter (the waves' counts summed in LDS first).
 constexpr int kBucketBlock = 1024;
-__global__ __launch_bounds__(kBucketBlock) void bucket_kernel(DevMesh m, int hex0, const int32_t *mixed,
+__global__ __launch_bounds__(kBucketBlock) void bucket_kernel(DevMesh m, int hex0, int joined, const int32_t *mixed,
                                                               const int32_t *counts, int64_t cap, int32_t *lists,
                                                               int64_t stride, int32_t *bcount) {
   constexpr int kW = kBucketBlock / 64;
@@ -1189,7 +1190,8 @@ __global__ __launch_bounds__(kBucketBlock) void bucket_kernel(DevMesh m, int hex
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   for (int64_t k0 = (int64_t)blockIdx.x * kBucketBlock; k0 < count; k0 += (int64_t)gridDim.x * kBucketBlock) {
     const int64_t k = k0 + threadIdx.x;
-    const int c = (k < count) ? cell_class(m, hex0 != 0, mixed[k]) : -1;
+    int c = (k < count) ? cell_class(m, hex0 != 0, mixed[k]) : -1;
+    if (c >= 0 && ((joined >> c) & 1)) c = 1;
     uint64_t mine = 0;
 #pragma unroll
     for (int q = 0; q < kClasses; ++q) {
@@ -1232,8 +1234,9 @@ vofpc_status launch_t(vofpc_ctx ctx, const ReconParams &p, int64_t n_cells) {
 // Launch the variant of class c in flavour `flav`: 3 or 4 = one cell per
 // wavefront with the register budget of that many waves per SIMD (the two
 // common classes have both), 10 + G = G lanes per cell (recon_thin.hip).
-vofpc_status launch_class(vofpc_ctx ctx, vofpc_mesh M, const ReconParams &p, int64_t n_cells, int c, int flav) {
-  if (flav >= 10) return launch_thin(ctx, p, n_cells, c, flav - 10, M->class_max[c]);
+vofpc_status launch_class(vofpc_ctx ctx, vofpc_mesh M, const ReconParams &p, int64_t n_cells, int c, int flav,
+                          bool with_large) {
+  if (flav >= 10) return launch_thin(ctx, p, n_cells, c, flav - 10, M->class_max[c], with_large);
   const int occ = flav == 4 ? 4 : 3;
   switch (c) {
     case 0:
@@ -1310,54 +1313,11 @@ vofpc_status launch_reconstruct(vofpc_ctx ctx, vofpc_mesh M, const double *alpha
     VOFPC_HIP(hipStreamIsCapturing(ctx->stream, &cs));
     timed = cs == hipStreamCaptureStatusNone;
     if (timed)
-      for (int c = 0; c < kClasses; ++c) ctx->cls_rec[c] = ctx->pass_rec[c] = false;
+      for (int c = 0; c < kClasses; ++c) ctx->cls_rec[c] = false;
   }
-  // learned form in a group build whose wavefronts hold fewer than 16 cells
-  // (G = 8, 16: classes 1 and 2): the brackets come from a pass of their own
-  // with full network tiles, and the class kernel checks them as a caller's
-  // brackets (the same check and flag)
-  auto pass_first = [&](int c) {
-    const int f = M->tune[c];
-    return p.net_wb != nullptr && (c == 1 || c == 2) && (f == VOFPC_FLAVOUR_GROUP(8) || f == VOFPC_FLAVOUR_GROUP(16));
-  };
-  bool any_pass = false;
-  for (int c = 0; c < kClasses; ++c)
-    any_pass = any_pass || ((M->bucketed ? M->class_cells[c] > 0 : c == M->max_class) && pass_first(c));
-  if (any_pass && !p.net_lo && !M->hint_buf) {
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    VOFPC_HIP(hipStreamIsCapturing(ctx->stream, &cs));
-    VOFPC_REQUIRE(cs == hipStreamCaptureStatusNone, VOFPC_E_STATE,
-                  "reconstruct_learned: the first call on a mesh without hint_lo/hint_hi sets up its bracket "
-                  "buffer and must not be captured");
-    void *b = nullptr;
-    vofpc_status st = mesh_scratch_alloc(M, 2 * sizeof(double) * (size_t)N, &b);
-    if (st) return st;
-    M->hint_buf = (double *)b;
-  }
-  auto run_class = [&](int64_t n_cells, int c) -> vofpc_status {
-    vofpc_status st;
-    if (pass_first(c)) {
-      double *hl = p.net_lo ? p.net_lo : M->hint_buf, *hh = p.net_hi ? p.net_hi : M->hint_buf + N;
-      if (timed) VOFPC_HIP(hipEventRecord(ctx->pass_ev[c][0], ctx->stream));
-      st = launch_bracket_pass(ctx, p, n_cells, c, hl, hh);
-      if (st) return st;
-      if (timed) {
-        VOFPC_HIP(hipEventRecord(ctx->pass_ev[c][1], ctx->stream));
-        ctx->pass_rec[c] = true;
-        VOFPC_HIP(hipEventRecord(ctx->cls_ev[c][0], ctx->stream));
-      }
-      ReconParams q = p;
-      q.net_wb = nullptr;
-      q.net_master = nullptr;
-      q.net_lo = q.net_hi = nullptr;
-      q.use_hint = 1;
-      q.hint_lo = hl;
-      q.hint_hi = hh;
-      st = launch_class(ctx, M, q, n_cells, c, M->tune[c]);
-    } else {
-      if (timed) VOFPC_HIP(hipEventRecord(ctx->cls_ev[c][0], ctx->stream));
-      st = launch_class(ctx, M, p, n_cells, c, M->tune[c]);
-    }
+  auto run_class = [&](int64_t n_cells, int c, bool with_large) -> vofpc_status {
+    if (timed) VOFPC_HIP(hipEventRecord(ctx->cls_ev[c][0], ctx->stream));
+    const vofpc_status st = launch_class(ctx, M, p, n_cells, c, M->tune[c], with_large);
     if (st) return st;
     if (timed) {
       VOFPC_HIP(hipEventRecord(ctx->cls_ev[c][1], ctx->stream));
@@ -1365,21 +1325,43 @@ vofpc_status launch_reconstruct(vofpc_ctx ctx, vofpc_mesh M, const double *alpha
     }
     return VOFPC_OK;
   };
-  if (!M->bucketed) return run_class(N, M->max_class);
-  // one launch per class present in the mesh, each over its own entries
+  // classes that ride with class 1 in one launch of its group kernel: class 0
+  // and class 2 when they are at most 1/16 of its cells (the few small and
+  // large cells of a Voronoi mesh) and run group builds themselves.  With a
+  // launch each, a step over 12 + 1,443 + 3 cells (112 mixed) took 111 us, in
+  // one launch 75 us: the bucketing and the fork and join of the streams cost
+  // more than the stray cells.  A larger share keeps its own launch: a class-2
+  // cell met by a class-1 wavefront runs after the wavefront's other cells.
+  int joined = 0;
+  for (int c = 0; c <= 2; c += 2)
+    if (M->class_cells[c] > 0 && M->class_cells[c] * 16 <= M->class_cells[1] && M->tune[c] >= 10 && M->tune[1] >= 10)
+      joined |= 1 << c;
+  int launches = 0, only = 0;
+  int64_t cells[kClasses];
+  for (int c = 0; c < kClasses; ++c) cells[c] = (joined >> c) & 1 ? 0 : M->class_cells[c];
+  for (int c = 0; c < kClasses; ++c)
+    if ((joined >> c) & 1) cells[1] += M->class_cells[c];
+  for (int c = 0; c < kClasses; ++c)
+    if (cells[c] > 0) {
+      ++launches;
+      only = c;
+    }
+  const bool with_large = (joined & 4) != 0;
+  if (launches == 1) return run_class(N, only, with_large);
+  // one launch per class, each over its own entries
   bucket_zero_kernel<<<1, 64, 0, ctx->stream>>>(M->bucket_counts);
   const int64_t span = std::min<int64_t>(out->cap, N);
   const int64_t bgrid = std::min<int64_t>((span + kBucketBlock - 1) / kBucketBlock, (int64_t)ctx->n_cu * 2);
   bucket_kernel<<<(unsigned)std::max<int64_t>(bgrid, 1), kBucketBlock, 0, ctx->stream>>>(
-      M->d, M->hex0 ? 1 : 0, mixed, counts, out->cap, M->bucket_lists, N, M->bucket_counts);
+      M->d, M->hex0 ? 1 : 0, joined, mixed, counts, out->cap, M->bucket_lists, N, M->bucket_counts);
   VOFPC_HIP(hipGetLastError());
-  // the usual Voronoi class (with its bracket pass) on the context's stream,
+  // the usual Voronoi class on the context's stream,
   // the other classes beside it on the side stream, forked after the
   // bucketing and joined before the call returns (each class claims from
   // its own counters), so one class's tail overlaps another's work
   bool others = false;
-  for (int c = 0; c < kClasses; ++c) others = others || (c != kMainClass && M->class_cells[c] > 0);
-  const bool fork = ctx->overlap_classes && ctx->side && others && M->class_cells[kMainClass] > 0;
+  for (int c = 0; c < kClasses; ++c) others = others || (c != kMainClass && cells[c] > 0);
+  const bool fork = ctx->overlap_classes && ctx->side && others && cells[kMainClass] > 0;
   hipStream_t main_stream = ctx->stream;
   if (fork) {
     VOFPC_HIP(hipEventRecord(ctx->fork_ev, main_stream));
@@ -1387,12 +1369,12 @@ vofpc_status launch_reconstruct(vofpc_ctx ctx, vofpc_mesh M, const double *alpha
   }
   vofpc_status st = VOFPC_OK;
   for (int c = 0; c < kClasses && st == VOFPC_OK; ++c) {
-    if (M->class_cells[c] == 0) continue;
+    if (cells[c] == 0) continue;
     p.entries = M->bucket_lists + (int64_t)c * N;
     p.entry_count = M->bucket_counts + c;
     p.queue = ctx->queue + c * kQueueSet;
     if (fork && c != kMainClass) ctx->stream = ctx->side;
-    st = run_class(M->class_cells[c], c);
+    st = run_class(cells[c], c, c == 1 && with_large);
     ctx->stream = main_stream;
   }
   if (fork) {
@@ -1419,18 +1401,16 @@ extern "C" vofpc_status vofpc_ctx_time_classes(vofpc_ctx ctx, int32_t enable) {
     for (int c = 0; c < kClasses; ++c)
       for (int j = 0; j < 2; ++j) {
         VOFPC_HIP(hipEventCreate(&ctx->cls_ev[c][j]));
-        VOFPC_HIP(hipEventCreate(&ctx->pass_ev[c][j]));
       }
   } else if (!enable && ctx->time_classes) {
     for (int c = 0; c < kClasses; ++c)
       for (int j = 0; j < 2; ++j) {
         (void)hipEventDestroy(ctx->cls_ev[c][j]);
-        (void)hipEventDestroy(ctx->pass_ev[c][j]);
-        ctx->cls_ev[c][j] = ctx->pass_ev[c][j] = nullptr;
+        ctx->cls_ev[c][j] = nullptr;
       }
   }
   ctx->time_classes = enable != 0;
-  for (int c = 0; c < kClasses; ++c) ctx->cls_rec[c] = ctx->pass_rec[c] = false;
+  for (int c = 0; c < kClasses; ++c) ctx->cls_rec[c] = false;
   return VOFPC_OK;
 }
 
@@ -1446,11 +1426,6 @@ extern "C" vofpc_status vofpc_ctx_class_ms(vofpc_ctx ctx, float ms[8]) {
       VOFPC_HIP(hipEventSynchronize(ctx->cls_ev[c][1]));
       VOFPC_HIP(hipEventElapsedTime(&ms[c], ctx->cls_ev[c][0], ctx->cls_ev[c][1]));
       ctx->cls_rec[c] = false;
-    }
-    if (ctx->pass_rec[c]) {
-      VOFPC_HIP(hipEventSynchronize(ctx->pass_ev[c][1]));
-      VOFPC_HIP(hipEventElapsedTime(&ms[kClasses + c], ctx->pass_ev[c][0], ctx->pass_ev[c][1]));
-      ctx->pass_rec[c] = false;
     }
   }
   return VOFPC_OK;
@@ -1479,7 +1454,8 @@ bool flavour_ok(vofpc_mesh M, int c, int f) {
 // The flavours the tuner tries for class c.
 int candidates(vofpc_mesh M, int c, int out[8]) {
   int n = 0;
-  const int all[] = {VOFPC_FLAVOUR_WAVE3, VOFPC_FLAVOUR_WAVE4, 11, 12, 14, 18, 26};
+  // (one group build serves every G of a class)
+  const int all[] = {VOFPC_FLAVOUR_WAVE3, VOFPC_FLAVOUR_WAVE4, VOFPC_FLAVOUR_GROUP(c == 0 ? 4 : 16)};
   for (int f : all)
     if (flavour_ok(M, c, f)) out[n++] = f;
   return n;

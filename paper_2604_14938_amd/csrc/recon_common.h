@@ -115,18 +115,13 @@ __device__ __forceinline__ NetFace load_net_face(const ReconParams &p, int P, do
   return r;
 }
 
-// Launch the group kernel with G lanes per cell on the entries of class c
-// (the class's largest cell sizes in cmax = vertices, faces, loop positions,
-// edges pick the LDS layout).  Returns VOFPC_E_INVALID_ARG when no build of
-// the kernel holds that class.
+// Launch the group kernel on the entries of class c (the class's largest cell
+// sizes in cmax = vertices, faces, loop positions, edges pick the build, which
+// serves every G).  with_large: the entries of class 1 also hold cells of
+// class 2.  Returns VOFPC_E_INVALID_ARG when no build holds that class.
 vofpc_status launch_thin(vofpc_ctx ctx, const ReconParams &p, int64_t n_entries, int c, int G,
-                         const int64_t cmax[4]);
+                         const int64_t cmax[4], bool with_large);
 // Whether launch_thin has a build for class c with these sizes and G.
 bool thin_available(int c, int G, const int64_t cmax[4]);
-// The learned brackets of the entries of class c (1 or 2) in a pass of their
-// own: 16 cells per wavefront; writes hlo/hhi[k] per mixed entry k (NaN
-// where the cell gets no network).  p carries the network and delta.
-vofpc_status launch_bracket_pass(vofpc_ctx ctx, const ReconParams &p, int64_t n_entries, int c, double *hlo,
-                                 double *hhi);
 
 }  // namespace vofpc

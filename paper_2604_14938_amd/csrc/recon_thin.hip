@@ -1,37 +1,56 @@
 // Volume-matched iso-polygon reconstruction with a group of G lanes per mixed
-// cell (G = 1 to 16) and 64/G cells per wavefront.
+// cell (G = 4 or 16) and up to 64/G cells per wavefront.
 //
-// The one-cell-per-wavefront kernel (recon.hip) spreads a cell's loop
-// positions over 64 lanes, so most lanes idle on hexahedra and on the search
-// control.  Here a group of G lanes shares a cell's edges and faces, combines
-// its lanes' sums by DPP butterflies, and a wavefront works on 64/G cells at
-// once, staged side by side in LDS (arrays indexed [item][cell slot], so the
-// cells of a wavefront read different banks).
+// A lane owns a few edges, faces and vertices of its cell for the whole
+// search and keeps them in registers: an edge's end values, its liquid end,
+// direction and whole-edge volume term, a face's fan point and two edge masks, a
+// vertex's value and adjacency mask.  The cut of an isovalue is described by
+// bit masks over the cell's edges and vertices, gathered with wavefront
+// ballots, so an evaluation reads LDS only for the crossing points of the
+// faces that are cut.
 //
 // One volume evaluation at isovalue s (divergence theorem, each face's
-// liquid polygon fanned from a point of its plane, here its first vertex):
-//   - per edge: the two faces' terms of the whole edge, D_e = det(c1, u, v) +
-//     det(c2, v, u), are fixed per cell; an evaluation adds D_e times the
-//     edge's liquid fraction (1, 0, or for a cut edge the fraction from its
-//     liquid end, which scales both faces' liquid pieces of the edge alike),
-//     and registers a cut edge with the face the iso-curve leaves through it
-//     and the face it enters through it;
-//   - per face: a face with two crossings has one chord, exit -> entry; a
-//     face with four or more pairs each exit with the next entry in loop
-//     order when the face-mean vertex value is >= s, else with the previous
-//     one (the oracle's rule); the chord closes the face's liquid polygon;
-//     crossing points follow Eq. edge_intersection from the liquid end of
-//     the edge, computed once per edge, so both faces get the same point;
+// liquid polygon fanned from a point of its plane, one of its vertices):
+//   - per edge, held from its end of larger value u to the other end v (the
+//     liquid end of a cut edge is always u): the two faces' terms of the
+//     whole edge, D_e = det(c1, u, v) + det(c2, v, u), are fixed per cell; an
+//     evaluation adds D_e times the edge's liquid fraction (1, 0, or for a
+//     cut edge the fraction from its liquid end, which scales both faces'
+//     liquid pieces of the edge alike) and stores the crossing point of a cut
+//     edge (Eq. edge_intersection) once, so both faces get the same point;
+//     the ballots of the cut edges give the cell's cut mask;
+//   - per face, the iso-curve leaves through the cut edges its loop runs
+//     along from u to v and enters through the others: two static masks
+//     and'ed with the cut mask.  A face with two crossings has one chord,
+//     exit -> entry; a face with four or more pairs each exit with the next
+//     entry in loop order when the face-mean vertex value is >= s, else with
+//     the previous one (the oracle's rule); the chord closes the face's
+//     liquid polygon;
 //   - per chord, the terms of its iso-loop: a loop is the chain of chords
 //     (the chord entering through edge e follows the chord leaving through
 //     e), and fanning a loop from its length-weighted polyline centroid k
 //     gives volume k . Y / 6 and area vector -Y / 2 with Y = sum over its
 //     chords of (entry point x exit point), the centroid from sum l and
 //     sum l (entry + exit): chord-local sums, taken about a reference
-//     vertex of the cell.  A single loop (the usual case, found by walking
-//     the chord links once) needs nothing else; several loops are labelled
-//     through LDS and their sums gathered loop by loop in a second pass over
-//     the faces.
+//     vertex of the cell.
+// The loops of a cut bound the connected pieces of the liquid and the vapour
+// part of the cell's surface, one loop fewer than there are pieces; when no
+// face has more than two crossings the pieces are the connected components of
+// the liquid and of the vapour vertices under the cell's edges.  A flood
+// fill of the vertex masks (ballots, no memory) therefore shows that there is
+// one loop, the usual case, and its result is kept while the liquid vertices
+// stay the same, which they do once the search is inside one interval of the
+// vertex values.  Otherwise the chords are linked through LDS, the loops
+// labelled and their sums gathered loop by loop in a second pass.
+//
+// What bounds it: instruction issue and the latency of dependent FP64
+// operations, not memory.  Holding the edges in registers and the cut in
+// masks, against cells staged in LDS and walked through byte tables (the
+// evaluation before), whole plain steps on one chip: 24,042 Voronoi cells cut
+// of 351k in 241 instead of 395 us, 31,948 hexahedra of 1.33M in 190 instead of
+// 249 us; with few cells the teams below: 2,832 of 195k Voronoi cells in 106
+// instead of 165 us (one cell per wavefront, recon.hip), 5,000 of 422k
+// hexahedra in 62 instead of 143 us.
 //
 // Search: Brent's method (Brent 1973, ch. 4) on r(s) = V(s)/V_P - alpha
 // over a bracket of [phi_min, phi_max] whose ends straddle the root: inverse
@@ -45,12 +64,12 @@
 // otherwise the part of the full bracket beyond that end does (status
 // LEARNED_FALLBACK: the root is outside the bracket).
 //
-// Scheduling: a wavefront takes 64/G consecutive mixed entries (a batch),
-// stages them together, runs their searches side by side until the last one
-// stops, writes them out and claims the next batch.  The batches go to the
-// XCDs in runs of consecutive batches (neighbouring cells share an L2), and
-// each XCD's wavefronts claim its batches from a counter of its own that
-// wraps back to zero after the XCD's last claim.
+// Scheduling: a wavefront takes up to 64/G consecutive mixed entries (a
+// batch), stages them together, runs their searches side by side until the
+// last one stops, writes them out and claims the next batch.  The batches go
+// to the XCDs in runs of consecutive batches (neighbouring cells share an
+// L2), and each XCD's wavefronts claim its batches from a counter of its own
+// that wraps back to zero after the XCD's last claim.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -134,45 +153,106 @@ __device__ __forceinline__ double iqi1(double x0, double f0, double x1, double f
   return x0 + qdiv((x2 - x0) * f0 * f1 * d01 - (x1 - x0) * f0 * f2 * d02, d01 * d02 * d12);
 }
 
+
+// Sum over the group of one value per slot (item q + G t in slot t), added
+// in the order of the wavefront kernel's reductions (its lane i holds item
+// i): within rows of 16 items, then rows 0 + 1, then the rest, so both
+// kernels feed the network the same bits.
+template <int G, int K>
+__device__ __forceinline__ double items_sum(const double (&v)[K]) {
+  static_assert(G == 4 || G == 16, "a DPP quad or row per group");
+  constexpr int R = (K * G + 15) / 16;   // rows of 16 items
+  double r[R];
+  if constexpr (G == 16) {
+#pragma unroll
+    for (int t = 0; t < R; ++t) r[t] = tsum<16>(v[t]);
+  } else {
+    double s[4 * R];
+#pragma unroll
+    for (int t = 0; t < 4 * R; ++t) s[t] = t < K ? tsum<4>(v[t < K ? t : 0]) : 0.0;
+#pragma unroll
+    for (int t = 0; t < R; ++t) r[t] = (s[4 * t] + s[4 * t + 1]) + (s[4 * t + 2] + s[4 * t + 3]);
+  }
+  double a = r[0];
+  if constexpr (R > 1) a += r[1];
+  if constexpr (R > 2) {
+    double b = r[2];
+    if constexpr (R > 3) b += r[3];
+    a += b;
+  }
+  return a;
+}
+__device__ __forceinline__ float quad_sum_f(float v) {
+  v += __builtin_bit_cast(float, dpp_i<kQuadXor1>(__builtin_bit_cast(int, v)));
+  v += __builtin_bit_cast(float, dpp_i<kQuadXor2>(__builtin_bit_cast(int, v)));
+  return v;
+}
+__device__ __forceinline__ float row_sum_f(float v) {
+  v = quad_sum_f(v);
+  v += __builtin_bit_cast(float, dpp_i<kHalfMirror>(__builtin_bit_cast(int, v)));
+  v += __builtin_bit_cast(float, dpp_i<kRowMirror>(__builtin_bit_cast(int, v)));
+  return v;
+}
+
+// The group's bits of a wavefront ballot, the group's first lane in bit 0.
+template <int G>
+__device__ __forceinline__ uint32_t group_bits(bool b, int base) {
+  return (uint32_t)(__ballot(b) >> base) & ((1u << G) - 1u);
+}
+
+template <int N>
+using mask_t = std::conditional_t<(N <= 32), uint32_t, uint64_t>;
+__device__ __forceinline__ int count_bits(uint32_t m) { return __popc(m); }
+__device__ __forceinline__ int count_bits(uint64_t m) { return __popcll(m); }
+__device__ __forceinline__ int first_bit(uint32_t m) { return __ffs((int)m) - 1; }
+__device__ __forceinline__ int first_bit(uint64_t m) { return __ffsll((long long)m) - 1; }
+__device__ __forceinline__ void or_lds(uint32_t *p, uint32_t v) { atomicOr(p, v); }
+__device__ __forceinline__ void or_lds(uint64_t *p, uint64_t v) {
+  atomicOr(reinterpret_cast<unsigned long long *>(p), (unsigned long long)v);
+}
+
 // ----------------------------------------------------------------- LDS layout
 // The staged cells of one wavefront, item-major and cell-slot-minor; the
-// 4- and 8-byte arrays have an odd slot stride CP, so the lanes of a group,
-// which read different items of one cell, spread over the LDS banks.
-// Network scratch of a wavefront (learned form): one BF16 input row per cell
-// slot (16 rows at least: a tile), one 16-row tile of hidden activations and
-// the first output per slot.
-template <int C>
-struct ThinNet {
-  static constexpr int R = C < 16 ? 16 : C;
-  alignas(16) uint16_t x[R][net::kIn];
-  alignas(16) uint16_t h[16][net::kHid];
-  float u[R];
+// 8-byte arrays have an odd slot stride CP, so the lanes of a group, which
+// read different items of one cell, spread over the LDS banks.
+//
+// Network scratch (learned form): a row of inputs and of hidden activations
+// per cell (BF16 values held as floats; rows padded by one 16-byte word
+// against bank conflicts), the face sums before the activations, and the
+// vertex ranks.
+template <int C, int NV>
+struct NetRows {
+  alignas(16) float x[C][net::kIn + 4];
+  union {
+    alignas(16) float h[C][net::kHid + 4];
+    double sum[C][19];
+  };
+  uint8_t rank[NV][C];   // vertex of each rank
 };
 
-template <int C, int NV, int NF, int NL, int NE>
-struct ThinMem {
-  static constexpr int CP = C | 1;
-  double X[3][NV][CP];  // vertex positions relative to the cell centroid
+template <int C, int CP, int NV, int NF, int NL, int NE>
+struct GroupCells {
   double phi[NV][CP];   // vertex field
-  double D[NE][CP];     // volume term of an edge taken whole by both of its faces
-  // scratch of one evaluation; outside evaluations (the network phase of the
-  // learned form) the same bytes hold the network's rows
+  double X[NV][CP][3];  // vertex positions relative to the cell centroid
   union {
+    // while a cell's registers are filled
     struct {
-      double fr[NE][CP];    // liquid fraction of each cut edge (this evaluation)
-      int32_t cnt[NF][CP];  // crossings of each face (this evaluation)
-    };
-    ThinNet<C> net;
+      mask_t<NE> out[NF][CP], in[NF][CP];   // edges the face's loop runs along u -> v, v -> u
+      mask_t<NV> adj[NV][CP];               // vertices joined to each vertex by an edge
+      uint32_t fan[NF][CP];                 // smallest vertex of each face: its fan point
+    } st;
+    NetRows<C, NV> net;   // network phase of the learned form
+    // one evaluation
+    struct {
+      double pt[NE][CP][3];   // crossing point of each cut edge
+      uint8_t part[NE][C];    // entry edge of the chord leaving through each cut edge (several loops)
+      uint8_t lab[NE][C];     // loop of each cut edge (several loops)
+    } ev;
   };
-  uint8_t eu[NE][C], ev[NE][C];    // end vertices of each edge
-  uint8_t ef1[NE][C], ef2[NE][C];  // face whose loop runs eu -> ev, and the other face
-  uint8_t fx[NF][C], fn[NF][C];    // exit and entry edge of a face with two crossings
-  uint8_t lv[NL][C];    // local vertex of each loop position
-  uint8_t eid[NL][C];   // local edge of each loop position
-  uint8_t foff[NF][C];  // first loop position of each face
-  uint8_t fsz[NF][C];   // positions of each face
-  uint8_t link[NE][C];  // exit edge of the chord entering through edge e (0xff: e not cut)
-  uint8_t lab[NE][C];   // loop of each cut edge (evaluations with several loops)
+  uint8_t lv[NL][C], eid[NL][C];   // vertex and edge of each loop position (faces with several chords)
+  double hint[3][C];    // narrowed bracket of each cell: first cut, lower end, upper end
+  double smp[2][C];     // a team's isovalues and residuals
+  double fin[9][C];     // what a search ended with: V / V_P, its loops' sums S, A, A k, and whether they failed
 };
 
 // per-lane sums of the chords of one loop (or of all loops)
@@ -187,40 +267,14 @@ __device__ __forceinline__ void reduce_acc(ChordAcc &a) {
   a.Y0 = tsum<G>(a.Y0); a.Y1 = tsum<G>(a.Y1); a.Y2 = tsum<G>(a.Y2);
 }
 
-// Crossing point of cut edge e at isovalue s: Eq. edge_intersection from
-// the edge's liquid end, with the liquid fraction of this evaluation, so
-// both faces of the edge get the same point.
-template <class TM>
-__device__ __forceinline__ void edge_point(const TM &M, int sl, int e, double s, double &p0, double &p1, double &p2) {
-  const int u = M.eu[e][sl], v = M.ev[e][sl];
-  const bool ul = M.phi[u][sl] >= s;
-  const int i = ul ? u : v, j = ul ? v : u;
-  const double lam = M.fr[e][sl];
-  p0 = M.X[0][i][sl] + lam * (M.X[0][j][sl] - M.X[0][i][sl]);
-  p1 = M.X[1][i][sl] + lam * (M.X[1][j][sl] - M.X[1][i][sl]);
-  p2 = M.X[2][i][sl] + lam * (M.X[2][j][sl] - M.X[2][i][sl]);
-}
-
-// One chord from exit point x to entry point e (edges ex, en) of a face with
-// fan point c.  mode 0: the face volume term, the link and the chord sums;
-// mode 1: only the sums, and only when the chord lies on loop `loop`.
-template <class TM>
-__device__ __forceinline__ void add_chord(TM &M, int sl, int mode, int loop, const double *r, double c0, double c1,
-                                          double c2, double x0, double x1, double x2, double e0, double e1, double e2,
-                                          int ex, int en, double &vf, ChordAcc &acc, int &nch, int &estart) {
-  if (mode == 0) {
-    vf += det3(c0, c1, c2, x0, x1, x2, e0, e1, e2);
-    M.link[en][sl] = (uint8_t)ex;
-    estart = en < estart ? en : estart;
-    ++nch;
-  } else if (M.lab[en][sl] != loop) {
-    return;
-  }
-  // the chord as a loop segment, from its entry point u to its exit point w,
-  // both relative to the cell's reference point r (near a small cut piece,
-  // so the cross products of a small loop do not cancel)
-  const double u0 = e0 - r[0], u1 = e1 - r[1], u2 = e2 - r[2];
-  const double w0 = x0 - r[0], w1 = x1 - r[1], w2 = x2 - r[2];
+// The chord from exit point x to entry point e as a loop segment, from its
+// entry point u to its exit point w, both relative to the cell's reference
+// point r (near a small cut piece, so the cross products of a small loop do
+// not cancel).
+__device__ __forceinline__ void add_segment(ChordAcc &acc, double r0, double r1, double r2, double x0, double x1,
+                                            double x2, double e0, double e1, double e2) {
+  const double u0 = e0 - r0, u1 = e1 - r1, u2 = e2 - r2;
+  const double w0 = x0 - r0, w1 = x1 - r1, w2 = x2 - r2;
   const double d0 = w0 - u0, d1 = w1 - u1, d2 = w2 - u2;
   const double l = qsqrt(d0 * d0 + d1 * d1 + d2 * d2);
   acc.L += l;
@@ -232,285 +286,28 @@ __device__ __forceinline__ void add_chord(TM &M, int sl, int mode, int loop, con
   acc.Y2 += u0 * w1 - u1 * w0;
 }
 
-// The chords of face f at isovalue s (see add_chord for mode): one chord,
-// exit -> entry, for a face with two crossings; with four or more, each exit
-// pairs with the next entry in loop order when the face-mean vertex value is
-// >= s, else with the previous one.  The fan point is the face's first
-// vertex.
-template <class TM>
-__device__ void chords_of_face(TM &M, int sl, int f, double s, int mode, int loop, const double *r, double &vf,
-                               ChordAcc &acc, int &nch, int &estart, bool &err) {
-  const int c = M.cnt[f][sl];
-  if (c == 0) return;
-  const int o = M.foff[f][sl];
-  const int a0 = M.lv[o][sl];
-  const double c0 = M.X[0][a0][sl], c1 = M.X[1][a0][sl], c2 = M.X[2][a0][sl];
-  if (c == 2) {
-    const int ex = M.fx[f][sl], en = M.fn[f][sl];
-    double x0, x1, x2, e0, e1, e2;
-    edge_point(M, sl, ex, s, x0, x1, x2);
-    edge_point(M, sl, en, s, e0, e1, e2);
-    add_chord(M, sl, mode, loop, r, c0, c1, c2, x0, x1, x2, e0, e1, e2, ex, en, vf, acc, nch, estart);
-    return;
-  }
-  if (c & 1) {
-    err = true;   // a closed loop alternates exits and entries
-    return;
-  }
-  const int n = M.fsz[f][sl];
-  double fm = 0.0;
-  for (int k = 0; k < n; ++k) fm += M.phi[M.lv[o + k][sl]][sl];
-  const bool conn = fm / (double)n >= s;
-  for (int k = 0; k < n; ++k) {
-    const int u = M.lv[o + k][sl], v = M.lv[o + ((k + 1 == n) ? 0 : k + 1)][sl];
-    if (!(M.phi[u][sl] >= s) || M.phi[v][sl] >= s) continue;   // not an exit
-    int rr = k;
-    bool found = false;
-    for (int t = 0; t < n && !found; ++t) {
-      rr = conn ? ((rr + 1 == n) ? 0 : rr + 1) : ((rr == 0) ? n - 1 : rr - 1);
-      const int ru = M.lv[o + rr][sl], rv = M.lv[o + ((rr + 1 == n) ? 0 : rr + 1)][sl];
-      found = !(M.phi[ru][sl] >= s) && M.phi[rv][sl] >= s;
-    }
-    if (!found) {
-      err = true;
-      continue;
-    }
-    const int ex = M.eid[o + k][sl], en = M.eid[o + rr][sl];
-    double x0, x1, x2, e0, e1, e2;
-    edge_point(M, sl, ex, s, x0, x1, x2);
-    edge_point(M, sl, en, s, e0, e1, e2);
-    add_chord(M, sl, mode, loop, r, c0, c1, c2, x0, x1, x2, e0, e1, e2, ex, en, vf, acc, nch, estart);
-  }
-}
-
-// Add one loop's fan: centroid k = r + M/(2L) from the length sums (relative
-// to r), volume k . Y, area vector -Y/2.
-__device__ __forceinline__ void finish_loop(const ChordAcc &a, const double *r, double &Vi, double &S0, double &S1,
-                                            double &S2, double &A, double &cw0, double &cw1, double &cw2) {
-  double k0 = r[0], k1 = r[1], k2 = r[2];   // a loop of zero length has zero area: its centre does not matter
+// Centroid of a loop from its length sums, k = r + M/(2L) (a loop of zero
+// length has zero area: its centre does not matter).
+__device__ __forceinline__ void loop_centre(const ChordAcc &a, double r0, double r1, double r2, double &k0, double &k1,
+                                            double &k2) {
+  k0 = r0; k1 = r1; k2 = r2;
   if (a.L > 0) {
     const double h = qdiv(0.5, a.L);
     k0 += a.M0 * h; k1 += a.M1 * h; k2 += a.M2 * h;
   }
+}
+
+// Add one loop's fan: volume k . Y, area vector -Y/2.
+__device__ __forceinline__ void finish_loop(const ChordAcc &a, double r0, double r1, double r2, double &Vi, double &S0,
+                                            double &S1, double &S2, double &A, double &cw0, double &cw1, double &cw2) {
+  double k0, k1, k2;
+  loop_centre(a, r0, r1, r2, k0, k1, k2);
   Vi += k0 * a.Y0 + k1 * a.Y1 + k2 * a.Y2;
   const double t0 = -0.5 * a.Y0, t1 = -0.5 * a.Y1, t2 = -0.5 * a.Y2;
   const double Ak = qsqrt(t0 * t0 + t1 * t1 + t2 * t2);
   S0 += t0; S1 += t1; S2 += t2;
   A += Ak;
   cw0 += Ak * k0; cw1 += Ak * k1; cw2 += Ak * k2;
-}
-
-// One volume evaluation of the cell in slot sl at isovalue s by its group.
-template <int G, class TM>
-__device__ CutRes thin_eval(TM &M, int sl, int q, int nf, int ne, double s, const double *r) {
-  for (int e = q; e < ne; e += G) M.link[e][sl] = 0xff;
-  for (int f = q; f < nf; f += G) M.cnt[f][sl] = 0;
-  wave_sync();
-  // edges: the liquid parts of the faces (an edge's term times its liquid
-  // fraction: 1, 0, or, for a cut edge, the fraction from its liquid end,
-  // which scales both faces' pieces alike), and each crossing registered
-  // with the face the iso-curve leaves through it and the one it enters
-  double vf = 0.0;
-  for (int e = q; e < ne; e += G) {
-    const int u = M.eu[e][sl], v = M.ev[e][sl];
-    const double pu = M.phi[u][sl], pv = M.phi[v][sl];
-    const bool lu = pu >= s, lw = pv >= s;
-    if (lu && lw) {
-      vf += M.D[e][sl];
-    } else if (lu != lw) {
-      const double pi = lu ? pu : pv, pj = lu ? pv : pu;
-      const double lam = qdiv(s - pi, pj - pi);
-      M.fr[e][sl] = lam;
-      vf += lam * M.D[e][sl];
-      const int f1 = M.ef1[e][sl], f2 = M.ef2[e][sl];
-      const int fo = lu ? f1 : f2, fi = lu ? f2 : f1;   // face f1 runs u -> v
-      M.fx[fo][sl] = (uint8_t)e;
-      M.fn[fi][sl] = (uint8_t)e;
-      atomicAdd(&M.cnt[fo][sl], 1);
-      atomicAdd(&M.cnt[fi][sl], 1);
-    }
-  }
-  wave_sync();
-  ChordAcc acc{0, 0, 0, 0, 0, 0, 0};
-  int nch = 0, estart = 0xff;
-  bool err = false;
-  for (int f = q; f < nf; f += G) chords_of_face(M, sl, f, s, 0, 0, r, vf, acc, nch, estart, err);
-  vf = tsum<G>(vf);
-  reduce_acc<G>(acc);
-  nch = tsum_i<G>(nch);
-  estart = tmin_i<G>(estart);
-  int bad = tsum_i<G>(err ? 1 : 0);
-  wave_sync();
-  double Vi = 0, S0 = 0, S1 = 0, S2 = 0, A = 0, cw0 = 0, cw1 = 0, cw2 = 0;
-  if (nch > 0 && bad == 0) {
-    // follow the chord links once from one cut edge: a single loop returns
-    // after nch chords
-    int e = estart, len = 0;
-    do {
-      e = M.link[e][sl];
-      ++len;
-    } while (e != estart && e != 0xff && len <= nch);
-    if (e == 0xff) {
-      bad = 1;
-    } else if (e == estart && len == nch) {
-      finish_loop(acc, r, Vi, S0, S1, S2, A, cw0, cw1, cw2);
-    } else {
-      // several loops: label the cut edges, then gather each loop's chords
-      for (int t = 0; t < ne; ++t) M.lab[t][sl] = 0xff;
-      int nloop = 0;
-      for (int t = 0; t < ne && bad == 0; ++t) {
-        if (M.link[t][sl] == 0xff || M.lab[t][sl] != 0xff) continue;
-        int u = t, steps = 0;
-        do {
-          M.lab[u][sl] = (uint8_t)nloop;
-          u = M.link[u][sl];
-          ++steps;
-        } while (u != t && u != 0xff && steps <= nch);
-        if (u != t) bad = 1;
-        ++nloop;
-      }
-      wave_sync();
-      for (int lp = 0; lp < nloop && bad == 0; ++lp) {
-        ChordAcc la{0, 0, 0, 0, 0, 0, 0};
-        double dv = 0.0;
-        int dn = 0, ds = 0;
-        bool derr = false;
-        for (int f = q; f < nf; f += G) chords_of_face(M, sl, f, s, 1, lp, r, dv, la, dn, ds, derr);
-        reduce_acc<G>(la);
-        finish_loop(la, r, Vi, S0, S1, S2, A, cw0, cw1, cw2);
-      }
-    }
-  }
-  wave_sync();
-  CutRes R;
-  R.err = bad != 0;
-  R.nch = nch;
-  R.V = (vf + Vi) * (1.0 / 6.0);
-  R.S0 = S0; R.S1 = S1; R.S2 = S2;
-  R.A = A;
-  if (A > 0) {
-    const double ia = qdiv(1.0, A);
-    R.c0 = cw0 * ia; R.c1 = cw1 * ia; R.c2 = cw2 * ia;
-  } else {
-    R.c0 = R.c1 = R.c2 = 0.0;
-  }
-  return R;
-}
-
-
-
-// Forward pass of the wavefront's rows on v_mfma_f32_16x16x16_bf16 tiles, all
-// 64 lanes, 16 rows per tile (BF16 weights and activations, FP32
-// accumulation, tanh hidden layers); u[r] = output 0 of row r.  Lane l holds
-// A[l%16][4(l/16)+j], B[4(l/16)+j][l%16] and D[4(l/16)+j][l%16].
-template <int C>
-__device__ void net_tiles(ThinNet<C> &T, const uint16_t *wb, const float *master, int lane) {
-  using namespace net;
-  const int col = lane & 15, rq = 4 * (lane >> 4);
-  for (int t0 = 0; t0 < ThinNet<C>::R; t0 += 16) {
-    for (int nt = 0; nt < kHid / 16; ++nt) {
-      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-      for (int kt = 0; kt < kIn / 16; ++kt)
-        acc = mfma16(*reinterpret_cast<const bf16x4 *>(&T.x[t0 + col][kt * 16 + rq]),
-                     b_weightT(wb + oW1, kIn, lane, nt * 16, kt * 16, kHid), acc);
-      const float b = master[oB1 + nt * 16 + col];
-      for (int j = 0; j < 4; ++j) T.h[rq + j][nt * 16 + col] = to_bf16(act_tanh(acc[j] + b));
-    }
-    wave_sync();
-    f32x4 acc2[kHid / 16];
-    for (int nt = 0; nt < kHid / 16; ++nt) {
-      acc2[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
-      for (int kt = 0; kt < kHid / 16; ++kt)
-        acc2[nt] = mfma16(*reinterpret_cast<const bf16x4 *>(&T.h[col][kt * 16 + rq]),
-                          b_weightT(wb + oW2, kHid, lane, nt * 16, kt * 16, kHid), acc2[nt]);
-    }
-    wave_sync();
-    for (int nt = 0; nt < kHid / 16; ++nt) {
-      const float b = master[oB2 + nt * 16 + col];
-      for (int j = 0; j < 4; ++j) T.h[rq + j][nt * 16 + col] = to_bf16(act_tanh(acc2[nt][j] + b));
-    }
-    wave_sync();
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int kt = 0; kt < kHid / 16; ++kt)
-      acc = mfma16(*reinterpret_cast<const bf16x4 *>(&T.h[col][kt * 16 + rq]),
-                   b_weightT(wb + oW3, kHid, lane, 0, kt * 16, kOut), acc);
-    if (col == 0) {
-      const float b = master[oB3];
-      for (int j = 0; j < 4; ++j) T.u[t0 + rq + j] = acc[j] + b;
-    }
-    wave_sync();
-  }
-}
-
-// The 32 network inputs of the cell in slot sl (the definitions of the
-// features entry point) into its BF16 row: face sums over the group's faces,
-// the vertex values ordered by rank (ties by index) through M.link.
-template <int G, class TM, int C>
-__device__ void cell_features(TM &M, ThinNet<C> &T, int sl, int q, const ReconParams &p, int P, double a, int nv,
-                              int nf, int64_t f0, double pmin, double Wd) {
-  double t[18];
-#pragma unroll
-  for (int i = 0; i < 18; ++i) t[i] = 0.0;
-  double amin = __builtin_inf(), amax = -__builtin_inf();
-  for (int f = q; f < nf; f += G) {
-    const NetFace g = load_net_face(p, P, a, f0 + f);
-    const double A = sqrt(g.S0 * g.S0 + g.S1 * g.S1 + g.S2 * g.S2);
-    const double n0 = g.S0 / A, n1 = g.S1 / A, n2 = g.S2 / A;
-    const double da = A * (g.aQ - a);
-    const double o[6] = {n0 * n0, n1 * n1, n2 * n2, n0 * n1, n0 * n2, n1 * n2};
-    t[0] += A;
-    t[1] += da * n0; t[2] += da * n1; t[3] += da * n2;
-#pragma unroll
-    for (int c = 0; c < 6; ++c) {
-      t[4 + c] += da * o[c];
-      t[10 + c] += A * o[c];
-    }
-    if (g.inner) {
-      t[16] += g.aQ;
-      t[17] += 1.0;
-      amin = fmin(amin, g.aQ);
-      amax = fmax(amax, g.aQ);
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < 18; ++i) t[i] = tsum<G>(t[i]);
-  amin = tmin<G>(amin);
-  amax = tmax<G>(amax);
-  double lsum = 0.0;
-  for (int i = q; i < nv; i += G) {
-    const double v = M.phi[i][sl];
-    int r = 0;
-    for (int jv = 0; jv < nv; ++jv) {
-      const double u = M.phi[jv][sl];
-      r += (u < v) || (u == v && jv < i);
-    }
-    M.link[r][sl] = (uint8_t)i;
-    lsum += v;
-  }
-  lsum = tsum<G>(lsum);
-  wave_sync();
-  auto sorted = [&](int r) { return M.phi[M.link[r][sl]][sl]; };
-  if constexpr (sizeof(T.h) >= sizeof(double) * 18 * C) {
-    // the sums go through LDS (the hidden-layer tile, not yet in use: 18
-    // doubles per cell slot), so each lane computes only its own features
-    // with a runtime index
-    double *ts = reinterpret_cast<double *>(&T.h[0][0]) + 18 * sl;
-    if (q == 0) {
-#pragma unroll
-      for (int i = 0; i < 18; ++i) ts[i] = t[i];
-    }
-    wave_sync();
-    for (int i = q; i < net::kIn; i += G)
-      T.x[sl][i] = net::to_bf16(net::feature(i, a, sorted, nv, lsum, pmin, Wd, ts, amin, amax, nf));
-    wave_sync();
-  } else {
-    // few lanes per cell: every feature index unrolled, each taken by the
-    // lane it falls to (the sums stay in registers; a runtime index would
-    // put them in scratch)
-#pragma unroll
-    for (int i = 0; i < net::kIn; ++i)
-      if (i % G == q) T.x[sl][i] = net::to_bf16(net::feature(i, a, sorted, nv, lsum, pmin, Wd, t, amin, amax, nf));
-  }
 }
 
 // The cell's vertices (positions relative to xP, when WANT_X) and their
@@ -582,9 +379,9 @@ __device__ __forceinline__ void stage_vertex_field(TM &M, const DevMesh &m, cons
       const int i = i0 + t * G;
       if (i < nv) {
         if constexpr (WANT_X) {
-          M.X[0][i][sl] = px[t] - xP0;
-          M.X[1][i][sl] = py[t] - xP1;
-          M.X[2][i][sl] = pz[t] - xP2;
+          M.X[i][sl][0] = px[t] - xP0;
+          M.X[i][sl][1] = py[t] - xP1;
+          M.X[i][sl][2] = pz[t] - xP2;
         }
         M.phi[i][sl] = ph[t];
         lo = fmin(lo, ph[t]);
@@ -594,665 +391,1051 @@ __device__ __forceinline__ void stage_vertex_field(TM &M, const DevMesh &m, cons
   }
 }
 
-// Waves per SIMD a build's register budget is sized for: enough for every
-// wave its LDS lets a CU hold (rounded up over the four SIMDs), at most 3
-// (168 VGPRs: the search state and one face walk fit without spills; a
-// 4-wave budget of 128 VGPRs spills).  The learned builds are held to the
-// same budget: what does not fit spills in the staging and network phases,
-// once per batch, not in the search.
-constexpr int thin_occupancy(int bytes) {
-  return (160 * 1024) / bytes >= 9 ? 3 : ((160 * 1024) / bytes + 3) / 4;
+
+// The 32 network inputs of the cell in slot sl (the definitions of the
+// features entry point) into its row: face sums over the group's faces, the
+// vertex values ordered by rank (ties by index).  Sums in the wavefront
+// kernel's order (items_sum).
+template <int G, int KF, int KV, class TM>
+__device__ __forceinline__ void cell_features(TM &M, int sl, int q, const ReconParams &p, int P, double a, int nv,
+                                              int nf, int64_t f0, double pmin, double Wd) {
+  double A[KF], n0[KF], n1[KF], n2[KF], da[KF], t[KF];
+  double amin = __builtin_inf(), amax = -__builtin_inf();
+  double *ns = &M.net.sum[sl][0];
+  {
+    double aq[KF], in[KF];
+#pragma unroll
+    for (int k = 0; k < KF; ++k) {
+      const int f = q + k * G;
+      A[k] = n0[k] = n1[k] = n2[k] = da[k] = aq[k] = in[k] = 0.0;
+      if (f < nf) {
+        const NetFace g = load_net_face(p, P, a, f0 + f);
+        A[k] = sqrt(g.S0 * g.S0 + g.S1 * g.S1 + g.S2 * g.S2);
+        n0[k] = g.S0 / A[k]; n1[k] = g.S1 / A[k]; n2[k] = g.S2 / A[k];
+        da[k] = A[k] * (g.aQ - a);
+        if (g.inner) {
+          aq[k] = g.aQ;
+          in[k] = 1.0;
+          amin = fmin(amin, g.aQ);
+          amax = fmax(amax, g.aQ);
+        }
+      }
+    }
+    const double s16 = items_sum<G>(aq), s17 = items_sum<G>(in), s0 = items_sum<G>(A);
+    if (q == 0) {
+      ns[0] = s0;
+      ns[16] = s16;
+      ns[17] = s17;
+    }
+  }
+  amin = tmin<G>(amin);
+  amax = tmax<G>(amax);
+  auto red = [&](int i) {
+    const double s = items_sum<G>(t);
+    if (q == 0) ns[i] = s;
+  };
+#define NET_SUM(i, expr)                         \
+  _Pragma("unroll") for (int k = 0; k < KF; ++k) t[k] = (expr); \
+  red(i);
+  NET_SUM(1, da[k] * n0[k])
+  NET_SUM(2, da[k] * n1[k])
+  NET_SUM(3, da[k] * n2[k])
+  NET_SUM(4, da[k] * n0[k] * n0[k])
+  NET_SUM(5, da[k] * n1[k] * n1[k])
+  NET_SUM(6, da[k] * n2[k] * n2[k])
+  NET_SUM(7, da[k] * n0[k] * n1[k])
+  NET_SUM(8, da[k] * n0[k] * n2[k])
+  NET_SUM(9, da[k] * n1[k] * n2[k])
+  NET_SUM(10, A[k] * n0[k] * n0[k])
+  NET_SUM(11, A[k] * n1[k] * n1[k])
+  NET_SUM(12, A[k] * n2[k] * n2[k])
+  NET_SUM(13, A[k] * n0[k] * n1[k])
+  NET_SUM(14, A[k] * n0[k] * n2[k])
+  NET_SUM(15, A[k] * n1[k] * n2[k])
+#undef NET_SUM
+  // ranks of the vertex values
+  double v[KV];
+  int r[KV];
+#pragma unroll
+  for (int k = 0; k < KV; ++k) {
+    v[k] = q + k * G < nv ? M.phi[q + k * G][sl] : 0.0;
+    r[k] = 0;
+  }
+#pragma unroll 4
+  for (int j = 0; j < nv; ++j) {
+    const double u = M.phi[j][sl];
+#pragma unroll
+    for (int k = 0; k < KV; ++k) r[k] += (u < v[k]) || (u == v[k] && j < q + k * G);
+  }
+#pragma unroll
+  for (int k = 0; k < KV; ++k)
+    if (q + k * G < nv) M.net.rank[r[k]][sl] = (uint8_t)(q + k * G);
+  const double lsum = items_sum<G>(v);
+  wave_sync();
+  auto sorted = [&](int i) { return M.phi[M.net.rank[i][sl]][sl]; };
+  for (int i = q; i < net::kIn; i += G)
+    M.net.x[sl][i] = net::from_bf16(net::to_bf16(net::feature(i, a, sorted, nv, lsum, pmin, Wd, ns, amin, amax, nf)));
 }
 
-template <int G, int NV, int NF, int NL, int NE, bool NET>
-__global__ __launch_bounds__(64, (thin_occupancy((int)sizeof(ThinMem<64 / G, NV, NF, NL, NE>))))
-void recon_thin_kernel(ReconParams p) {
-  constexpr int C = 64 / G;
-  __shared__ ThinMem<C, NV, NF, NL, NE> M;
-  ThinNet<C> &T = M.net;
-  const int lane = threadIdx.x, sl = lane / G, q = lane % G;
+// kB hidden units of one layer for a cell shared by W lanes: unit W (j0 + b)
+// + l for slot b of lane l, its BF16 weights against the cell's LDS row, FP32
+// FMAs in input order.
+template <int W, int KIN, int kB>
+__device__ __forceinline__ void net_units(const uint16_t *wts, const float *x, int l, int j0, float (&z)[kB]) {
+#pragma unroll
+  for (int b = 0; b < kB; ++b) z[b] = 0.f;
+#pragma unroll 2
+  for (int i = 0; i < KIN / 8; ++i) {
+    const float4 xa = *reinterpret_cast<const float4 *>(x + 8 * i), xb = *reinterpret_cast<const float4 *>(x + 8 * i + 4);
+    const float xv[8] = {xa.x, xa.y, xa.z, xa.w, xb.x, xb.y, xb.z, xb.w};
+#pragma unroll
+    for (int b = 0; b < kB; ++b) {
+      const uint4 w = *reinterpret_cast<const uint4 *>(wts + (int64_t)((j0 + b) * W + l) * KIN + 8 * i);
+      const uint32_t wv[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+      for (int h = 0; h < 4; ++h) {
+        z[b] = __builtin_fmaf(__uint_as_float(wv[h] << 16), xv[2 * h], z[b]);
+        z[b] = __builtin_fmaf(__uint_as_float(wv[h] & 0xffff0000u), xv[2 * h + 1], z[b]);
+      }
+    }
+  }
+}
+
+// Forward pass of one cell by the W lanes that share it (4, 16 or the whole
+// wavefront; l: the lane among them; x, h: the cell's rows): the arithmetic of
+// the wavefront kernel's row_forward, unit by unit and in its summation
+// order, so both predict the same bits.  Returns output 0.
+template <int W>
+__device__ __forceinline__ float net_forward(const float *x, float *hrow, int l, const uint16_t *wb,
+                                             const float *master) {
+  using namespace net;
+  static_assert(W == 4 || W == 16 || W == 64, "a quad, a row or a wavefront per cell");
+  constexpr int KU = kHid / W, kB = KU < 4 ? KU : 4;
+#pragma unroll 1
+  for (int j0 = 0; j0 < KU; j0 += kB) {
+    float z[kB];
+    net_units<W, kIn, kB>(wb + oW1, x, l, j0, z);
+#pragma unroll
+    for (int b = 0; b < kB; ++b) {
+      const int u = (j0 + b) * W + l;
+      hrow[u] = from_bf16(to_bf16(act_tanh(z[b] + master[oB1 + u])));
+    }
+  }
+  wave_sync();
+  float row[4] = {0.f, 0.f, 0.f, 0.f};   // sums over the rows of 16 units
+#pragma unroll 1
+  for (int j0 = 0; j0 < KU; j0 += kB) {
+    float z[kB], o[kB];
+    net_units<W, kHid, kB>(wb + oW2, hrow, l, j0, z);
+#pragma unroll
+    for (int b = 0; b < kB; ++b) {
+      const int u = (j0 + b) * W + l;
+      o[b] = from_bf16(wb[oW3 + u]) * from_bf16(to_bf16(act_tanh(z[b] + master[oB2 + u])));
+    }
+    if constexpr (W == 64) {          // row r of the wavefront holds row r
+      return wave_sum_f(o[0]) + master[oB3];
+    } else if constexpr (W == 16) {   // a block is every unit, slot b row b
+#pragma unroll
+      for (int b = 0; b < kB; ++b) row[b] = row_sum_f(o[b]);
+    } else {                          // a block is one row of 16 units
+#pragma unroll
+      for (int b = 0; b < kB; ++b) o[b] = quad_sum_f(o[b]);
+      const float s = (o[0] + o[1]) + (o[2] + o[3]);
+#pragma unroll
+      for (int b = 0; b < 4; ++b) row[b] = b * kB == j0 ? s : row[b];
+    }
+  }
+  return ((row[0] + row[1]) + (row[2] + row[3])) + master[oB3];
+}
+
+// Largest cell of a build (vertices, faces, loop positions, edges), its
+// group size and the slot stride of its LDS arrays.
+template <int G_, int NV_, int NF_, int NL_, int NE_, int CP_ = (64 / G_) | 1>
+struct Build {
+  static constexpr int G = G_, NV = NV_, NF = NF_, NL = NL_, NE = NE_;
+  using Mem = GroupCells<64 / G_, CP_, NV_, NF_, NL_, NE_>;
+  static __device__ __host__ bool fits(int64_t nv, int64_t nf, int64_t nl) {
+    return nv <= NV && nf <= NF && nl <= NL && nl / 2 <= NE;
+  }
+};
+
+// The groups of a wavefront: cw cells per batch, ts groups (a team) per cell.
+struct Team {
+  int lane, sl, q, base;   // lane, its group, its place in the group, the group's first lane
+  int cw, ts, g, lead;     // g: the group's place in its team, lead: the team's first group
+  int weight;              // evaluations a step counts as
+};
+
+// A mixed entry and its cell's place in the mesh arrays.
+struct CellRef {
+  int64_t k = 0, f0 = 0, v0 = 0, l0 = 0;
+  int P = 0, nf = 0, nv = 0, nl = 0;
+  double a = 0.0;
+};
+
+// The active groups' cells: staging, bracket, search and outputs.
+template <class Caps, bool NET>
+__device__ __forceinline__ void solve_cells(const ReconParams &p, typename Caps::Mem &M, const Team &tm,
+                                            const CellRef &cell, bool active) {
+  constexpr int G = Caps::G, C = 64 / G, NV = Caps::NV, NE = Caps::NE;
+  constexpr int KE = (NE + G - 1) / G, KF = (Caps::NF + G - 1) / G, KV = (NV + G - 1) / G,
+                KL = (Caps::NL + G - 1) / G;
+  using EM = mask_t<NE>;
+  using VM = mask_t<NV>;
+  const int lane = tm.lane, sl = tm.sl, q = tm.q, base = tm.base, cw = tm.cw, ts = tm.ts, g = tm.g, lead = tm.lead;
   const DevMesh &m = p.m;
-  const int64_t N = m.n_cells;
-  const int64_t cap = p.out.cap;
+  const int64_t N = m.n_cells, cap = p.out.cap;
+  // ---- phase 1, per cell: checks and staging
+  const int64_t k = cell.k, f0 = cell.f0, v0 = cell.v0, l0 = cell.l0;
+  const int P = cell.P, nf = cell.nf, nv = cell.nv, ne = cell.nl / 2;   // a closed surface uses every edge twice
+  const double a = cell.a;
+  int st = VOFPC_CELL_OK, it = 0;
+  double VP = 1.0, pmin = 0.0, pmax = 0.0;
+  bool have_field = false;
+  double s_out = __builtin_nan(""), A_out = 0, d_out = 0, n0 = 0, n1 = 0, n2 = 0, ag = a;
+  uint32_t ew[KE];   // the lane's edge records
+  uint32_t fl[KF];   // and its faces' loops: first position, positions << 16
+  if (active) {
+    if (!(a >= 0.0 && a <= 1.0)) {
+      st = VOFPC_CELL_BAD_INPUT;
+    } else if (!(a > p.eps && a < 1.0 - p.eps)) {
+      st = VOFPC_CELL_NOT_MIXED;
+    } else if (!Caps::fits(nv, nf, cell.nl)) {
+      st = VOFPC_CELL_BAD_INPUT;   // cannot happen: the launcher sizes the build by the class
+    } else {
+      const double xP0 = m.xc[P], xP1 = m.xc[N + P], xP2 = m.xc[2 * N + P];
+      VP = m.V[P];
+#pragma unroll
+      for (int t = 0; t < KE; ++t) {
+        const int e = q + t * G;
+        ew[t] = e < ne ? m.ce[(l0 >> 1) + e] : 0u;
+      }
+      uint8_t tl[KL], te[KL];
+#pragma unroll
+      for (int t = 0; t < KL; ++t) {
+        const int i = q + t * G;
+        tl[t] = i < cell.nl ? m.cl_lv[l0 + i] : (uint8_t)0;
+        te[t] = i < cell.nl ? (uint8_t)m.cl_eid[l0 + i] : (uint8_t)0;
+      }
+#pragma unroll
+      for (int t = 0; t < KF; ++t) {
+        const int f = q + t * G;
+        fl[t] = f < nf ? (uint32_t)m.cf_loff[f0 + f] | (uint32_t)m.cf_lsz[f0 + f] << 16 : 0u;
+      }
+      // the vertices with the inverse-distance vertex field, level by
+      // level (ids, positions and incidence ranges, incidences, neighbour
+      // alphas), so the latencies of a level's loads overlap
+      constexpr int KS = KV < 2 ? KV : 2;   // vertices per lane per round
+      double lo_phi = __builtin_inf(), hi_phi = -__builtin_inf();
+      stage_vertex_field<G, KS, true>(M, m, p, sl, q, v0, nv, xP0, xP1, xP2, lo_phi, hi_phi);
+#pragma unroll
+      for (int t = 0; t < KL; ++t) {
+        const int i = q + t * G;
+        if (i < cell.nl) {
+          M.lv[i][sl] = tl[t];
+          M.eid[i][sl] = te[t];
+        }
+      }
+      pmin = tmin<G>(lo_phi);
+      pmax = tmax<G>(hi_phi);
+      have_field = true;
+      wave_sync();
+      if (pmax - pmin <= 1e-12) {
+        // degenerate vertex field: linear alpha from the plain least-squares
+        // gradient over the interior face neighbours
+        st = VOFPC_CELL_DEGENERATE;
+        double gxx = 0, gyy = 0, gzz = 0, gxy = 0, gxz = 0, gyz = 0, b0 = 0, b1 = 0, b2 = 0;
+        for (int f = q; f < nf; f += G) {
+          const int qq = m.cf_nbr[f0 + f];
+          if (qq < 0) continue;
+          const double r0 = m.xc[qq] - xP0, r1 = m.xc[N + qq] - xP1, r2 = m.xc[2 * N + qq] - xP2;
+          const double dv = p.alpha[qq] - a;
+          gxx += r0 * r0; gyy += r1 * r1; gzz += r2 * r2; gxy += r0 * r1; gxz += r0 * r2; gyz += r1 * r2;
+          b0 += r0 * dv; b1 += r1 * dv; b2 += r2 * dv;
+        }
+        gxx = tsum<G>(gxx); gyy = tsum<G>(gyy); gzz = tsum<G>(gzz);
+        gxy = tsum<G>(gxy); gxz = tsum<G>(gxz); gyz = tsum<G>(gyz);
+        b0 = tsum<G>(b0); b1 = tsum<G>(b1); b2 = tsum<G>(b2);
+        const double c00 = gyy * gzz - gyz * gyz, c01 = gxz * gyz - gxy * gzz, c02 = gxy * gyz - gxz * gyy;
+        const double c11 = gxx * gzz - gxz * gxz, c12 = gxy * gxz - gxx * gyz, c22 = gxx * gyy - gxy * gxy;
+        const double det = gxx * c00 + gxy * c01 + gxz * c02;
+        const double tr = (gxx + gyy + gzz) / 3.0;
+        double g0 = 0, g1 = 0, g2 = 0;
+        if (det > 1e-12 * tr * tr * tr) {
+          g0 = (c00 * b0 + c01 * b1 + c02 * b2) / det;
+          g1 = (c01 * b0 + c11 * b1 + c12 * b2) / det;
+          g2 = (c02 * b0 + c12 * b1 + c22 * b2) / det;
+        }
+        lo_phi = __builtin_inf();
+        hi_phi = -__builtin_inf();
+        for (int i = q; i < nv; i += G) {
+          const double ph = a + (g0 * M.X[i][sl][0] + g1 * M.X[i][sl][1] + g2 * M.X[i][sl][2]);
+          M.phi[i][sl] = ph;
+          lo_phi = fmin(lo_phi, ph);
+          hi_phi = fmax(hi_phi, ph);
+        }
+        pmin = tmin<G>(lo_phi);
+        pmax = tmax<G>(hi_phi);
+        if (pmax - pmin <= 1e-12) have_field = false;
+        wave_sync();
+      }
+    }
+  }
+  // ---- phase 2: the narrowed bracket of every cell with a vertex field,
+  // from the network or the caller
+  bool hint = false;
+  if constexpr (NET) {
+    double nlo = __builtin_nan(""), nhi = __builtin_nan("");   // none where the network does not run
+    if (active && have_field && st == VOFPC_CELL_OK) {         // degenerate fields skip the network
+      const double Wd = pmax - pmin;
+      cell_features<G, KF, KV>(M, sl, q, p, P, a, nv, nf, f0, pmin, Wd);
+      wave_sync();
+      float u;
+      if (cw == 1)
+        u = net_forward<64>(M.net.x[0], M.net.h[0], lane, p.net_wb, p.net_master);
+      else if (G == 4 && ts == 1)
+        u = net_forward<4>(M.net.x[sl], M.net.h[sl], q, p.net_wb, p.net_master);
+      else
+        u = net_forward<16>(M.net.x[lead], M.net.h[lead], lane & 15, p.net_wb, p.net_master);
+      if (!isnan(u)) {
+        const double uc = u < 0.f ? 0.0 : (u > 1.f ? 1.0 : (double)u);
+        const double sh = pmin + uc * Wd, dl = p.net_delta * Wd;
+        nlo = sh - dl;
+        nhi = sh + dl;
+        const double hl = nlo > pmin ? nlo : pmin, hh = nhi < pmax ? nhi : pmax;
+        hint = hl <= hh;
+        M.hint[0][sl] = sh < hl ? hl : (sh > hh ? hh : sh);
+        M.hint[1][sl] = hl;
+        M.hint[2][sl] = hh;
+      }
+    }
+    if (active && q == 0 && g == 0 && p.net_lo) {
+      p.net_lo[k] = nlo;
+      p.net_hi[k] = nhi;
+    }
+    wave_sync();
+  } else {
+    if (active && have_field && p.use_hint) {
+      double hl = p.hint_lo[k], hh = p.hint_hi[k];
+      if (!isnan(hl) && !isnan(hh)) {
+        hl = hl > pmin ? hl : pmin;
+        hh = hh < pmax ? hh : pmax;
+        hint = hl <= hh;
+        M.hint[0][sl] = hl + (hh - hl) / 2.0;
+        M.hint[1][sl] = hl;
+        M.hint[2][sl] = hh;
+      }
+    }
+  }
+  // ---- phase 3, per cell: registers of the search, the search, the outputs
+  if (active && have_field) {
+    // edges from their end of larger value u (liquid whenever the edge is
+    // cut) to v: values, 1/(phi_v - phi_u), and the whole-edge volume term
+    // of its two faces' fans, det(c1, u, v) + det(c2, v, u); the face whose
+    // loop runs u -> v takes the edge as an exit of the iso-curve, the other
+    // one as an entry.  Missing edges are never liquid and never cut.
+    double pu[KE], pv[KE], iv[KE], D[KE];
+    EM fo[KF], fi[KF];
+    int fc[KF];       // fan vertex of each face
+    double pw[KV];
+    VM adj[KV];
+    int rv;           // reference vertex of the loop sums
+    for (int f = q; f < nf; f += G) {
+      M.st.out[f][sl] = 0;
+      M.st.in[f][sl] = 0;
+      M.st.fan[f][sl] = 0xffffffffu;
+    }
+    for (int i = q; i < nv; i += G) M.st.adj[i][sl] = 0;
+    wave_sync();
+#pragma unroll
+    for (int t = 0; t < KE; ++t) {
+      const int e = q + t * G;
+      pu[t] = pv[t] = -__builtin_inf();
+      iv[t] = D[t] = 0.0;
+      if (e < ne) {
+        const uint32_t wv = ew[t];
+        int u = (int)(wv & 0xffu), v = (int)((wv >> 8) & 0xffu), f1 = (int)((wv >> 16) & 0xffu), f2 = (int)(wv >> 24);
+        pu[t] = M.phi[u][sl];
+        pv[t] = M.phi[v][sl];
+        if (pv[t] > pu[t]) {
+          const double x = pu[t];
+          pu[t] = pv[t];
+          pv[t] = x;
+          int i = u;
+          u = v;
+          v = i;
+          i = f1;
+          f1 = f2;
+          f2 = i;
+          ew[t] = (uint32_t)u | (uint32_t)v << 8 | (uint32_t)f1 << 16 | (uint32_t)f2 << 24;
+        }
+        iv[t] = qdiv(1.0, pv[t] - pu[t]);   // not used when the values are equal
+        or_lds(&M.st.out[f1][sl], (EM)1 << e);
+        or_lds(&M.st.in[f2][sl], (EM)1 << e);
+        or_lds(&M.st.adj[u][sl], (VM)1 << v);
+        or_lds(&M.st.adj[v][sl], (VM)1 << u);
+        const uint32_t lowv = (uint32_t)(u < v ? u : v);
+        atomicMin(&M.st.fan[f1][sl], lowv);
+        atomicMin(&M.st.fan[f2][sl], lowv);
+      }
+    }
+    wave_sync();
+#pragma unroll
+    for (int t = 0; t < KE; ++t) {
+      if (q + t * G >= ne) continue;
+      const double *c1 = M.X[M.st.fan[(ew[t] >> 16) & 0xffu][sl]][sl], *c2 = M.X[M.st.fan[ew[t] >> 24][sl]][sl];
+      const double *u = M.X[ew[t] & 0xffu][sl], *v = M.X[(ew[t] >> 8) & 0xffu][sl];
+      D[t] = det3(c1[0] - c2[0], c1[1] - c2[1], c1[2] - c2[2], u[0], u[1], u[2], v[0], v[1], v[2]);
+    }
+#pragma unroll
+    for (int t = 0; t < KF; ++t) {
+      const int f = q + t * G;
+      const bool in = f < nf;
+      fo[t] = in ? M.st.out[f][sl] : 0;
+      fi[t] = in ? M.st.in[f][sl] : 0;
+      fc[t] = in ? (int)M.st.fan[f][sl] : 0;
+    }
+    // reference point of the loop sums: the vertex of largest value when
+    // the cell is mostly vapour (a small liquid piece sits at it), else
+    // the vertex of smallest value (the smallest index among ties)
+    {
+      const double want = a < 0.5 ? pmax : pmin;
+      int cand = 0x7fffffff;
+#pragma unroll
+      for (int t = KV - 1; t >= 0; --t) {
+        const int i = q + t * G;
+        pw[t] = i < nv ? M.phi[i][sl] : -__builtin_inf();
+        adj[t] = i < nv ? M.st.adj[i][sl] : 0;
+        if (i < nv && pw[t] == want) cand = i;
+      }
+      rv = tmin_i<G>(cand);
+    }
+    wave_sync();   // the staging masks give way to the evaluations' points
+    const VM all = (VM)(~(VM)0) >> (8 * (int)sizeof(VM) - nv);
+    VM seen = 0;           // liquid vertices of the last flood fill
+    bool single = false;   // and whether it found one loop
+    uint32_t many = 0;     // the lane's faces with four or more crossings at the last evaluation (bit per slot)
+    const double far = 0.01 * (pmax - pmin);
+
+    // face-mean vertex value of the lane's face in slot t (vertex values
+    // added in loop order)
+    auto face_mean = [&](int t) {
+      const int o = (int)(fl[t] & 0xffffu), n = (int)(fl[t] >> 16);
+      double fm = 0.0;
+      for (int i = 0; i < n; ++i) fm += M.phi[M.lv[o + i][sl]][sl];
+      return fm / (double)n;
+    };
+    // One evaluation site; the phase decides where the next one is:
+    // the fixed isovalue, the centre of a narrowed bracket and then its
+    // end on the root's side, the search estimate, or the bracket end
+    // kept when the search cannot stop.
+    enum { kFixed, kHintMid, kHintUp, kHintDown, kStart, kSearch, kFinal };
+    const double iVP = 1.0 / VP;
+    const double tol = p.tol_rel * (a < 1.0 - a ? a : 1.0 - a);
+    // Brent's method (Brent 1973, ch. 4) on the residual r(s) = V(s)/V_P - alpha:
+    // xb is the bracket end of smaller |r|, xa the other end (before the
+    // start the lower and the upper end), xc the previous xb, xd the one
+    // before; the estimate is inverse quadratic interpolation through (xa,
+    // xb, xc) when the three residuals differ, else the secant through xa
+    // and xb, replaced by the midpoint when it falls outside the quarter of
+    // the bracket next to xb or does not shrink fast enough against the
+    // previous steps.
+    double xa = pmin, fa = 1.0 - a, xb = pmax, fb = -a, xc = 0, fcv = 0, xd = 0;
+    bool bis = true;
+    // a jump of V: where a face with four or more crossings switches its
+    // pairing (at its vertex-value mean) or a loop pinches at a vertex
+    // (at that vertex's value), V may step over alpha V_P and the search
+    // bisects down to two ulps.  From the second bisection step in a row
+    // on a bracket narrower than a hundredth of [phi_min, phi_max], such
+    // a value inside the bracket (the one nearest the bisection point)
+    // is cut instead, then the adjacent double on the root's side: a
+    // sign change between the two pins the bracket to one ulp (at most
+    // four tries per cell).
+    double xj = 0.0;
+    int jtries = 0, nbis = 0;   // nbis in a team: steps in a row that hardly lowered the residual
+    bool jnext = false, jpin = false, above = false;   // above: the last residual was positive
+    int ph = p.fixed_iso ? kFixed : (hint ? kHintMid : kStart);
+    double se;
+    while (true) {
+      if (ph >= kStart) {
+        if (ph == kStart && ts == 1) {
+          // the bracket [xa, xb] (full, or what the narrowed bracket's
+          // check left) starts the method
+          if (fabs(fa) < fabs(fb)) {
+            const double tx = xa, tf = fa;
+            xa = xb; fa = fb; xb = tx; fb = tf;
+          }
+          xc = xa; fcv = fa; xd = xa;
+          bis = true;
+          ph = kSearch;
+        }
+        const double big = fabs(xa) > fabs(xb) ? fabs(xa) : fabs(xb);
+        const bool collapsed = fabs(xb - xa) <= 2.0 * ulp_of(big);
+        if (collapsed || it >= p.max_iter) {
+          // no isovalue meets the tolerance: the end of smaller residual
+          const bool b = fabs(fb) <= fabs(fa) && !(ts > 1 && fabs(fa) == fabs(fb));
+          se = b ? xb : xa;
+          if (!collapsed) st = VOFPC_CELL_MAX_ITER;
+          else if (fabs(b ? fb : fa) > 1e-10) st = VOFPC_CELL_NO_ROOT;
+          ph = kFinal;
+        } else {
+          const double blo = fmin(xa, xb), bhi = fmax(xa, xb), w = bhi - blo;
+          const bool three = fa != fcv && fb != fcv;
+          const double sec = xb - fb * qdiv(xb - xa, fb - fa), mid = xa + (xb - xa) * 0.5;
+          const double qi = iqi1(xa, fa, xb, fb, xc, fcv);
+          bool look = false;
+          if (ts == 1) {
+            if (jnext) {
+              // the double next to the tried value, on the root's side
+              jnext = false;
+              se = above ? next_up(xj) : -next_up(-xj);
+            }
+            if (!(jpin && se > blo && se < bhi)) {
+              se = three ? qi : sec;
+              const double q0 = (3.0 * xa + xb) * 0.25;
+              const bool inside = q0 < xb ? (se > q0 && se < xb) : (se > xb && se < q0);
+              const double du = 4.0 * ulp_of(xb);
+              const double lastd = bis ? fabs(xb - xc) : fabs(xc - xd);
+              bis = !inside || fabs(se - xb) >= 0.5 * lastd || lastd < du;
+              if (bis) se = mid;
+              nbis = bis ? nbis + 1 : 0;
+              look = nbis >= 2 && it > 0;
+            }
+            jpin = false;
+          } else {
+            // a team's isovalues: the estimate; pairs of points around it at
+            // distances spread over the scale of its correction of the secant
+            // (a sixteenth of it with four isovalues, 8 times it down to a
+            // 4096th with sixteen); and points that divide the bracket evenly,
+            // in place of those that fall outside it, and of all but the
+            // estimate after a step that hardly lowered the residual
+            double e0 = ph != kStart && three ? qi : sec;
+            if (!(e0 > blo && e0 < bhi)) e0 = sec;
+            if (!(e0 > blo && e0 < bhi)) e0 = mid;
+            const int pairs = ts == 4 ? 1 : 6;
+            const double du = 16.0 * ulp_of(e0);
+            double d = ldexp(fabs(e0 - sec), ts == 4 ? -4 : 3 - 3 * ((g - 1) >> 1));
+            d = d > du ? d : du;
+            const bool even = ph == kStart || nbis >= 1;
+            se = g == 0 ? e0 : ((g & 1) ? e0 - d : e0 + d);
+            const double part = ph == kStart ? (double)(g + 1) / (double)(ts + 1)
+                                : (even || g <= 2 * pairs) ? (double)g / (double)ts
+                                                           : (double)(g - 2 * pairs) / (double)(ts - 2 * pairs);
+            if (ph == kStart || (even && g > 0) || g > 2 * pairs || !(se > blo && se < bhi)) se = blo + w * part;
+            look = nbis >= 2;
+            ph = kSearch;
+          }
+          if (look && jtries < 4 && w <= far) {
+            // candidates: the means of the faces with four or more
+            // crossings at the last evaluation, and the vertex values
+            double bd = __builtin_inf(), bv = __builtin_inf();
+            auto candidate = [&](double sj) {
+              const double d = fabs(sj - mid);
+              if (sj > blo && sj < bhi && sj != xj && (d < bd || (d == bd && sj < bv))) {
+                bd = d;
+                bv = sj;
+              }
+            };
+#pragma unroll
+            for (int t = 0; t < KF; ++t)
+              if ((many >> t) & 1) candidate(face_mean(t));
+#pragma unroll
+            for (int t = 0; t < KV; ++t)
+              if (q + t * G < nv) candidate(pw[t]);
+            double bdm = tmin<G>(bd);
+            double cj = tmin<G>(bd == bdm ? bv : __builtin_inf());
+            if (ts > 1) {
+              // (the groups' last cuts, and so their face means, differ)
+              if (q == 0) {
+                M.smp[0][sl] = cj;
+                M.smp[1][sl] = bdm;
+              }
+              wave_sync();
+              const int i = lead + (lane & (ts - 1));
+              bd = M.smp[1][i];
+              bv = M.smp[0][i];
+              bdm = tmin<16>(bd);
+              cj = tmin<16>(bd == bdm ? bv : __builtin_inf());
+              wave_sync();
+            }
+            if (cj < __builtin_inf()) {
+              if (ts == 1 || g == 0) se = cj;
+              if (ts > 1 && g == 1) se = next_up(cj);
+              if (ts > 1 && g == 2) se = -next_up(-cj);
+              xj = cj;
+              jnext = jpin = ts == 1;
+              ++jtries;
+            }
+          }
+        }
+      } else if (ph == kFixed) {
+        se = p.iso;
+      } else if (ts == 1) {
+        se = M.hint[ph == kHintMid ? 0 : (ph == kHintUp ? 2 : 1)][sl];
+      } else {
+        // a team checks the narrowed bracket in one step: its first cut and
+        // both ends, and points inside it
+        const double hl = M.hint[1][sl], hh = M.hint[2][sl];
+        se = g < 3 ? M.hint[g][sl] : hl + (hh - hl) * ((double)(g - 2) / (double)(ts - 2));
+      }
+      // ---- the evaluation at se: edges
+      double vf = 0.0;
+      EM cut = 0;
+#pragma unroll
+      for (int t = 0; t < KE; ++t) {
+        const bool lv = pv[t] >= se, c = pu[t] >= se && !lv;
+        const double lam = (se - pu[t]) * iv[t];
+        vf = fma(lv ? 1.0 : (c ? lam : 0.0), D[t], vf);
+        if (c) {
+          const double *u = M.X[ew[t] & 0xffu][sl], *v = M.X[(ew[t] >> 8) & 0xffu][sl];
+          double *x = M.ev.pt[q + t * G][sl];
+          const double u0 = u[0], u1 = u[1], u2 = u[2];
+          x[0] = u0 + lam * (v[0] - u0);
+          x[1] = u1 + lam * (v[1] - u1);
+          x[2] = u2 + lam * (v[2] - u2);
+        }
+        cut |= (EM)group_bits<G>(c, base) << (t * G);
+      }
+      // one loop or several: flood fill when the liquid vertices changed
+      VM lm = 0;
+#pragma unroll
+      for (int t = 0; t < KV; ++t) lm |= (VM)group_bits<G>(pw[t] >= se, base) << (t * G);
+      lm &= all;
+      if (__any(lm != seen)) {
+        const VM vm = ~lm & all;
+        VM r = (lm & (~lm + 1)) | (vm & (~vm + 1));
+        bool grow = true;
+        while (__any(grow)) {
+          VM nr = r;
+#pragma unroll
+          for (int t = 0; t < KV; ++t) {
+            const VM same = pw[t] >= se ? lm : vm;
+            nr |= (VM)group_bits<G>((adj[t] & same & r) != 0, base) << (t * G);
+          }
+          grow = nr != r;
+          r = nr;
+        }
+        single = r == all;
+        seen = lm;
+      }
+      wave_sync();
+      // faces with one chord
+      ChordAcc acc{0, 0, 0, 0, 0, 0, 0};
+      const double r0 = M.X[rv][sl][0], r1 = M.X[rv][sl][1], r2 = M.X[rv][sl][2];
+      many = 0;
+#pragma unroll
+      for (int t = 0; t < KF; ++t) {
+        const EM ex = cut & fo[t], en = cut & fi[t];
+        if ((ex | en) == 0) continue;
+        if (ex == 0 || en == 0 || ((ex & (ex - 1)) | (en & (en - 1))) != 0) {
+          many |= 1u << t;
+          continue;
+        }
+        const double *xe = M.ev.pt[first_bit(ex)][sl], *ee = M.ev.pt[first_bit(en)][sl];
+        const double *c = M.X[fc[t]][sl];
+        const double x0 = xe[0], x1 = xe[1], x2 = xe[2], e0 = ee[0], e1 = ee[1], e2 = ee[2];
+        vf += det3(c[0], c[1], c[2], x0, x1, x2, e0, e1, e2);
+        add_segment(acc, r0, r1, r2, x0, x1, x2, e0, e1, e2);
+      }
+      bool bad = false;
+      const bool one = single && group_bits<G>(many != 0, base) == 0;
+      double Vi = 0.0;
+      if (one) {
+        vf = tsum<G>(vf);
+        reduce_acc<G>(acc);
+        double k0, k1, k2;
+        loop_centre(acc, r0, r1, r2, k0, k1, k2);
+        Vi = k0 * acc.Y0 + k1 * acc.Y1 + k2 * acc.Y2;
+      } else {
+        // several loops: the chords' entry edges by exit edge, and the
+        // volume terms that the faces with several chords still owe
+#pragma unroll
+        for (int t = 0; t < KF; ++t) {
+          const EM ex = cut & fo[t], en = cut & fi[t];
+          if ((ex | en) == 0) continue;
+          if (count_bits(ex) != count_bits(en)) {
+            bad = true;   // a closed loop alternates exits and entries
+          } else if (((many >> t) & 1) == 0) {
+            M.ev.part[first_bit(ex)][sl] = (uint8_t)first_bit(en);
+          } else {
+            // exits and entries as bits over the loop's positions; each exit
+            // goes with the next entry or the previous one
+            const bool conn = face_mean(t) >= se;
+            const int o = (int)(fl[t] & 0xffffu), n = (int)(fl[t] >> 16);
+            uint64_t xb = 0, nb = 0;
+            for (int i = 0; i < n; ++i) {
+              const int e = M.eid[o + i][sl];
+              xb |= (uint64_t)((ex >> e) & 1) << i;
+              nb |= (uint64_t)((en >> e) & 1) << i;
+            }
+            const double *c = M.X[fc[t]][sl];
+            for (uint64_t left = xb; left != 0; left &= left - 1) {
+              const int i = first_bit(left);
+              const uint64_t after = i == 63 ? 0 : nb >> (i + 1) << (i + 1), before = nb & ~after;
+              const int r = conn ? first_bit(after ? after : nb) : 63 - __clzll((long long)(before ? before : nb));
+              const int e = M.eid[o + i][sl], er = M.eid[o + r][sl];
+              M.ev.part[e][sl] = (uint8_t)er;
+              const double *xe = M.ev.pt[e][sl], *x = M.ev.pt[er][sl];
+              vf += det3(c[0], c[1], c[2], xe[0], xe[1], xe[2], x[0], x[1], x[2]);
+            }
+          }
+        }
+        bad = group_bits<G>(bad, base) != 0;
+        vf = tsum<G>(vf);
+        wave_sync();
+        // label the loops by following the chords, then add up each loop
+        int nloop = 0;
+        for (EM left = cut; left != 0 && !bad; ++nloop) {
+          const int t0 = first_bit(left);
+          int u = t0;
+          do {
+            M.ev.lab[u][sl] = (uint8_t)nloop;
+            left &= ~((EM)1 << u);
+            u = M.ev.part[u][sl];
+          } while ((left >> u) & 1);
+          bad = u != t0;
+        }
+        wave_sync();
+        double S0 = 0, S1 = 0, S2 = 0, A = 0, cw0 = 0, cw1 = 0, cw2 = 0;
+        for (int lp = 0; lp < nloop && !bad; ++lp) {
+          acc = ChordAcc{0, 0, 0, 0, 0, 0, 0};
+          for (int e = q; e < ne; e += G) {
+            if (!((cut >> e) & 1) || M.ev.lab[e][sl] != lp) continue;
+            const double *xe = M.ev.pt[e][sl], *en = M.ev.pt[M.ev.part[e][sl]][sl];
+            add_segment(acc, r0, r1, r2, xe[0], xe[1], xe[2], en[0], en[1], en[2]);
+          }
+          reduce_acc<G>(acc);
+          finish_loop(acc, r0, r1, r2, Vi, S0, S1, S2, A, cw0, cw1, cw2);
+        }
+        M.fin[1][sl] = S0; M.fin[2][sl] = S1; M.fin[3][sl] = S2;
+        M.fin[4][sl] = A;
+        M.fin[5][sl] = cw0; M.fin[6][sl] = cw1; M.fin[7][sl] = cw2;
+      }
+      wave_sync();
+      // the liquid fraction, V / V_P by the reciprocal and one correction
+      // (the value reported is the one the tolerance was tested on)
+      const double V = (vf + Vi) * (1.0 / 6.0);
+      double frac = V * iVP;
+      frac = fma(fma(-VP, frac, V), iVP, frac);
+      it += tm.weight;
+      const double r = frac - a;
+      bool done = ph == kFixed || ph == kFinal;
+      int win = g;   // the group whose cut ends the search
+      if (ts == 1) {
+        done = done || fabs(r) <= tol;
+      } else {
+        if (q == 0) {
+          M.smp[0][sl] = se;
+          M.smp[1][sl] = r;
+        }
+        wave_sync();
+        // sample i of the team on the lanes i, i + ts, ... of every row
+        const int i = lane & (ts - 1);
+        const double sx = M.smp[0][lead + i], sr = M.smp[1][lead + i], ar = fabs(sr);
+        if (done) {
+          win = 0;
+        } else {
+          if (ph == kHintMid) {
+            // the residual at the first cut tells the side of the root; the
+            // bracket holds when its end on that side is past the root
+            const double rm = M.smp[1][lead];
+            const int end = rm > 0 ? 2 : 1;
+            const double re = M.smp[1][lead + end];
+            if (fabs(rm) <= tol || fabs(re) <= tol) {
+              done = true;
+              win = fabs(rm) <= tol ? 0 : end;
+            } else if (!(rm > 0 ? re < 0 : re > 0) && st == VOFPC_CELL_OK) {
+              st = VOFPC_CELL_LEARNED_FALLBACK;
+            }
+          }
+          if (!done) {
+            const double m1 = tmin<16>(ar);
+            done = m1 <= tol;
+            win = tmin_i<16>(ar == m1 ? i : ts);
+          }
+        }
+        if (!done) {
+          // the tightest sign change becomes the bracket [xa, xb]; the third
+          // point of the estimate is the one of smallest residual off it
+          const double inf = __builtin_inf();
+          const double plo = xa, pfl = fa, phi_ = xb, pfh = fb;
+          const bool pos = sr > 0 && sx > plo && sx < phi_;
+          const double slo = tmax<16>(pos ? sx : -inf);
+          if (slo > plo) {
+            fa = tmin<16>(pos && sx == slo ? sr : inf);
+            xa = slo;
+          }
+          const bool neg = !(sr > 0) && sx > xa && sx < phi_;
+          const double shi = tmin<16>(neg ? sx : inf);
+          if (shi < phi_) {
+            fb = tmax<16>(neg && sx == shi ? sr : -inf);
+            xb = shi;
+          }
+          const bool off = sx != xa && sx != xb;
+          double m3 = tmin<16>(off ? ar : inf);
+          if (m3 < inf) {
+            xc = tmin<16>(off && ar == m3 ? sx : inf);
+            fcv = tmin<16>(off && sx == xc ? sr : inf);
+          }
+          if (xa != plo && fabs(pfl) < m3) {
+            m3 = fabs(pfl);
+            xc = plo; fcv = pfl;
+          }
+          if (xb != phi_ && fabs(pfh) < m3) {
+            xc = phi_; fcv = pfh;
+          }
+          nbis = fmin(fabs(fa), fabs(fb)) > 0.25 * fmin(fabs(pfl), fabs(pfh)) ? nbis + 1 : 0;
+          if (ph == kHintMid) {
+            nbis = 0;
+            ph = kSearch;
+          }
+          wave_sync();
+          continue;
+        }
+      }
+      if (done) {
+        // the cut that ends the search, in the slot of the cell's first group
+        if (one) {
+          double vi = 0.0, S0 = 0, S1 = 0, S2 = 0, A = 0, cw0 = 0, cw1 = 0, cw2 = 0;
+          finish_loop(acc, r0, r1, r2, vi, S0, S1, S2, A, cw0, cw1, cw2);
+          M.fin[1][sl] = S0; M.fin[2][sl] = S1; M.fin[3][sl] = S2;
+          M.fin[4][sl] = A;
+          M.fin[5][sl] = cw0; M.fin[6][sl] = cw1; M.fin[7][sl] = cw2;
+        }
+        M.fin[0][sl] = frac;
+        M.fin[8][sl] = bad ? 1.0 : 0.0;
+        wave_sync();
+        if (ts > 1) {
+          se = M.smp[0][lead + win];
+          if (g == win && g != 0)
+            for (int i = q; i < 9; i += G) M.fin[i][lead] = M.fin[i][sl];
+          wave_sync();
+        }
+        break;
+      }
+      if (ph < kStart) {
+        if (ph == kHintMid) {
+          // the residual at the centre tells the side of the root: that
+          // half of the bracket is checked by a cut at its end (which is
+          // the centre itself when the root lies beyond it)
+          const bool end = M.hint[r > 0 ? 2 : 1][sl] == se;
+          if (end && st == VOFPC_CELL_OK) st = VOFPC_CELL_LEARNED_FALLBACK;
+          ph = end ? kStart : (r > 0 ? kHintUp : kHintDown);
+        } else {
+          // the bracket holds when its end is past the root; otherwise the
+          // root lies beyond that end
+          if (!(ph == kHintUp ? r < 0 : r > 0) && st == VOFPC_CELL_OK) st = VOFPC_CELL_LEARNED_FALLBACK;
+          ph = kStart;
+        }
+        if (r > 0) {
+          xa = se; fa = r;
+        } else {
+          xb = se; fb = r;
+        }
+        continue;
+      }
+      // keep the end across the root from the estimate; xb the end of
+      // smaller residual
+      above = r > 0;
+      xd = xc;
+      xc = xb; fcv = fb;
+      if ((fa > 0) != above) {
+        xb = se; fb = r;
+      } else {
+        xa = se; fa = r;
+      }
+      if (fabs(fa) < fabs(fb)) {
+        const double tx = xa, tf = fa;
+        xa = xb; fa = fb; xb = tx; fb = tf;
+      }
+    }
+    if (M.fin[8][lead] != 0.0) {
+      st = VOFPC_CELL_BAD_INPUT;
+    } else {
+      s_out = se;
+      ag = M.fin[0][lead];
+      A_out = M.fin[4][lead];
+      const double S0 = M.fin[1][lead], S1 = M.fin[2][lead], S2 = M.fin[3][lead];
+      const double Sm = sqrt(S0 * S0 + S1 * S1 + S2 * S2);
+      if (Sm > 0) {
+        n0 = S0 / Sm; n1 = S1 / Sm; n2 = S2 / Sm;
+        d_out = -(n0 * M.fin[5][lead] + n1 * M.fin[6][lead] + n2 * M.fin[7][lead]) / A_out;
+      }
+    }
+  }
+  if (active && q == 0 && g == 0) {
+    if (p.mf.gradT) {
+      // mass transfer of the entry (one-sided form, as vofpc_mass_transfer)
+      double md = 0.0;
+      if (A_out > 0.0) {
+        const double gn = p.mf.gradT[P] * n0 + p.mf.gradT[N + P] * n1 + p.mf.gradT[2 * N + P] * n2;
+        const double gl = (a >= 0.5) ? gn : 0.0, gv = (a >= 0.5) ? 0.0 : gn;
+        const double ql = p.mf.k_l * gl * A_out;
+        const double qv = -p.mf.k_v * gv * A_out;
+        md = (ql + qv) / (p.mf.h_lv * m.V[P]);
+      }
+      p.mf.mdot[k] = md;
+      p.mf.Qdot[k] = -md * p.mf.h_lv;
+    }
+    p.out.s[k] = s_out;
+    p.out.n[k] = n0; p.out.n[cap + k] = n1; p.out.n[2 * cap + k] = n2;
+    p.out.A[k] = A_out;
+    p.out.d[k] = d_out;
+    p.out.alpha_got[k] = ag;
+    p.out.status[k] = st;
+    p.out.iters[k] = it;
+  }
+}
+
+// A wavefront's groups work as teams while every cell still gets a wavefront,
+// or a team of four groups a quarter of one, in this many rounds: a step of a
+// team costs what a step of one cell does, and the groups it joins had no
+// cells of their own.  On a launch of 2,048 wavefronts, whole plain steps:
+// 2,832 Voronoi cells 106 us in two rounds of teams, 123 us without; 3,342
+// cells 109 and 168 us; 5,000 hexahedra in teams of four 62 us, 79 us without,
+// 107 us in teams of sixteen (three rounds); 226 hexahedra in teams of
+// sixteen 45 us, 71 us without.
+constexpr int kTeamWaves = 2;
+
+// Waves per SIMD a build's register budget is sized for: at most 2 (256
+// VGPRs).  A third one leaves 168 VGPRs and spills in the search: 24,042
+// Voronoi cells reconstructed in 224 us against 202 us, 31,948 hexahedra in
+// 159 against 146 us.
+constexpr int group_occupancy(int bytes) {
+  const int w = (160 * 1024) / bytes / 4;
+  return w >= 2 ? 2 : 1;
+}
+
+// LDS of a wavefront: the larger of the builds it runs (Big: void for one).
+template <class Main, class Big>
+struct WaveMem {
+  union {
+    typename Main::Mem a;
+    typename Big::Mem b;
+  };
+};
+template <class Main>
+struct WaveMem<Main, void> {
+  typename Main::Mem a;
+};
+
+// The cells of a launch.  With Big, cells that do not fit Main are solved by
+// the wavefront that meets them in the Big build, after its other cells.
+template <class Main, class Big, bool NET>
+__global__ __launch_bounds__(64, (group_occupancy((int)sizeof(WaveMem<Main, Big>))))
+void recon_group_kernel(ReconParams p) {
+  constexpr int G = Main::G, C = 64 / G;
+  __shared__ WaveMem<Main, Big> M;
+  const DevMesh &m = p.m;
   int64_t count = p.entries ? (int64_t)*p.entry_count : (int64_t)p.counts[0];
-  if (count > cap) count = cap;
-  const int64_t nbatch = (count + C - 1) / C;
-  // this XCD's batches (runs of kRunCells cells): the first one per
-  // workgroup by its index, the rest claimed from the XCD's counter
+  if (count > p.out.cap) count = p.out.cap;
+  Team tm;
+  tm.lane = threadIdx.x;
+  tm.sl = tm.lane / G;
+  tm.q = tm.lane % G;
+  tm.base = tm.lane & ~(G - 1);
+  // cells per batch, cw, and groups per cell, ts: with few cells the groups
+  // of a wavefront form teams that cut one cell at ts isovalues per step
+  tm.cw = C;
+  if (count <= (int64_t)kTeamWaves * gridDim.x) tm.cw = 1;
+  else if (C == 16 && count <= (int64_t)4 * kTeamWaves * gridDim.x) tm.cw = 4;
+  tm.ts = C / tm.cw;
+  tm.g = tm.sl & (tm.ts - 1);
+  tm.lead = tm.sl - tm.g;
+  // a step of 4 or 16 isovalues narrows the bracket as 2 or 4 halvings do and
+  // counts as that many evaluations
+  tm.weight = tm.ts == 16 ? 4 : (tm.ts == 4 ? 2 : 1);
+  const int64_t nbatch = (count + tm.cw - 1) / tm.cw;
+  // this XCD's batches (runs of kRunCells cells for full batches): the first
+  // one per workgroup by its index, the rest claimed from the XCD's counter
   constexpr int kRun = kRunCells / C;
   const int xcd = (int)(blockIdx.x % kXcd);
   const int64_t nx = xcd_count<kRun>(nbatch, xcd);
   const int64_t wx = ((int64_t)gridDim.x - xcd + kXcd - 1) / kXcd;
   unsigned int *claim = reinterpret_cast<unsigned int *>(p.queue + (1 + xcd) * kQueueStride);
   for (int64_t ix = blockIdx.x / kXcd; ix < nx;) {
-    const int64_t bt = xcd_batch<kRun>(ix, xcd);
-    const int64_t j = bt * C + sl;
+    const int64_t j = xcd_batch<kRun>(ix, xcd) * tm.cw + tm.sl / tm.ts;
     const bool active = j < count;
-    // ---- phase 1, per cell: checks and staging
-    int64_t k = 0, f0 = 0;
-    int P = 0, nf = 0, nv = 0, nl = 0, ne = 0, st = VOFPC_CELL_OK, it = 0;
-    double a = 0.0, VP = 1.0, pmin = 0.0, pmax = 0.0;
-    bool have_field = false;
-    double s_out = __builtin_nan(""), A_out = 0, d_out = 0, n0 = 0, n1 = 0, n2 = 0, ag = 0.0;
+    CellRef cell;
     if (active) {
-      k = p.entries ? (int64_t)p.entries[j] : j;
-      P = p.mixed[k];
-      a = p.alpha[P];
-      ag = a;
-      f0 = m.cell_face_off[P];
-      nf = (int)(m.cell_face_off[P + 1] - f0);
-      const int64_t v0 = m.cv_off[P];
-      nv = (int)(m.cv_off[P + 1] - v0);
-      const int64_t l0 = m.cl_off[P];
-      nl = (int)(m.cl_off[P + 1] - l0);
-      ne = nl / 2;   // a closed surface uses every edge twice
-      if (!(a >= 0.0 && a <= 1.0)) {
-        st = VOFPC_CELL_BAD_INPUT;
-      } else if (!(a > p.eps && a < 1.0 - p.eps)) {
-        st = VOFPC_CELL_NOT_MIXED;
-      } else if (nv > NV || nf > NF || nl > NL || ne > NE) {
-        st = VOFPC_CELL_BAD_INPUT;   // cannot happen: the launcher sizes the build by the class
-      } else {
-        const double xP0 = m.xc[P], xP1 = m.xc[N + P], xP2 = m.xc[2 * N + P];
-        VP = m.V[P];
-        // ---- stage the polyhedron: loop positions, face offsets and edges,
-        // and the vertices with the inverse-distance vertex field.  The
-        // loads of each part are issued together (topology into registers
-        // first, then the vertices level by level: ids, positions and
-        // incidence ranges, incidences, neighbour alphas), so their
-        // latencies overlap instead of adding up.
-        // (builds whose topology takes more than 40 registers per lane store
-        // it straight to LDS after the vertices instead)
-        constexpr int KL = (NL + G - 1) / G, KF = (NF + G - 1) / G, KE = (NE + G - 1) / G;
-        constexpr bool kPre = 2 * KL + 2 * KF + KE <= 40;
-        constexpr int KV = (NV + G - 1) / G < 2 ? (NV + G - 1) / G : 2;   // vertices per lane per round
-        uint8_t tl[kPre ? KL : 1], te[kPre ? KL : 1], tfo[kPre ? KF : 1], tfs[kPre ? KF : 1];
-        uint32_t tw[kPre ? KE : 1];
-        if constexpr (kPre) {
-#pragma unroll
-        for (int t = 0; t < KL; ++t) {
-          const int i = q + t * G;
-          tl[t] = i < nl ? m.cl_lv[l0 + i] : (uint8_t)0;
-          te[t] = i < nl ? (uint8_t)m.cl_eid[l0 + i] : (uint8_t)0;
-        }
-#pragma unroll
-        for (int t = 0; t < KF; ++t) {
-          const int f = q + t * G;
-          tfo[t] = f < nf ? (uint8_t)m.cf_loff[f0 + f] : (uint8_t)0;
-          tfs[t] = f < nf ? m.cf_lsz[f0 + f] : (uint8_t)0;
-        }
-#pragma unroll
-        for (int t = 0; t < KE; ++t) {
-          const int e = q + t * G;
-          tw[t] = e < ne ? m.ce[(l0 >> 1) + e] : 0u;
-        }
-        }
-        double lo_phi = __builtin_inf(), hi_phi = -__builtin_inf();
-        stage_vertex_field<G, KV, true>(M, m, p, sl, q, v0, nv, xP0, xP1, xP2, lo_phi, hi_phi);
-        if constexpr (kPre) {
-#pragma unroll
-          for (int t = 0; t < KL; ++t) {
-            const int i = q + t * G;
-            if (i < nl) {
-              M.lv[i][sl] = tl[t];
-              M.eid[i][sl] = te[t];
-            }
-          }
-#pragma unroll
-          for (int t = 0; t < KF; ++t) {
-            const int f = q + t * G;
-            if (f < nf) {
-              M.foff[f][sl] = tfo[t];
-              M.fsz[f][sl] = tfs[t];
-            }
-          }
-#pragma unroll
-          for (int t = 0; t < KE; ++t) {
-            const int e = q + t * G;
-            if (e < ne) {
-              const uint32_t wv = tw[t];
-              M.eu[e][sl] = (uint8_t)(wv & 0xffu);
-              M.ev[e][sl] = (uint8_t)((wv >> 8) & 0xffu);
-              M.ef1[e][sl] = (uint8_t)((wv >> 16) & 0xffu);
-              M.ef2[e][sl] = (uint8_t)(wv >> 24);
-            }
-          }
-        } else {
-          for (int i = q; i < nl; i += G) {
-            M.lv[i][sl] = m.cl_lv[l0 + i];
-            M.eid[i][sl] = (uint8_t)m.cl_eid[l0 + i];
-          }
-          for (int f = q; f < nf; f += G) {
-            M.foff[f][sl] = (uint8_t)m.cf_loff[f0 + f];
-            M.fsz[f][sl] = m.cf_lsz[f0 + f];
-          }
-          for (int e = q; e < ne; e += G) {
-            const uint32_t wv = m.ce[(l0 >> 1) + e];
-            M.eu[e][sl] = (uint8_t)(wv & 0xffu);
-            M.ev[e][sl] = (uint8_t)((wv >> 8) & 0xffu);
-            M.ef1[e][sl] = (uint8_t)((wv >> 16) & 0xffu);
-            M.ef2[e][sl] = (uint8_t)(wv >> 24);
-          }
-        }
-        wave_sync();
-        // the whole-edge volume term of each edge: its two faces' fan terms,
-        // det(c1, u, v) + det(c2, v, u) with c = the face's first vertex
-        for (int e = q; e < ne; e += G) {
-          const int u = M.eu[e][sl], v = M.ev[e][sl];
-          const int a1 = M.lv[M.foff[M.ef1[e][sl]][sl]][sl], a2 = M.lv[M.foff[M.ef2[e][sl]][sl]][sl];
-          const double d0 = M.X[0][a1][sl] - M.X[0][a2][sl], d1 = M.X[1][a1][sl] - M.X[1][a2][sl],
-                       d2 = M.X[2][a1][sl] - M.X[2][a2][sl];
-          M.D[e][sl] = det3(d0, d1, d2, M.X[0][u][sl], M.X[1][u][sl], M.X[2][u][sl], M.X[0][v][sl], M.X[1][v][sl],
-                            M.X[2][v][sl]);
-        }
-        pmin = tmin<G>(lo_phi);
-        pmax = tmax<G>(hi_phi);
-        have_field = true;
-        wave_sync();
-        if (pmax - pmin <= 1e-12) {
-          // degenerate vertex field: linear alpha from the plain least-squares
-          // gradient over the interior face neighbours
-          st = VOFPC_CELL_DEGENERATE;
-          double gxx = 0, gyy = 0, gzz = 0, gxy = 0, gxz = 0, gyz = 0, b0 = 0, b1 = 0, b2 = 0;
-          for (int f = q; f < nf; f += G) {
-            const int qq = m.cf_nbr[f0 + f];
-            if (qq < 0) continue;
-            const double r0 = m.xc[qq] - xP0, r1 = m.xc[N + qq] - xP1, r2 = m.xc[2 * N + qq] - xP2;
-            const double dv = p.alpha[qq] - a;
-            gxx += r0 * r0; gyy += r1 * r1; gzz += r2 * r2; gxy += r0 * r1; gxz += r0 * r2; gyz += r1 * r2;
-            b0 += r0 * dv; b1 += r1 * dv; b2 += r2 * dv;
-          }
-          gxx = tsum<G>(gxx); gyy = tsum<G>(gyy); gzz = tsum<G>(gzz);
-          gxy = tsum<G>(gxy); gxz = tsum<G>(gxz); gyz = tsum<G>(gyz);
-          b0 = tsum<G>(b0); b1 = tsum<G>(b1); b2 = tsum<G>(b2);
-          const double c00 = gyy * gzz - gyz * gyz, c01 = gxz * gyz - gxy * gzz, c02 = gxy * gyz - gxz * gyy;
-          const double c11 = gxx * gzz - gxz * gxz, c12 = gxy * gxz - gxx * gyz, c22 = gxx * gyy - gxy * gxy;
-          const double det = gxx * c00 + gxy * c01 + gxz * c02;
-          const double tr = (gxx + gyy + gzz) / 3.0;
-          double g0 = 0, g1 = 0, g2 = 0;
-          if (det > 1e-12 * tr * tr * tr) {
-            g0 = (c00 * b0 + c01 * b1 + c02 * b2) / det;
-            g1 = (c01 * b0 + c11 * b1 + c12 * b2) / det;
-            g2 = (c02 * b0 + c12 * b1 + c22 * b2) / det;
-          }
-          lo_phi = __builtin_inf();
-          hi_phi = -__builtin_inf();
-          for (int i = q; i < nv; i += G) {
-            const double ph = a + (g0 * M.X[0][i][sl] + g1 * M.X[1][i][sl] + g2 * M.X[2][i][sl]);
-            M.phi[i][sl] = ph;
-            lo_phi = fmin(lo_phi, ph);
-            hi_phi = fmax(hi_phi, ph);
-          }
-          pmin = tmin<G>(lo_phi);
-          pmax = tmax<G>(hi_phi);
-          if (pmax - pmin <= 1e-12) have_field = false;
-          wave_sync();
-        }
-      }
+      cell.k = p.entries ? (int64_t)p.entries[j] : j;
+      cell.P = p.mixed[cell.k];
+      cell.a = p.alpha[cell.P];
+      cell.f0 = m.cell_face_off[cell.P];
+      cell.nf = (int)(m.cell_face_off[cell.P + 1] - cell.f0);
+      cell.v0 = m.cv_off[cell.P];
+      cell.nv = (int)(m.cv_off[cell.P + 1] - cell.v0);
+      cell.l0 = m.cl_off[cell.P];
+      cell.nl = (int)(m.cl_off[cell.P + 1] - cell.l0);
     }
-    // ---- phase 2: the narrowed bracket of every cell with a vertex field,
-    // from the network (run on the wavefront's cells together) or the caller
-    double hl = 0.0, hh = 0.0, hm = 0.0;
-    bool hint = false;
-    if constexpr (NET) {
-      const bool row = active && have_field && st == VOFPC_CELL_OK;   // degenerate fields skip the network
-      // rows of a tile beyond the wavefront's cells are zero (the bytes are
-      // the evaluations' scratch in between)
-      for (int i = lane; i < (ThinNet<C>::R - C) * net::kIn; i += 64) T.x[C + i / net::kIn][i % net::kIn] = 0;
-      if (row) {
-        cell_features<G>(M, T, sl, q, p, P, a, nv, nf, f0, pmin, pmax - pmin);
-      } else {
-        for (int i = q; i < net::kIn; i += G) T.x[sl][i] = 0;
-      }
-      wave_sync();
-      net_tiles<C>(T, p.net_wb, p.net_master, lane);
-      if (row) {
-        const float u = T.u[sl];
-        if (!isnan(u)) {
-          const double Wd = pmax - pmin;
-          const double uc = u < 0.f ? 0.0 : (u > 1.f ? 1.0 : (double)u);
-          const double sh = pmin + uc * Wd, dl = p.net_delta * Wd;
-          hl = sh - dl;
-          hh = sh + dl;
-          if (q == 0 && p.net_lo) {
-            p.net_lo[k] = hl;
-            p.net_hi[k] = hh;
-          }
-          hl = hl > pmin ? hl : pmin;
-          hh = hh < pmax ? hh : pmax;
-          if (hl > hh) { hl = pmin; hh = pmax; }
-          hm = sh < hl ? hl : (sh > hh ? hh : sh);
-          hint = true;
-        } else if (q == 0 && p.net_lo) {
-          p.net_lo[k] = __builtin_nan("");
-          p.net_hi[k] = __builtin_nan("");
-        }
-      } else if (active && q == 0 && p.net_lo) {
-        p.net_lo[k] = __builtin_nan("");
-        p.net_hi[k] = __builtin_nan("");
-      }
-      wave_sync();
+    if constexpr (std::is_void_v<Big>) {
+      solve_cells<Main, NET>(p, M.a, tm, cell, active);
     } else {
-      if (active && have_field && p.use_hint) {
-        hl = p.hint_lo[k];
-        hh = p.hint_hi[k];
-        if (!isnan(hl) && !isnan(hh)) {
-          hl = hl > pmin ? hl : pmin;
-          hh = hh < pmax ? hh : pmax;
-          if (hl > hh) { hl = pmin; hh = pmax; }
-          hm = hl + (hh - hl) / 2.0;
-          hint = true;
-        }
-      }
-    }
-    // ---- phase 3, per cell: the search and the outputs
-    if (active) {
-        if (have_field) {
-          // reference point of the loop sums: the vertex of largest value when
-          // the cell is mostly vapour (a small liquid piece sits at it), else
-          // the vertex of smallest value (the smallest index among ties)
-          double ref[3];
-          {
-            const bool top = a < 0.5;
-            const double want = top ? pmax : pmin;
-            int cand = 0x7fffffff;
-            for (int i = q; i < nv; i += G)
-              if (M.phi[i][sl] == want && i < cand) cand = i;
-            cand = tmin_i<G>(cand);
-            ref[0] = M.X[0][cand][sl];
-            ref[1] = M.X[1][cand][sl];
-            ref[2] = M.X[2][cand][sl];
-          }
-          // One evaluation site; the phase decides where the next one is:
-          // the fixed isovalue, the centre of a narrowed bracket and then its
-          // end on the root's side, the search estimate, or the bracket end
-          // kept when the search cannot stop.
-          enum { kFixed, kHintMid, kHintEnd, kSearch, kFinal };
-          CutRes c;
-          c.err = false;
-          double s = __builtin_nan("");
-          double lo = pmin, hi = pmax, rlo = 1.0 - a, rhi = -a, rm = 0.0;
-          const double iVP = 1.0 / VP;
-          const double tol = p.tol_rel * (a < 1.0 - a ? a : 1.0 - a);
-          // Brent's method (Brent 1973, ch. 4) on the residual r(s) = V(s)/V_P - alpha:
-          // xb is the bracket end of smaller |r|, xa the other end, xc the
-          // previous xb, xd the one before; the estimate is inverse quadratic
-          // interpolation through (xa, xb, xc) when the three residuals differ,
-          // else the secant through xa and xb, replaced by the midpoint when it
-          // falls outside the quarter of the bracket next to xb or does not
-          // shrink fast enough against the previous steps.
-          double xa = 0, fa = 0, xb = 0, fb = 0, xc = 0, fc = 0, xd = 0;
-          bool bis = true, started = false, collapsed = false;
-          // a jump of V: where a face with four or more crossings switches its
-          // pairing (at its vertex-value mean) or a loop pinches at a vertex
-          // (at that vertex's value), V may step over alpha V_P and the search
-          // bisects down to two ulps.  From the second bisection step in a row
-          // on a bracket narrower than a hundredth of [phi_min, phi_max], such
-          // a value inside the bracket (the one nearest the bisection point)
-          // is cut instead, then the adjacent double on the root's side: a
-          // sign change between the two pins the bracket to one ulp (at most
-          // four tries per cell).
-          double xj = 0.0, rlast = 0.0;
-          int jtries = 0, nbis = 0;
-          bool jnext = false;
-          int ph = p.fixed_iso ? kFixed : (hint ? kHintMid : kSearch);
-          while (true) {
-            double se = 0.0;
-            if (ph == kSearch) {
-              if (!started) {
-                // the bracket [lo, hi] (full, or what the narrowed bracket's
-                // check left) starts the method
-                xa = lo; fa = rlo; xb = hi; fb = rhi;
-                if (fabs(fa) < fabs(fb)) {
-                  xa = hi; fa = rhi; xb = lo; fb = rlo;
-                }
-                xc = xa; fc = fa; xd = xa;
-                bis = true;
-                started = true;
-              }
-              const double big = fabs(xa) > fabs(xb) ? fabs(xa) : fabs(xb);
-              if (fabs(xb - xa) <= 2.0 * ulp_of(big)) {
-                collapsed = true;
-                ph = kFinal;
-              } else if (it >= p.max_iter) {
-                st = VOFPC_CELL_MAX_ITER;
-                ph = kFinal;
-              } else {
-                const double blo = xa < xb ? xa : xb, bhi = xa < xb ? xb : xa;
-                bool pinned = false;
-                if (jnext) {
-                  // the double next to the tried face mean, on the root's side
-                  jnext = false;
-                  const double nb = rlast > 0 ? nextafter(xj, __builtin_inf()) : nextafter(xj, -__builtin_inf());
-                  if (nb > blo && nb < bhi) {
-                    se = nb;
-                    pinned = true;
-                  }
-                }
-                if (!pinned) {
-                  if (fa != fc && fb != fc) se = iqi1(xa, fa, xb, fb, xc, fc);
-                  else se = xb - fb * qdiv(xb - xa, fb - fa);
-                  const double q0 = (3.0 * xa + xb) * 0.25;
-                  const bool inside = q0 < xb ? (se > q0 && se < xb) : (se > xb && se < q0);
-                  const double du = 4.0 * ulp_of(xb);
-                  const double lastd = bis ? fabs(xb - xc) : fabs(xc - xd);
-                  if (!inside || fabs(se - xb) >= 0.5 * lastd || lastd < du) {
-                    se = xa + (xb - xa) * 0.5;
-                    bis = true;
-                  } else {
-                    bis = false;
-                  }
-                  nbis = bis ? nbis + 1 : 0;
-                  if (nbis >= 2 && it > 0 && jtries < 4 && bhi - blo <= 0.01 * (pmax - pmin)) {
-                    // candidates: the means of the faces with four or more
-                    // crossings at the last evaluation, and the vertex values
-                    const double mid = se;
-                    double bd = __builtin_inf(), bv = __builtin_inf();
-                    for (int f = q; f < nf; f += G) {
-                      if (M.cnt[f][sl] < 4) continue;
-                      const int o = M.foff[f][sl], n = M.fsz[f][sl];
-                      double fm = 0.0;
-                      for (int k2 = 0; k2 < n; ++k2) fm += M.phi[M.lv[o + k2][sl]][sl];
-                      const double sj = fm / (double)n;
-                      const double d = fabs(sj - mid);
-                      if (sj > blo && sj < bhi && sj != xj && (d < bd || (d == bd && sj < bv))) {
-                        bd = d;
-                        bv = sj;
-                      }
-                    }
-                    for (int i = q; i < nv; i += G) {
-                      const double sj = M.phi[i][sl];
-                      const double d = fabs(sj - mid);
-                      if (sj > blo && sj < bhi && sj != xj && (d < bd || (d == bd && sj < bv))) {
-                        bd = d;
-                        bv = sj;
-                      }
-                    }
-                    const double bdm = tmin<G>(bd);
-                    const double cj = tmin<G>(bd == bdm ? bv : __builtin_inf());
-                    if (cj < __builtin_inf()) {
-                      se = cj;
-                      xj = cj;
-                      jnext = true;
-                      ++jtries;
-                    }
-                  }
-                }
-              }
-            }
-            if (ph == kFinal) {
-              se = xb;
-            } else if (ph == kFixed) {
-              se = p.iso;
-            } else if (ph == kHintMid) {
-              se = hm;
-            } else if (ph == kHintEnd) {
-              se = rm > 0 ? hh : hl;
-            }
-            const CutRes cf = thin_eval<G>(M, sl, q, nf, ne, se, ref);
-            ++it;
-            const double r = cf.V * iVP - a;
-            if (ph == kFixed || ph == kFinal || fabs(r) <= tol) {
-              s = se;
-              c = cf;
-              if (ph == kFinal && collapsed && fabs(fb) > 1e-10) st = VOFPC_CELL_NO_ROOT;
-              break;
-            }
-            if (ph == kHintMid) {
-              // the residual at the centre tells the side of the root: that
-              // half of the bracket is checked by a cut at its end
-              rm = r;
-              if (r > 0) {
-                lo = se; rlo = r;
-              } else {
-                hi = se; rhi = r;
-              }
-              if ((r > 0 ? hh : hl) == se) {
-                // the centre is the end: the root lies beyond it
-                if (st == VOFPC_CELL_OK) st = VOFPC_CELL_LEARNED_FALLBACK;
-                ph = kSearch;
-              } else {
-                ph = kHintEnd;
-              }
-              continue;
-            }
-            if (ph == kHintEnd) {
-              // the bracket holds when its end is past the root; otherwise the
-              // root lies beyond that end
-              const bool up = rm > 0;
-              if (up ? r < 0 : r > 0) {
-                if (up) { hi = se; rhi = r; } else { lo = se; rlo = r; }
-              } else {
-                if (up) { lo = se; rlo = r; } else { hi = se; rhi = r; }
-                if (st == VOFPC_CELL_OK) st = VOFPC_CELL_LEARNED_FALLBACK;
-              }
-              ph = kSearch;
-              continue;
-            }
-            // keep the end across the root from the estimate; xb the end of
-            // smaller residual
-            rlast = r;
-            xd = xc;
-            xc = xb; fc = fb;
-            if ((fa > 0) != (r > 0)) {
-              xb = se; fb = r;
-            } else {
-              xa = se; fa = r;
-            }
-            if (fabs(fa) < fabs(fb)) {
-              const double tx = xa, tf = fa;
-              xa = xb; fa = fb; xb = tx; fb = tf;
-            }
-          }
-          const bool cut_ok = true;
-          if (cut_ok && c.err) {
-            st = VOFPC_CELL_BAD_INPUT;
-          } else if (cut_ok) {
-            s_out = s;
-            ag = c.V / VP;
-            A_out = c.A;
-            const double Sm = sqrt(c.S0 * c.S0 + c.S1 * c.S1 + c.S2 * c.S2);
-            if (Sm > 0) {
-              n0 = c.S0 / Sm; n1 = c.S1 / Sm; n2 = c.S2 / Sm;
-              d_out = -(n0 * c.c0 + n1 * c.c1 + n2 * c.c2);
-            }
-          }
-        }
-      if (q == 0) {
-        if (p.mf.gradT) {
-          // mass transfer of the entry (one-sided form, as vofpc_mass_transfer)
-          double md = 0.0;
-          if (A_out > 0.0) {
-            const double gn = p.mf.gradT[P] * n0 + p.mf.gradT[N + P] * n1 + p.mf.gradT[2 * N + P] * n2;
-            const double gl = (a >= 0.5) ? gn : 0.0, gv = (a >= 0.5) ? 0.0 : gn;
-            const double ql = p.mf.k_l * gl * A_out;
-            const double qv = -p.mf.k_v * gv * A_out;
-            md = (ql + qv) / (p.mf.h_lv * m.V[P]);
-          }
-          p.mf.mdot[k] = md;
-          p.mf.Qdot[k] = -md * p.mf.h_lv;
-        }
-        p.out.s[k] = s_out;
-        p.out.n[k] = n0; p.out.n[cap + k] = n1; p.out.n[2 * cap + k] = n2;
-        p.out.A[k] = A_out;
-        p.out.d[k] = d_out;
-        p.out.alpha_got[k] = ag;
-        p.out.status[k] = st;
-        p.out.iters[k] = it;
+      const bool fits = Main::fits(cell.nv, cell.nf, cell.nl);
+      solve_cells<Main, NET>(p, M.a, tm, cell, active && fits);
+      if (__any(active && !fits)) {
+        wave_sync();
+        solve_cells<Big, NET>(p, M.b, tm, cell, active && !fits);
       }
     }
     // next batch: a wrapping increment, so the XCD's nx claims (one per
     // batch done) bring its counter back to zero
     int nb = 0;
-    if (lane == 0) nb = (int)atomicInc(claim, (unsigned int)(nx - 1));
+    if (tm.lane == 0) nb = (int)atomicInc(claim, (unsigned int)(nx - 1));
     ix = wx + __builtin_amdgcn_readfirstlane(nb);
     wave_sync();
   }
 }
 
-// ---- the learned bracket in a pass of its own
-// In the builds whose wavefronts hold fewer than 16 cells (G >= 8) the
-// network's 16-row tile would run mostly empty inside the reconstruction.
-// This pass takes 16 cells per wavefront (4 lanes each), stages only their
-// vertex field, computes the features, runs one full tile and writes each
-// entry's bracket [sh - d, sh + d] around the predicted isovalue sh (NaN
-// where the reconstruction would run no network: not mixed, bad input,
-// degenerate field).  The reconstruction then checks it as a caller's
-// bracket.
-template <int NVM>
-struct PassMem {
-  double phi[NVM][17];
-  uint8_t link[NVM][16];
-  ThinNet<16> net;
-};
-
-template <int NVM>
-__global__ __launch_bounds__(64) void bracket_pass_kernel(ReconParams p, double *hlo, double *hhi) {
-  constexpr int G = 4, C = 16;
-  __shared__ PassMem<NVM> M;
-  ThinNet<C> &T = M.net;
-  const int lane = threadIdx.x, sl = lane / G, q = lane % G;
-  const DevMesh &m = p.m;
-  int64_t count = p.entries ? (int64_t)*p.entry_count : (int64_t)p.counts[0];
-  if (count > p.out.cap) count = p.out.cap;
-  const int64_t nbatch = (count + C - 1) / C;
-  // this XCD's batches (runs of kRunCells cells), a fixed share per workgroup
-  constexpr int kRun = kRunCells / C;
-  const int xcd = (int)(blockIdx.x % kXcd);
-  const int64_t nx = xcd_count<kRun>(nbatch, xcd);
-  const int64_t wx = ((int64_t)gridDim.x - xcd + kXcd - 1) / kXcd;
-  for (int64_t ix = blockIdx.x / kXcd; ix < nx; ix += wx) {
-    const int64_t bt = xcd_batch<kRun>(ix, xcd);
-    const int64_t j = bt * C + sl;
-    const bool active = j < count;
-    int64_t k = 0, f0 = 0;
-    int P = 0, nf = 0, nv = 0;
-    double a = 0.0, pmin = 0.0, pmax = 0.0;
-    bool row = false;
-    if (active) {
-      k = p.entries ? (int64_t)p.entries[j] : j;
-      P = p.mixed[k];
-      a = p.alpha[P];
-      f0 = m.cell_face_off[P];
-      nf = (int)(m.cell_face_off[P + 1] - f0);
-      const int64_t v0 = m.cv_off[P];
-      nv = (int)(m.cv_off[P + 1] - v0);
-      if (a > p.eps && a < 1.0 - p.eps && nv <= NVM) {   // a NaN alpha fails both tests
-        double lo = __builtin_inf(), hi = -__builtin_inf();
-        stage_vertex_field<G, 2, false>(M, m, p, sl, q, v0, nv, 0.0, 0.0, 0.0, lo, hi);
-        pmin = tmin<G>(lo);
-        pmax = tmax<G>(hi);
-        row = pmax - pmin > 1e-12;
-      }
-    }
-    wave_sync();
-    if (row) {
-      cell_features<G>(M, T, sl, q, p, P, a, nv, nf, f0, pmin, pmax - pmin);
-    } else {
-      for (int i = q; i < net::kIn; i += G) T.x[sl][i] = 0;
-    }
-    wave_sync();
-    net_tiles<C>(T, p.net_wb, p.net_master, lane);
-    if (active && q == 0) {
-      double lo = __builtin_nan(""), hi = __builtin_nan("");
-      const float u = T.u[sl];
-      if (row && !isnan(u)) {
-        const double Wd = pmax - pmin;
-        const double uc = u < 0.f ? 0.0 : (u > 1.f ? 1.0 : (double)u);
-        const double sh = pmin + uc * Wd, dl = p.net_delta * Wd;
-        lo = sh - dl;
-        hi = sh + dl;
-      }
-      hlo[k] = lo;
-      hhi[k] = hi;
-    }
-    wave_sync();
-  }
-}
-
-template <int NVM>
-vofpc_status launch_pass(vofpc_ctx ctx, const ReconParams &p, int64_t n_entries, double *hlo, double *hhi) {
-  int blocks_per_cu = 0;
-  hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks_per_cu, bracket_pass_kernel<NVM>, 64, 0);
-  if (e != hipSuccess || blocks_per_cu <= 0) blocks_per_cu = 4;
-  int64_t grid = (int64_t)ctx->n_cu * blocks_per_cu;
-  const int64_t need = (n_entries + 15) / 16;
-  if (grid > need) grid = need;
-  if (grid < 1) grid = 1;
-  bracket_pass_kernel<NVM><<<(unsigned)grid, 64, 0, ctx->stream>>>(p, hlo, hhi);
-  VOFPC_HIP(hipGetLastError());
-  return VOFPC_OK;
-}
-
-template <int G, int NV, int NF, int NL, int NE, bool NET>
+template <class Main, class Big, bool NET>
 vofpc_status launch_net(vofpc_ctx ctx, const ReconParams &p, int64_t n_entries) {
-  constexpr int C = 64 / G;
   int blocks_per_cu = 0;
-  hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks_per_cu,
-                                                              recon_thin_kernel<G, NV, NF, NL, NE, NET>, 64, 0);
+  hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks_per_cu, recon_group_kernel<Main, Big, NET>, 64, 0);
   if (e != hipSuccess || blocks_per_cu <= 0) blocks_per_cu = 1;
   int64_t grid = (int64_t)ctx->n_cu * blocks_per_cu;
-  const int64_t need = (n_entries + C - 1) / C;
-  if (grid > need) grid = need;
+  if (grid > n_entries) grid = n_entries;
   if (grid < 1) grid = 1;
-  recon_thin_kernel<G, NV, NF, NL, NE, NET><<<(unsigned)grid, 64, 0, ctx->stream>>>(p);
+  recon_group_kernel<Main, Big, NET><<<(unsigned)grid, 64, 0, ctx->stream>>>(p);
   VOFPC_HIP(hipGetLastError());
   return VOFPC_OK;
 }
 
 // the plain build, or the build that runs the network (learned form)
-template <int G, int NV, int NF, int NL, int NE>
+template <class Main, class Big = void>
 vofpc_status launch_t(vofpc_ctx ctx, const ReconParams &p, int64_t n_entries) {
-  if (p.net_wb) return launch_net<G, NV, NF, NL, NE, true>(ctx, p, n_entries);
-  return launch_net<G, NV, NF, NL, NE, false>(ctx, p, n_entries);
+  if (p.net_wb) return launch_net<Main, Big, true>(ctx, p, n_entries);
+  return launch_net<Main, Big, false>(ctx, p, n_entries);
 }
 
-// The builds: class 0 in two sizes (hexahedra and smaller: G = 1, 2, 4; the
-// class caps: G = 2, 4), class 1 at its caps (G = 4, 8, 16).
-struct ThinCaps {
-  int nv, nf, nl, ne;
-};
-constexpr ThinCaps kHex{8, 6, 24, 12}, kC0{16, 8, 48, 24}, kC1{32, 20, 96, 48}, kC2{48, 32, 128, 64};
+// The builds: class 0 in two sizes (hexahedra and smaller; the class caps),
+// classes 1 and 2 at their caps.  The group is the smallest whose lanes hold
+// a cell's edges in registers.
+using HexBuild = Build<4, 8, 6, 24, 12>;
+using SmallBuild = Build<4, 16, 8, 48, 24>;
+using UsualBuild = Build<16, 32, 20, 96, 48>;
+using LargeBuild = Build<16, 48, 32, 128, 64, 4>;   // unpadded: beside UsualBuild it must not cost wavefronts
 
-__host__ bool fits(const ThinCaps &t, const int64_t cmax[4]) {
-  return cmax[0] <= t.nv && cmax[1] <= t.nf && cmax[2] <= t.nl && cmax[3] <= t.ne;
+template <class B>
+__host__ bool fits(const int64_t cmax[4]) {
+  return B::fits(cmax[0], cmax[1], cmax[2]) && cmax[3] <= B::NE;
 }
 
 }  // namespace
 
 bool thin_available(int c, int G, const int64_t cmax[4]) {
-  if (c == 0) return fits(kHex, cmax) ? (G == 1 || G == 2 || G == 4) : ((G == 2 || G == 4) && fits(kC0, cmax));
-  if (c == 1) return (G == 4 || G == 8 || G == 16) && fits(kC1, cmax);
-  if (c == 2) return (G == 4 || G == 8 || G == 16) && fits(kC2, cmax);
+  if (c == 0) return fits<HexBuild>(cmax) ? (G == 1 || G == 2 || G == 4) : ((G == 2 || G == 4) && fits<SmallBuild>(cmax));
+  if (c == 1) return (G == 4 || G == 8 || G == 16) && fits<UsualBuild>(cmax);
+  if (c == 2) return (G == 4 || G == 8 || G == 16) && fits<LargeBuild>(cmax);
   return false;
 }
 
-vofpc_status launch_bracket_pass(vofpc_ctx ctx, const ReconParams &p, int64_t n_entries, int c, double *hlo,
-                                 double *hhi) {
-  VOFPC_REQUIRE(c == 1 || c == 2, VOFPC_E_INVALID_ARG, "reconstruct: no bracket pass for this class");
-  return c == 1 ? launch_pass<kC1.nv>(ctx, p, n_entries, hlo, hhi) : launch_pass<kC2.nv>(ctx, p, n_entries, hlo, hhi);
-}
-
-vofpc_status launch_thin(vofpc_ctx ctx, const ReconParams &p, int64_t n_entries, int c, int G,
-                         const int64_t cmax[4]) {
+vofpc_status launch_thin(vofpc_ctx ctx, const ReconParams &p, int64_t n_entries, int c, int G, const int64_t cmax[4],
+                         bool with_large) {
   VOFPC_REQUIRE(thin_available(c, G, cmax), VOFPC_E_INVALID_ARG, "reconstruct: no group build for this class");
-  if (c == 0) {
-    if (fits(kHex, cmax)) {
-      if (G == 1) return launch_t<1, kHex.nv, kHex.nf, kHex.nl, kHex.ne>(ctx, p, n_entries);
-      if (G == 2) return launch_t<2, kHex.nv, kHex.nf, kHex.nl, kHex.ne>(ctx, p, n_entries);
-      return launch_t<4, kHex.nv, kHex.nf, kHex.nl, kHex.ne>(ctx, p, n_entries);
-    }
-    if (G == 2) return launch_t<2, kC0.nv, kC0.nf, kC0.nl, kC0.ne>(ctx, p, n_entries);
-    return launch_t<4, kC0.nv, kC0.nf, kC0.nl, kC0.ne>(ctx, p, n_entries);
-  }
-  if (c == 1) {
-    if (G == 4) return launch_t<4, kC1.nv, kC1.nf, kC1.nl, kC1.ne>(ctx, p, n_entries);
-    if (G == 8) return launch_t<8, kC1.nv, kC1.nf, kC1.nl, kC1.ne>(ctx, p, n_entries);
-    return launch_t<16, kC1.nv, kC1.nf, kC1.nl, kC1.ne>(ctx, p, n_entries);
-  }
-  if (G == 4) return launch_t<4, kC2.nv, kC2.nf, kC2.nl, kC2.ne>(ctx, p, n_entries);
-  if (G == 8) return launch_t<8, kC2.nv, kC2.nf, kC2.nl, kC2.ne>(ctx, p, n_entries);
-  return launch_t<16, kC2.nv, kC2.nf, kC2.nl, kC2.ne>(ctx, p, n_entries);
+  if (c == 0) return fits<HexBuild>(cmax) ? launch_t<HexBuild>(ctx, p, n_entries) : launch_t<SmallBuild>(ctx, p, n_entries);
+  if (c == 1)
+    return with_large ? launch_t<UsualBuild, LargeBuild>(ctx, p, n_entries) : launch_t<UsualBuild>(ctx, p, n_entries);
+  return launch_t<LargeBuild>(ctx, p, n_entries);
 }
 
 }  // namespace vofpc

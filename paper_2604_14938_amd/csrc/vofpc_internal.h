@@ -159,13 +159,10 @@ struct vofpc_ctx_s {
   hipEvent_t fork_ev = nullptr, join_ev = nullptr;
   bool overlap_classes = true;   // use the second stream (vofpc_ctx_overlap_classes)
   // per-class kernel timing of the reconstruction (eager launches only):
-  // an event pair around each class kernel of the latest call, and around
-  // its bracket pass (learned form) when it has one
+  // an event pair around each class kernel of the latest call
   bool time_classes = false;
   hipEvent_t cls_ev[vofpc::kClasses][2] = {};
   bool cls_rec[vofpc::kClasses] = {};
-  hipEvent_t pass_ev[vofpc::kClasses][2] = {};
-  bool pass_rec[vofpc::kClasses] = {};
 };
 
 struct vofpc_mesh_s {
@@ -186,9 +183,6 @@ struct vofpc_mesh_s {
   // (cells spread over several classes) launch one variant per class over
   // per-class entry lists [kClasses][n_cells] with device counts
   int64_t class_cells[vofpc::kClasses];
-  // learned brackets [2][n_cells] of a bracket pass when the caller keeps
-  // none (allocated by the first such call, outside capture)
-  double *hint_buf = nullptr;
   int64_t class_max[vofpc::kClasses][4];   // largest vertices, faces, loop positions, edges per class
   vofpc::ClassStats class_stats;           // by class_of, before the hex0 move
   bool hex0;                               // class 0 holds only hexahedral-sized cells (mesh_class_of)
