@@ -9,6 +9,7 @@
 //
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <new>
 #include <vector>
@@ -28,249 +29,389 @@ __device__ __forceinline__ void wsync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-struct TileMem {
-  uint16_t x[16][kIn];    // BF16 inputs
-  uint16_t h1[16][kHid];  // BF16 activations
-  uint16_t h2[16][kHid];
-  uint16_t dz2[16][kHid]; // BF16 back-propagated pre-activation gradients
-  uint16_t dz1[16][kHid];
-  float y[16][kOut];
-  float dy[16][kOut];
+// The network of a wavefront in registers, as operands of
+// v_mfma_f32_16x16x16_bf16 with the units as rows and the batch rows as
+// columns: D[unit][row] = sum_k W[unit][k] in[k][row].  Lane l holds
+// D[4(l/16)+j][l%16], which, rounded to BF16, is the B operand of the next
+// layer for the 16 inputs those units are, so the activations never leave
+// their lanes.  (Against rows as A operands staged through LDS the products
+// and their order are the same: the results keep their bits.)
+struct NetRegs {
+  bf16x4 w1[kHid / 16][kIn / 16], w2[kHid / 16][kHid / 16], w3[kHid / 16];
+  f32x4 b1[kHid / 16], b2[kHid / 16], b3;
 };
+constexpr int kNT = kHid / 16;   // tiles of 16 hidden units
+// four consecutive floats of a caller's array (any float alignment)
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
-// A operand from a row-major BF16 tile: rows 0..15, columns k0 + 4(l/16) + j
-template <int LD>
-__device__ __forceinline__ bf16x4 a_rows(const uint16_t (*t)[LD], int lane, int k0) {
-  const int r = lane & 15, k = k0 + 4 * (lane >> 4);
-  bf16x4 v;
-  v[0] = (short)t[r][k]; v[1] = (short)t[r][k + 1]; v[2] = (short)t[r][k + 2]; v[3] = (short)t[r][k + 3];
+// A operand: rows r0 + l%16 (zero past nrows) of a row-major matrix with
+// rows of ld values, columns k0 + 4(l/16) + j
+__device__ __forceinline__ bf16x4 a_weight(const uint16_t *W, int ld, int lane, int r0, int k0, int nrows) {
+  const int r = r0 + (lane & 15), k = k0 + 4 * (lane >> 4);
+  bf16x4 v = {0, 0, 0, 0};
+  if (r < nrows) v = *reinterpret_cast<const bf16x4 *>(W + r * ld + k);
   return v;
 }
-// Forward pass of one 16-row tile (rows past nrows are zero inputs).
-__device__ void tile_forward(TileMem &T, const float *X, int64_t row0, int nrows, const uint16_t *wb,
-                             const float *master, int lane) {
-  for (int i = lane; i < 16 * kIn; i += 64) {
-    const int r = i / kIn, c = i % kIn;
-    T.x[r][c] = (r < nrows) ? to_bf16(X[(row0 + r) * kIn + c]) : (uint16_t)0;
+
+__device__ __forceinline__ void net_load(NetRegs &R, const uint16_t *wb, const float *master, int lane) {
+  const int rq = 4 * (lane >> 4);
+  // in the order of their use
+#pragma unroll
+  for (int t = 0; t < kNT; ++t) {
+#pragma unroll
+    for (int k = 0; k < kIn / 16; ++k) R.w1[t][k] = a_weight(wb + oW1, kIn, lane, t * 16, k * 16, kHid);
+    R.b1[t] = *reinterpret_cast<const f32x4 *>(master + oB1 + t * 16 + rq);
   }
-  wsync();
-  const int col = lane & 15, rq = 4 * (lane >> 4);
-  // layer 1: h1 = tanh(x W1^T + b1)
-  for (int nt = 0; nt < kHid / 16; ++nt) {
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int kt = 0; kt < kIn / 16; ++kt)
-      acc = mfma16(a_rows<kIn>(T.x, lane, kt * 16), b_weightT(wb + oW1, kIn, lane, nt * 16, kt * 16, kHid), acc);
-    const float b = master[oB1 + nt * 16 + col];
-    for (int j = 0; j < 4; ++j) T.h1[rq + j][nt * 16 + col] = to_bf16(act_tanh(acc[j] + b));
+#pragma unroll
+  for (int t = 0; t < kNT; ++t) {
+#pragma unroll
+    for (int k = 0; k < kNT; ++k) R.w2[t][k] = a_weight(wb + oW2, kHid, lane, t * 16, k * 16, kHid);
+    R.b2[t] = *reinterpret_cast<const f32x4 *>(master + oB2 + t * 16 + rq);
   }
-  wsync();
-  // layer 2
-  for (int nt = 0; nt < kHid / 16; ++nt) {
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int kt = 0; kt < kHid / 16; ++kt)
-      acc = mfma16(a_rows<kHid>(T.h1, lane, kt * 16), b_weightT(wb + oW2, kHid, lane, nt * 16, kt * 16, kHid), acc);
-    const float b = master[oB2 + nt * 16 + col];
-    for (int j = 0; j < 4; ++j) T.h2[rq + j][nt * 16 + col] = to_bf16(act_tanh(acc[j] + b));
-  }
-  wsync();
-  // layer 3 (4 outputs, padded to a 16-wide tile)
-  {
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int kt = 0; kt < kHid / 16; ++kt)
-      acc = mfma16(a_rows<kHid>(T.h2, lane, kt * 16), b_weightT(wb + oW3, kHid, lane, 0, kt * 16, kOut), acc);
-    if (col < kOut) {
-      const float b = master[oB3 + col];
-      for (int j = 0; j < 4; ++j) T.y[rq + j][col] = acc[j] + b;
-    }
-  }
-  wsync();
+#pragma unroll
+  for (int t = 0; t < kNT; ++t) R.w3[t] = a_weight(wb + oW3, kHid, lane, 0, t * 16, kOut);
+  R.b3 = *reinterpret_cast<const f32x4 *>(master + oB3);
 }
 
-__global__ __launch_bounds__(64) void mlp_forward_kernel(const float *X, int64_t n, const uint16_t *wb,
-                                                         const float *master, float *Y) {
-  __shared__ TileMem T;
-  const int lane = threadIdx.x;
-  const int64_t tiles = (n + 15) / 16;
-  for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x) {
-    const int64_t r0 = t * 16;
-    const int nr = (int)((n - r0) < 16 ? (n - r0) : 16);
-    tile_forward(T, X, r0, nr, wb, master, lane);
-    for (int i = lane; i < 16 * kOut; i += 64) {
-      const int r = i / kOut, c = i % kOut;
-      if (r < nr) Y[(r0 + r) * kOut + c] = T.y[r][c];
-    }
-    wsync();
+// four floats to BF16 (round to nearest even, the hardware's packed conversion)
+__device__ __forceinline__ bf16x4 pack_bf16(f32x4 v) {
+  typedef __bf16 bf16v __attribute__((ext_vector_type(4)));
+  return __builtin_bit_cast(bf16x4, __builtin_convertvector(v, bf16v));
+}
+
+__device__ __forceinline__ bf16x4 activate(f32x4 z, f32x4 b) {
+  f32x4 h;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) h[j] = act_tanh(z[j] + b[j]);
+  return pack_bf16(h);
+}
+
+// Inputs of batch row r0 + l%16 (zero past nr rows), columns 4(l/16) + j and
+// 16 + 4(l/16) + j: two 16-byte loads a lane, whole rows a wavefront.
+__device__ __forceinline__ void row_load(const float *X, int64_t r0, int nr, int lane, f32x4 (&x)[kIn / 16]) {
+  const int r = lane & 15;
+#pragma unroll
+  for (int k = 0; k < kIn / 16; ++k) {
+    x[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (r < nr) x[k] = *reinterpret_cast<const f32x4u *>(X + (r0 + r) * kIn + k * 16 + 4 * (lane >> 4));
   }
 }
 
-// Forward, loss and backward of the rows of one block; writes the block's
-// partial gradient and loss (no atomics: a fixed-order reduction follows).
-__global__ __launch_bounds__(64) void mlp_grad_partial_kernel(const float *X, const float *Tg, int64_t n,
-                                                              const uint16_t *wb, const float *master,
-                                                              float *partial) {
-  __shared__ TileMem T;
+// Forward pass of 16 rows; y: the four outputs of row l%16 on lanes l < 16.
+__device__ __forceinline__ void tile_forward(const NetRegs &R, const f32x4 (&x)[kIn / 16], bf16x4 (&xb)[kIn / 16],
+                                             bf16x4 (&h1)[kNT], bf16x4 (&h2)[kNT], f32x4 &y) {
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int k = 0; k < kIn / 16; ++k) xb[k] = pack_bf16(x[k]);
+#pragma unroll
+  for (int t = 0; t < kNT; ++t) {
+    f32x4 acc = zero;
+#pragma unroll
+    for (int k = 0; k < kIn / 16; ++k) acc = mfma16(R.w1[t][k], xb[k], acc);
+    h1[t] = activate(acc, R.b1[t]);
+  }
+#pragma unroll
+  for (int t = 0; t < kNT; ++t) {
+    f32x4 acc = zero;
+#pragma unroll
+    for (int k = 0; k < kNT; ++k) acc = mfma16(R.w2[t][k], h1[k], acc);
+    h2[t] = activate(acc, R.b2[t]);
+  }
+  f32x4 acc = zero;
+#pragma unroll
+  for (int k = 0; k < kNT; ++k) acc = mfma16(R.w3[k], h2[k], acc);
+#pragma unroll
+  for (int j = 0; j < kOut; ++j) y[j] = acc[j] + R.b3[j];
+}
+
+// The rows in tiles of 16 over the wavefronts of the grid, each wavefront
+// with the network in its registers and the next tile's rows in flight.
+// emit(row, y) is called on the lanes that hold a row.  Bound by the vector
+// ALU, the 32 tanh of a lane and tile (about 2,900 of 3,400 cycles a tile);
+// the 144 bytes a row take a third of the time.  221,861 rows: 22.8 us (1.4
+// TB/s), 71.9 us when each tile went through LDS with the weights re-read.
+template <class Emit>
+__device__ __forceinline__ void forward_rows(const float *X, int64_t n, const uint16_t *wb, const float *master,
+                                             Emit emit) {
+  const int lane = threadIdx.x & 63;
+  const int64_t tiles = (n + 15) / 16, stride = (int64_t)gridDim.x * (blockDim.x / 64);
+  int64_t t = (int64_t)blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6);
+  if (t >= tiles) return;
+  NetRegs R;
+  f32x4 x[kIn / 16];
+  row_load(X, t * 16, (int)(n - t * 16 < 16 ? n - t * 16 : 16), lane, x);
+  net_load(R, wb, master, lane);
+  for (; t < tiles; t += stride) {
+    const int64_t r0 = t * 16, q0 = r0 + stride * 16;
+    const int nr = (int)(n - r0 < 16 ? n - r0 : 16);
+    f32x4 nx[kIn / 16];
+    row_load(X, q0, (int)(n - q0 < 16 ? n - q0 : 16), lane, nx);
+    bf16x4 xb[kIn / 16], h1[kNT], h2[kNT];
+    f32x4 y;
+    tile_forward(R, x, xb, h1, h2, y);
+    if (lane < nr) emit(r0 + lane, y);
+#pragma unroll
+    for (int k = 0; k < kIn / 16; ++k) x[k] = nx[k];
+  }
+}
+
+constexpr int kNetBlock = 256;     // four wavefronts
+constexpr int kNetBlocksPerCu = 3;
+
+__global__ __launch_bounds__(kNetBlock) void mlp_forward_kernel(const float *X, int64_t n, const uint16_t *wb,
+                                                                const float *master, float *Y) {
+  forward_rows(X, n, wb, master, [&](int64_t r, f32x4 y) { *reinterpret_cast<f32x4u *>(Y + r * kOut) = y; });
+}
+
+// blocks of a forward launch over at most n rows
+static unsigned forward_grid(vofpc_ctx ctx, int64_t n) {
+  const int64_t need = ((n + 15) / 16 + kNetBlock / 64 - 1) / (kNetBlock / 64);
+  return (unsigned)std::max<int64_t>(1, std::min<int64_t>(need, (int64_t)ctx->n_cu * kNetBlocksPerCu));
+}
+
+// Forward, loss and backward of the 64 rows of one block, one tile of 16 rows
+// per wavefront; writes the block's partial gradient and loss (no atomics: a
+// fixed-order reduction follows).  A wavefront computes its tile's
+// activations and back-propagated differences in registers (the layouts of
+// tile_forward serve the backward product dz1 = W2^T dz2 too) and leaves them
+// in LDS with the rows innermost; then the wavefronts share out the weight
+// gradients, whose products run over the rows, each sum over the block's rows
+// in row order.
+// Bound by the latency of one tile and of the row-ordered sums: 4,096 rows
+// are 64 blocks.  A training step of 4,096 rows takes 19 us in two launches;
+// one wavefront per 64 rows, scalar LDS operands, and launches of their own
+// for the Adam step and the loss copy took 74 us.
+constexpr int kTiles = kTilesPerBlock;
+static_assert(kTiles * 64 == kNetBlock, "a wavefront per tile");
+struct GradMem {
+  uint16_t h1[kTiles][kHid][16], h2[kTiles][kHid][16], dz2[kTiles][kHid][16], dz1[kTiles][kHid][16];   // BF16
+  uint16_t x[kTiles][kIn][16];
+  float dy[kOut][kTiles * 16];
+  float err[kTiles][16][kOut];
+};
+
+__device__ __forceinline__ void rows_to_lds(uint16_t (*t)[16], int u0, int row, bf16x4 v) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j) t[u0 + j][row] = (uint16_t)v[j];
+}
+
+__global__ __launch_bounds__(kNetBlock) void mlp_grad_partial_kernel(const float *X, const float *Tg, int64_t n,
+                                                                     const uint16_t *wb, const uint16_t *w2t,
+                                                                     const float *master, float *partial) {
+  __shared__ GradMem M;
   __shared__ float red[64];
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int col = lane & 15, rq = 4 * (lane >> 4);
   const float inv_n = 1.0f / (float)n;
-  f32x4 gW2[4][4], gW1[4][2];
-  for (int a = 0; a < 4; ++a) {
-    for (int b = 0; b < 4; ++b) gW2[a][b] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    for (int b = 0; b < 2; ++b) gW1[a][b] = (f32x4){0.f, 0.f, 0.f, 0.f};
-  }
-  float gW3[kOut] = {0.f, 0.f, 0.f, 0.f};  // lane = hidden unit
-  float gb3 = 0.f, gb2 = 0.f, gb1 = 0.f;     // lane-indexed (gb3 for lane < 4)
-  float lsum = 0.f;
-  const int64_t tiles = (n + 15) / 16;
-  const int64_t t0 = (int64_t)blockIdx.x * kTilesPerBlock;
-  for (int64_t t = t0; t < t0 + kTilesPerBlock && t < tiles; ++t) {
-    const int64_t r0 = t * 16;
-    const int nr = (int)((n - r0) < 16 ? (n - r0) : 16);
-    tile_forward(T, X, r0, nr, wb, master, lane);
-    // output gradient of the mean loss
-    if (lane < 16 * kOut) {
-      const int r = lane / kOut, c = lane % kOut;
-      float d = 0.f;
-      if (r < nr) {
-        const float e = T.y[r][c] - Tg[(r0 + r) * kOut + c];
-        const float w = (c == 0) ? 1.0f : kNormalWeight;
-        d = 2.0f * w * e * inv_n;
-        lsum += w * e * e;
-      }
-      T.dy[r][c] = d;
-    }
-    wsync();
-    // dW3 = dy^T h2, db3, dz2 = (dy W3) * (1 - h2^2)   (FP32, K = 4)
-    for (int r = 0; r < 16; ++r) {
-      const float h = from_bf16(T.h2[r][lane]);
-      float dh = 0.f;
+  {
+    const int64_t r0 = ((int64_t)blockIdx.x * kTiles + wave) * 16;
+    const int nr = (int)(n - r0 < 16 ? n - r0 : 16);   // may be 0 or less: a tile past the end
+    f32x4 x[kIn / 16], tg = {0.f, 0.f, 0.f, 0.f};
+    row_load(X, r0, nr, lane, x);
+    if (lane < nr && lane < 16) tg = *reinterpret_cast<const f32x4u *>(Tg + (r0 + lane) * kOut);
+    NetRegs R;
+    net_load(R, wb, master, lane);
+    bf16x4 wt[kNT][kNT], w3[kOut][kNT];
+#pragma unroll
+    for (int a = 0; a < kNT; ++a)
+#pragma unroll
+      for (int k = 0; k < kNT; ++k) wt[a][k] = a_weight(w2t, kHid, lane, a * 16, k * 16, kHid);
+#pragma unroll
+    for (int c = 0; c < kOut; ++c)
+#pragma unroll
+      for (int t = 0; t < kNT; ++t) w3[c][t] = *reinterpret_cast<const bf16x4 *>(wb + oW3 + c * kHid + t * 16 + rq);
+    bf16x4 xb[kIn / 16], h1[kNT], h2[kNT];
+    f32x4 y;
+    tile_forward(R, x, xb, h1, h2, y);
+    // output gradient of the mean loss, then to every lane of its row
+    f32x4 d = {0.f, 0.f, 0.f, 0.f}, e = {0.f, 0.f, 0.f, 0.f};
+    if (lane < 16) {
+#pragma unroll
       for (int c = 0; c < kOut; ++c) {
-        const float d = T.dy[r][c];
-        gW3[c] += d * h;
-        dh += d * from_bf16(wb[oW3 + c * kHid + lane]);
+        if (lane < nr) {
+          e[c] = y[c] - tg[c];
+          const float w = (c == 0) ? 1.0f : kNormalWeight;
+          d[c] = 2.0f * w * e[c] * inv_n;
+        }
+        M.dy[c][wave * 16 + lane] = d[c];
       }
-      T.dz2[r][lane] = to_bf16(dh * (1.0f - h * h));
+      *reinterpret_cast<f32x4 *>(&M.err[wave][lane][0]) = e;
     }
-    if (lane < kOut)
-      for (int r = 0; r < 16; ++r) gb3 += T.dy[r][lane];
-    wsync();
-    // dz1 = (dz2 W2) * (1 - h1^2): A = dz2 (rows), B[k][n] = W2[k][n]
-    for (int nt = 0; nt < kHid / 16; ++nt) {
+#pragma unroll
+    for (int c = 0; c < kOut; ++c) d[c] = __shfl(d[c], col);
+    // dz2 = (dy W3) * (1 - h2^2)   (FP32, K = 4)
+    bf16x4 z2[kNT];
+#pragma unroll
+    for (int t = 0; t < kNT; ++t) {
+      f32x4 v;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float h = from_bf16((uint16_t)h2[t][j]);
+        float dh = 0.f;
+#pragma unroll
+        for (int c = 0; c < kOut; ++c) dh += d[c] * from_bf16((uint16_t)w3[c][t][j]);
+        v[j] = dh * (1.0f - h * h);
+      }
+      z2[t] = pack_bf16(v);
+    }
+    // dz1 = (dz2 W2) * (1 - h1^2)
+    bf16x4 z1[kNT];
+#pragma unroll
+    for (int t = 0; t < kNT; ++t) {
       f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-      for (int kt = 0; kt < kHid / 16; ++kt) {
-        bf16x4 bv;
-        const int n = nt * 16 + col, k = kt * 16 + 4 * (lane >> 4);
-        for (int j = 0; j < 4; ++j) bv[j] = (short)wb[oW2 + (k + j) * kHid + n];
-        acc = mfma16(a_rows<kHid>(T.dz2, lane, kt * 16), bv, acc);
-      }
+#pragma unroll
+      for (int k = 0; k < kNT; ++k) acc = mfma16(wt[t][k], z2[k], acc);
+#pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const float h = from_bf16(T.h1[rq + j][nt * 16 + col]);
-        T.dz1[rq + j][nt * 16 + col] = to_bf16(acc[j] * (1.0f - h * h));
+        const float h = from_bf16((uint16_t)h1[t][j]);
+        acc[j] = acc[j] * (1.0f - h * h);
       }
+      z1[t] = pack_bf16(acc);
     }
-    wsync();
-    // dW2 += dz2^T h1, dW1 += dz1^T x: A[m][k] = dz[k][m], B[k][n] = act[k][n]
-    for (int mt = 0; mt < 4; ++mt) {
-      bf16x4 a2, a1;
-      for (int j = 0; j < 4; ++j) {
-        a2[j] = (short)T.dz2[rq + j][mt * 16 + col];
-        a1[j] = (short)T.dz1[rq + j][mt * 16 + col];
-      }
-      for (int nt = 0; nt < 4; ++nt) {
-        bf16x4 bv;
-        for (int j = 0; j < 4; ++j) bv[j] = (short)T.h1[rq + j][nt * 16 + col];
-        gW2[mt][nt] = mfma16(a2, bv, gW2[mt][nt]);
-      }
-      for (int nt = 0; nt < 2; ++nt) {
-        bf16x4 bv;
-        for (int j = 0; j < 4; ++j) bv[j] = (short)T.x[rq + j][nt * 16 + col];
-        gW1[mt][nt] = mfma16(a1, bv, gW1[mt][nt]);
-      }
+#pragma unroll
+    for (int t = 0; t < kNT; ++t) {
+      rows_to_lds(M.h1[wave], t * 16 + rq, col, h1[t]);
+      rows_to_lds(M.h2[wave], t * 16 + rq, col, h2[t]);
+      rows_to_lds(M.dz2[wave], t * 16 + rq, col, z2[t]);
+      rows_to_lds(M.dz1[wave], t * 16 + rq, col, z1[t]);
     }
-    for (int r = 0; r < 16; ++r) {
-      gb2 += from_bf16(T.dz2[r][lane]);
-      gb1 += from_bf16(T.dz1[r][lane]);
-    }
-    wsync();
+#pragma unroll
+    for (int t = 0; t < kIn / 16; ++t) rows_to_lds(M.x[wave], t * 16 + rq, col, xb[t]);
   }
+  __syncthreads();
   float *out = partial + (int64_t)blockIdx.x * (kParams + 1);
-  for (int mt = 0; mt < 4; ++mt) {
-    for (int nt = 0; nt < 4; ++nt)
-      for (int j = 0; j < 4; ++j) out[oW2 + (mt * 16 + rq + j) * kHid + nt * 16 + col] = gW2[mt][nt][j];
-    for (int nt = 0; nt < 2; ++nt)
-      for (int j = 0; j < 4; ++j) out[oW1 + (mt * 16 + rq + j) * kIn + nt * 16 + col] = gW1[mt][nt][j];
+  // tiles of the block that hold rows
+  const int64_t left = (n + 15) / 16 - (int64_t)blockIdx.x * kTiles;
+  const int nt = left < kTiles ? (int)left : kTiles;
+  auto rows4 = [&](const uint16_t (*t)[16], int u) { return *reinterpret_cast<const bf16x4 *>(&t[u][rq]); };
+  // dW2 = dz2^T h1, dW1 = dz1^T x: this wavefront's 16 units, A[m][k] = dz[k][m], B[k][n] = act[k][n]
+  {
+    f32x4 g2[kNT], g1[kIn / 16];
+#pragma unroll
+    for (int b = 0; b < kNT; ++b) g2[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int b = 0; b < kIn / 16; ++b) g1[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < nt; ++t) {
+      const bf16x4 a2 = rows4(M.dz2[t], wave * 16 + col), a1 = rows4(M.dz1[t], wave * 16 + col);
+#pragma unroll
+      for (int b = 0; b < kNT; ++b) g2[b] = mfma16(a2, rows4(M.h1[t], b * 16 + col), g2[b]);
+#pragma unroll
+      for (int b = 0; b < kIn / 16; ++b) g1[b] = mfma16(a1, rows4(M.x[t], b * 16 + col), g1[b]);
+    }
+#pragma unroll
+    for (int b = 0; b < kNT; ++b)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) out[oW2 + (wave * 16 + rq + j) * kHid + b * 16 + col] = g2[b][j];
+#pragma unroll
+    for (int b = 0; b < kIn / 16; ++b)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) out[oW1 + (wave * 16 + rq + j) * kIn + b * 16 + col] = g1[b][j];
   }
-  for (int c = 0; c < kOut; ++c) out[oW3 + c * kHid + lane] = gW3[c];
-  out[oB2 + lane] = gb2;
-  out[oB1 + lane] = gb1;
-  if (lane < kOut) out[oB3 + lane] = gb3;
-  red[lane] = lsum;
-  wsync();
-  if (lane == 0) {
-    float s = 0.f;
-    for (int i = 0; i < 64; ++i) s += red[i];
-    out[kParams] = s * inv_n;
+  // dW3 = dy^T h2, one output per wavefront, lane = hidden unit; the bias
+  // sums and the loss beside it, one each
+  {
+    float g3 = 0.f, gb = 0.f;
+    const uint16_t (*bias)[kHid][16] = wave == 0 ? M.dz2 : M.dz1;
+    for (int t = 0; t < nt; ++t) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) g3 += M.dy[wave][t * 16 + r] * from_bf16(M.h2[t][lane][r]);
+      if (wave < 2) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) gb += from_bf16(bias[t][lane][r]);
+      } else if (wave == 2 && lane < kOut) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) gb += M.dy[lane][t * 16 + r];
+      } else if (wave == 3) {
+        const float e = M.err[t][lane / kOut][lane % kOut], w = (lane % kOut == 0) ? 1.0f : kNormalWeight;
+        gb += w * e * e;
+      }
+    }
+    out[oW3 + wave * kHid + lane] = g3;
+    if (wave == 0) out[oB2 + lane] = gb;
+    if (wave == 1) out[oB1 + lane] = gb;
+    if (wave == 2 && lane < kOut) out[oB3 + lane] = gb;
+    if (wave == 3) {
+      red[lane] = gb;
+      wsync();
+      if (lane == 0) {
+        float s = 0.f;
+        for (int i = 0; i < 64; ++i) s += red[i];
+        out[kParams] = s * inv_n;
+      }
+    }
   }
 }
 
-// Fixed-order sum of the block partials.
-__global__ void mlp_reduce_kernel(const float *partial, int nblk, float *grad, float *loss) {
+// Entry i of the network's parameters and its BF16 copies: row-major, and W2
+// once more transposed (the backward product's operand).
+__device__ __forceinline__ void store_bf16(uint16_t *wb, uint16_t *w2t, int i, float w) {
+  const uint16_t h = to_bf16(w);
+  wb[i] = h;
+  const int k = i - oW2;
+  if (k >= 0 && k < kHid * kHid) w2t[(k % kHid) * kHid + k / kHid] = h;
+}
+
+// Adam on one parameter.
+struct AdamArgs {
+  float *master, *m, *v;
+  uint16_t *wb, *w2t;
+  float lr, b1, b2, eps, bc1, bc2;
+};
+
+// Sum of the block partials in block order; the gradient and the loss go to
+// the caller's arrays where given, and with `adam` each thread goes on to the
+// Adam step of its parameter (a training step is this launch and the one
+// before it).  The loads of a run of partials are in flight together.
+__global__ __launch_bounds__(64) void mlp_reduce_kernel(const float *partial, int nblk, float *grad, float *loss,
+                                                        int adam, AdamArgs p) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i > kParams) return;
   float s = 0.f;
-  for (int b = 0; b < nblk; ++b) s += partial[(int64_t)b * (kParams + 1) + i];
-  if (i < kParams) grad[i] = s;
-  else if (loss) *loss = s;
+  constexpr int kRun = 64;
+  for (int b0 = 0; b0 < nblk; b0 += kRun) {
+    float v[kRun];
+#pragma unroll
+    for (int b = 0; b < kRun; ++b) v[b] = b0 + b < nblk ? partial[(int64_t)(b0 + b) * (kParams + 1) + i] : 0.f;
+#pragma unroll
+    for (int b = 0; b < kRun; ++b)
+      if (b0 + b < nblk) s += v[b];
+  }
+  if (i == kParams) {
+    if (loss) *loss = s;
+    return;
+  }
+  if (grad) grad[i] = s;
+  if (!adam) return;
+  const float mi = p.b1 * p.m[i] + (1.f - p.b1) * s;
+  const float vi = p.b2 * p.v[i] + (1.f - p.b2) * s * s;
+  p.m[i] = mi;
+  p.v[i] = vi;
+  const float w = p.master[i] - p.lr * (mi / p.bc1) / (sqrtf(vi / p.bc2) + p.eps);
+  p.master[i] = w;
+  store_bf16(p.wb, p.w2t, i, w);
 }
 
-__global__ void adam_kernel(float *master, uint16_t *wb, float *m, float *v, const float *g, float lr, float b1,
-                            float b2, float eps, float bc1, float bc2) {
+__global__ void to_bf16_kernel(const float *src, uint16_t *wb, uint16_t *w2t) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= kParams) return;
-  const float gi = g[i];
-  const float mi = b1 * m[i] + (1.f - b1) * gi;
-  const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-  m[i] = mi;
-  v[i] = vi;
-  const float w = master[i] - lr * (mi / bc1) / (sqrtf(vi / bc2) + eps);
-  master[i] = w;
-  wb[i] = to_bf16(w);
-}
-
-__global__ void to_bf16_kernel(const float *src, uint16_t *dst, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) dst[i] = to_bf16(src[i]);
+  if (i < kParams) store_bf16(wb, w2t, i, src[i]);
 }
 
 // Decode the network output into a bracket per mixed entry.
-__global__ __launch_bounds__(64) void mlp_bracket_kernel(const float *X, const double *prange, const int32_t *counts,
-                                                         int64_t cap, const uint16_t *wb, const float *master,
-                                                         double ksig, double *hlo, double *hhi) {
-  __shared__ TileMem T;
-  const int lane = threadIdx.x;
+__global__ __launch_bounds__(kNetBlock) void mlp_bracket_kernel(const float *X, const double *prange,
+                                                                const int32_t *counts, int64_t cap,
+                                                                const uint16_t *wb, const float *master, double ksig,
+                                                                double *hlo, double *hhi) {
   int64_t n = counts[0];
   if (n > cap) n = cap;
-  const int64_t tiles = (n + 15) / 16;
-  for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x) {
-    const int64_t r0 = t * 16;
-    const int nr = (int)((n - r0) < 16 ? (n - r0) : 16);
-    tile_forward(T, X, r0, nr, wb, master, lane);
-    if (lane < nr) {
-      const int64_t k = r0 + lane;
-      const double lo = prange[2 * k], W = prange[2 * k + 1];
-      double u = (double)T.y[lane][0];
-      u = u < 0.0 ? 0.0 : (u > 1.0 ? 1.0 : u);
-      const double sh = lo + u * W, d = ksig * W;
-      if (W > 0 && !isnan(u)) {
-        hlo[k] = sh - d;
-        hhi[k] = sh + d;
-      } else {
-        hlo[k] = __builtin_nan("");
-        hhi[k] = __builtin_nan("");
-      }
-    }
-    wsync();
-  }
+  forward_rows(X, n, wb, master, [&](int64_t k, f32x4 y) {
+    const double lo = prange[2 * k], W = prange[2 * k + 1];
+    double u = (double)y[0];
+    u = u < 0.0 ? 0.0 : (u > 1.0 ? 1.0 : u);
+    const double sh = lo + u * W, d = ksig * W;
+    const bool ok = W > 0 && !isnan(u);
+    hlo[k] = ok ? sh - d : __builtin_nan("");
+    hhi[k] = ok ? sh + d : __builtin_nan("");
+  });
 }
 
 // ----------------------------------------------------------------- features
@@ -387,11 +528,9 @@ using namespace vofpc;
 struct vofpc_mlp_s {
   vofpc_ctx ctx;
   float *master = nullptr;
-  uint16_t *wb = nullptr;
+  uint16_t *wb = nullptr, *w2t = nullptr;   // BF16 parameters; W2 transposed
   float *m = nullptr, *v = nullptr;
-  float *grad = nullptr;
   float *partial = nullptr;
-  float *loss = nullptr;
   int max_blocks = 0;
   int64_t t = 0;
 };
@@ -412,9 +551,8 @@ extern "C" vofpc_status vofpc_mlp_create(vofpc_ctx ctx, int64_t max_batch, vofpc
   if (hipMalloc(&M->master, sizeof(float) * kParams) != hipSuccess ||
       hipMalloc(&M->m, sizeof(float) * kParams) != hipSuccess ||
       hipMalloc(&M->v, sizeof(float) * kParams) != hipSuccess ||
-      hipMalloc(&M->grad, sizeof(float) * kParams) != hipSuccess ||
-      hipMalloc(&M->loss, sizeof(float)) != hipSuccess ||
       hipMalloc(&M->wb, sizeof(uint16_t) * kParams) != hipSuccess ||
+      hipMalloc(&M->w2t, sizeof(uint16_t) * kHid * kHid) != hipSuccess ||
       hipMalloc(&M->partial, sizeof(float) * (size_t)M->max_blocks * (kParams + 1)) != hipSuccess) {
     vofpc_mlp_destroy(M);
     set_error("mlp_create: hipMalloc failed");
@@ -422,6 +560,7 @@ extern "C" vofpc_status vofpc_mlp_create(vofpc_ctx ctx, int64_t max_batch, vofpc
   }
   VOFPC_HIP(hipMemset(M->master, 0, sizeof(float) * kParams));
   VOFPC_HIP(hipMemset(M->wb, 0, sizeof(uint16_t) * kParams));
+  VOFPC_HIP(hipMemset(M->w2t, 0, sizeof(uint16_t) * kHid * kHid));
   VOFPC_HIP(hipMemset(M->m, 0, sizeof(float) * kParams));
   VOFPC_HIP(hipMemset(M->v, 0, sizeof(float) * kParams));
   M->t = 0;
@@ -434,7 +573,7 @@ extern "C" vofpc_status vofpc_mlp_destroy(vofpc_mlp M) {
   if (!M) return VOFPC_OK;
   (void)hipSetDevice(M->ctx->device);
   (void)hipFree(M->master); (void)hipFree(M->wb); (void)hipFree(M->m); (void)hipFree(M->v);
-  (void)hipFree(M->grad); (void)hipFree(M->partial); (void)hipFree(M->loss);
+  (void)hipFree(M->w2t); (void)hipFree(M->partial);
   delete M;
   return VOFPC_OK;
 }
@@ -446,7 +585,7 @@ extern "C" vofpc_status vofpc_mlp_set_params(vofpc_mlp M, const float *host, int
   VOFPC_HIP(hipMemcpy(M->master, host, sizeof(float) * kParams, hipMemcpyHostToDevice));
   VOFPC_HIP(hipMemset(M->m, 0, sizeof(float) * kParams));
   VOFPC_HIP(hipMemset(M->v, 0, sizeof(float) * kParams));
-  to_bf16_kernel<<<(kParams + 255) / 256, 256, 0, M->ctx->stream>>>(M->master, M->wb, kParams);
+  to_bf16_kernel<<<(kParams + 255) / 256, 256, 0, M->ctx->stream>>>(M->master, M->wb, M->w2t);
   VOFPC_HIP(hipGetLastError());
   VOFPC_HIP(hipStreamSynchronize(M->ctx->stream));
   M->t = 0;
@@ -466,18 +605,26 @@ extern "C" vofpc_status vofpc_mlp_forward(vofpc_ctx ctx, vofpc_mlp M, const floa
   clear_error();
   VOFPC_REQUIRE(ctx && M && X && Y && n > 0, VOFPC_E_INVALID_ARG, "mlp_forward: bad argument");
   VOFPC_HIP(hipSetDevice(ctx->device));
-  int64_t grid = (n + 15) / 16;
-  if (grid > ctx->n_cu * 8) grid = ctx->n_cu * 8;
-  mlp_forward_kernel<<<(unsigned)grid, 64, 0, ctx->stream>>>(X, n, M->wb, M->master, Y);
+  mlp_forward_kernel<<<forward_grid(ctx, n), kNetBlock, 0, ctx->stream>>>(X, n, M->wb, M->master, Y);
   VOFPC_HIP(hipGetLastError());
   return VOFPC_OK;
 }
 
-static vofpc_status mlp_gradient(vofpc_ctx ctx, vofpc_mlp M, const float *X, const float *T, int64_t n) {
+// The gradient of the mean loss over n rows into grad and loss (either may be
+// null); with `step`, Adam step number t on it.
+static vofpc_status mlp_gradient(vofpc_ctx ctx, vofpc_mlp M, const float *X, const float *T, int64_t n, float *grad,
+                                 float *loss, bool step, float lr) {
   const int nblk = (int)((n + 16 * kTilesPerBlock - 1) / (16 * kTilesPerBlock));
   VOFPC_REQUIRE(nblk <= M->max_blocks, VOFPC_E_INVALID_ARG, "mlp: batch larger than max_batch");
-  mlp_grad_partial_kernel<<<nblk, 64, 0, ctx->stream>>>(X, T, n, M->wb, M->master, M->partial);
-  mlp_reduce_kernel<<<(kParams + 1 + 255) / 256, 256, 0, ctx->stream>>>(M->partial, nblk, M->grad, M->loss);
+  AdamArgs p{};
+  if (step) {
+    M->t += 1;
+    const float b1 = 0.9f, b2 = 0.999f;
+    p = AdamArgs{M->master, M->m, M->v, M->wb, M->w2t, lr, b1, b2, 1e-8f, 1.0f - powf(b1, (float)M->t),
+                 1.0f - powf(b2, (float)M->t)};
+  }
+  mlp_grad_partial_kernel<<<nblk, kNetBlock, 0, ctx->stream>>>(X, T, n, M->wb, M->w2t, M->master, M->partial);
+  mlp_reduce_kernel<<<(kParams + 1 + 63) / 64, 64, 0, ctx->stream>>>(M->partial, nblk, grad, loss, step ? 1 : 0, p);
   VOFPC_HIP(hipGetLastError());
   return VOFPC_OK;
 }
@@ -487,11 +634,7 @@ extern "C" vofpc_status vofpc_mlp_gradient(vofpc_ctx ctx, vofpc_mlp M, const flo
   clear_error();
   VOFPC_REQUIRE(ctx && M && X && T && n > 0, VOFPC_E_INVALID_ARG, "mlp_gradient: bad argument");
   VOFPC_HIP(hipSetDevice(ctx->device));
-  vofpc_status s = mlp_gradient(ctx, M, X, T, n);
-  if (s) return s;
-  if (grad) VOFPC_HIP(hipMemcpyAsync(grad, M->grad, sizeof(float) * kParams, hipMemcpyDeviceToDevice, ctx->stream));
-  if (loss) VOFPC_HIP(hipMemcpyAsync(loss, M->loss, sizeof(float), hipMemcpyDeviceToDevice, ctx->stream));
-  return VOFPC_OK;
+  return mlp_gradient(ctx, M, X, T, n, grad, loss, false, 0.f);
 }
 
 extern "C" vofpc_status vofpc_mlp_train_step(vofpc_ctx ctx, vofpc_mlp M, const float *X, const float *T, int64_t n,
@@ -499,16 +642,7 @@ extern "C" vofpc_status vofpc_mlp_train_step(vofpc_ctx ctx, vofpc_mlp M, const f
   clear_error();
   VOFPC_REQUIRE(ctx && M && X && T && n > 0 && lr > 0, VOFPC_E_INVALID_ARG, "mlp_train_step: bad argument");
   VOFPC_HIP(hipSetDevice(ctx->device));
-  vofpc_status s = mlp_gradient(ctx, M, X, T, n);
-  if (s) return s;
-  M->t += 1;
-  const float b1 = 0.9f, b2 = 0.999f;
-  const float bc1 = 1.0f - powf(b1, (float)M->t), bc2 = 1.0f - powf(b2, (float)M->t);
-  adam_kernel<<<(kParams + 255) / 256, 256, 0, ctx->stream>>>(M->master, M->wb, M->m, M->v, M->grad, lr, b1, b2,
-                                                              1e-8f, bc1, bc2);
-  VOFPC_HIP(hipGetLastError());
-  if (loss) VOFPC_HIP(hipMemcpyAsync(loss, M->loss, sizeof(float), hipMemcpyDeviceToDevice, ctx->stream));
-  return VOFPC_OK;
+  return mlp_gradient(ctx, M, X, T, n, nullptr, loss, true, lr);
 }
 
 namespace vofpc {
@@ -536,10 +670,8 @@ vofpc_status launch_bracket(vofpc_ctx ctx, vofpc_mlp M, const float *feat, const
                             const int32_t *counts, int64_t cap, double ksig, double *hlo, double *hhi) {
   VOFPC_REQUIRE(M && feat && prange && counts && hlo && hhi && cap > 0, VOFPC_E_INVALID_ARG,
                 "mlp_bracket: bad argument");
-  int64_t grid = (cap + 15) / 16;
-  if (grid > ctx->n_cu * 8) grid = ctx->n_cu * 8;
-  mlp_bracket_kernel<<<(unsigned)grid, 64, 0, ctx->stream>>>(feat, prange, counts, cap, M->wb, M->master, ksig, hlo,
-                                                             hhi);
+  mlp_bracket_kernel<<<forward_grid(ctx, cap), kNetBlock, 0, ctx->stream>>>(feat, prange, counts, cap, M->wb,
+                                                                            M->master, ksig, hlo, hhi);
   VOFPC_HIP(hipGetLastError());
   return VOFPC_OK;
 }

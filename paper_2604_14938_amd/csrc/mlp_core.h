@@ -36,30 +36,18 @@ __device__ __forceinline__ float from_bf16(uint16_t h) { return __uint_as_float(
 // reciprocal; e^{2|x|} overflowing to infinity gives 1), the sign restored;
 // below, the Taylor series x - x^3/3 + 2x^5/15 - 17x^7/315 (truncation error
 // under 2e-10 there).  Errors of a few 1e-7, far below the BF16 rounding the
-// activations get next.
+// activations get next.  Both are computed and one is selected: a branch
+// around the series costs more than its five instructions.
 __device__ __forceinline__ float act_tanh(float x) {
-  const float ax = fabsf(x);
-  if (ax < 0.125f) {
-    const float x2 = x * x;
-    return x * (1.0f + x2 * (-1.0f / 3.0f + x2 * (2.0f / 15.0f + x2 * (-17.0f / 315.0f))));
-  }
+  const float ax = fabsf(x), x2 = x * x;
+  const float series = x * (1.0f + x2 * (-1.0f / 3.0f + x2 * (2.0f / 15.0f + x2 * (-17.0f / 315.0f))));
   const float e = __builtin_amdgcn_exp2f(2.8853900817779268f * ax);   // 2 log2(e) |x|
-  return copysignf(1.0f - 2.0f * __builtin_amdgcn_rcpf(e + 1.0f), x);
+  const float t = copysignf(1.0f - 2.0f * __builtin_amdgcn_rcpf(e + 1.0f), x);
+  return ax < 0.125f ? series : t;
 }
 
 __device__ __forceinline__ f32x4 mfma16(bf16x4 a, bf16x4 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
-}
-
-// B operand from a row-major weight matrix W[n][k] (B[k][n] = W[n][k]);
-// columns n >= nmax are zero.  The four values of a lane are contiguous and
-// 8-byte aligned (every matrix offset and row length is a multiple of 4), so
-// they come in one load.
-__device__ __forceinline__ bf16x4 b_weightT(const uint16_t *W, int ldk, int lane, int n0, int k0, int nmax) {
-  const int n = n0 + (lane & 15), k = k0 + 4 * (lane >> 4);
-  bf16x4 v = {0, 0, 0, 0};
-  if (n < nmax) v = *reinterpret_cast<const bf16x4 *>(W + n * ldk + k);
-  return v;
 }
 
 // v[l & ~Z] + v[l | Z] on every lane l (Z = 16 or 32) by the gfx950 lane
