@@ -383,10 +383,10 @@ vofpc_status vofpc_extrap_opts_default(vofpc_extrap_opts *opts);
  * alpha, T: DEVICE [n_cells]; T_bface: DEVICE [n_faces]; mixed_idx, counts,
  * itf: the compaction and reconstruction of this alpha; opts may be NULL.
  * gradT_l, gradT_v: DEVICE [3][n_cells], written on D only.  report:
- * optional DEVICE int32[2] = (sweeps done, 0).  Each sweep is one kernel;
- * after convergence the remaining sweep kernels return at once
- * (opts->max_iter kernels are always issued, so a captured graph holds them
- * all; an idle one costs about 1.6 microseconds).  The first
+ * optional DEVICE int32[2] = (sweeps done, 0).  All sweeps run in one
+ * cooperative kernel of at most one block per compute unit, which ends after
+ * the last one needed; a wait for another block that takes 2 seconds ends it
+ * with NaN outputs and a 1 in report[1].  The first
  * call on a mesh allocates its scratch (mesh-owned) and must not be captured;
  * later calls are graph-capturable.  Calls on one mesh must not overlap. */
 vofpc_status vofpc_extrapolate(vofpc_ctx ctx, vofpc_mesh mesh, const double *alpha, const double *T,

@@ -99,16 +99,23 @@ __global__ __launch_bounds__(kCsfBlock) void csf_smooth_kernel(DevMesh m, const 
   }
 }
 
-__global__ __launch_bounds__(kCsfBlock) void csf_seed_faces_kernel(DevMesh m, const double *alpha, int8_t *mark) {
-  const int64_t f = blockIdx.x * (int64_t)kCsfBlock + threadIdx.x;
-  if (f >= m.n_faces) return;
-  const int q = m.face_neigh[f];
-  if (q < 0) return;
-  const int o = m.face_owner[f];
-  if (alpha[o] != alpha[q]) {
-    mark[o] = 0;
-    mark[q] = 0;
+__global__ __launch_bounds__(kRingBlock) void csf_seed_faces_kernel(DevMesh m, const double *alpha, int8_t *mark) {
+  const int64_t f0 = (blockIdx.x * (int64_t)kRingBlock + threadIdx.x) * kRingRun;
+  if (f0 >= m.n_faces) return;
+  int o[kRingRun], q[kRingRun];
+  ring_faces(m, f0, o, q);
+  double ao[kRingRun], aq[kRingRun];
+#pragma unroll
+  for (int t = 0; t < kRingRun; ++t) {
+    ao[t] = alpha[o[t]];
+    aq[t] = q[t] >= 0 ? alpha[q[t]] : ao[t];
   }
+#pragma unroll
+  for (int t = 0; t < kRingRun; ++t)
+    if (q[t] >= 0 && ao[t] != aq[t]) {
+      mark[o[t]] = 0;
+      mark[q[t]] = 0;
+    }
 }
 
 // every cell: alpha_hat = alpha (both smoothing buffers) and every other
@@ -295,17 +302,16 @@ extern "C" vofpc_status vofpc_curvature(vofpc_ctx ctx, vofpc_mesh M, const doubl
   int8_t *mark = M->csf_mark;
   int32_t *list = M->csf_list;
   int32_t *len = M->csf_len + 1;   // [1]: domain length (the gradient reads a band count there)
-  const unsigned gN = (unsigned)std::max<int64_t>(1, (N + kCsfBlock - 1) / kCsfBlock);
-  const unsigned gF = (unsigned)std::max<int64_t>(1, (NF + kCsfBlock - 1) / kCsfBlock);
+  const unsigned gF = ring_face_blocks(NF);
   const unsigned gC = (unsigned)std::max<int64_t>(1, std::min<int64_t>((N + kCsfCells - 1) / kCsfCells,
                                                                          (int64_t)ctx->n_cu * 16));
   const unsigned gE = (unsigned)std::max<int64_t>(1, std::min<int64_t>((N + kCsfBlock - 1) / kCsfBlock,
                                                                          (int64_t)ctx->n_cu * 8));
   // the domain: seed, then n_smooth + 3 rings
   csf_fill_kernel<<<gE, kCsfBlock, 0, s>>>(N, alpha, alpha_hat, tmp, n, kr, ks, kappa, force, mark, len);
-  csf_seed_faces_kernel<<<gF, kCsfBlock, 0, s>>>(M->d, alpha, mark);
+  csf_seed_faces_kernel<<<gF, kRingBlock, 0, s>>>(M->d, alpha, mark);
   for (int l = 1; l <= o.n_smooth + 3; ++l) ring_grow_kernel<<<gF, kRingBlock, 0, s>>>(M->d, mark, l);
-  ring_list_kernel<<<gN, kRingBlock, 0, s>>>(N, mark, list, len);
+  ring_list_kernel<<<ring_list_blocks(N), kRingBlock, 0, s>>>(N, mark, list, len);
   // smoothing: sweep k writes alpha_hat when n_smooth - 1 - k is even, so the
   // last sweep lands there
   const double *src = alpha;

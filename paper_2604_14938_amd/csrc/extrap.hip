@@ -12,15 +12,22 @@
 //   face neighbours; stop at the first sweep whose largest change is below
 //   tol, or after max_iter sweeps.
 //
-// One kernel per sweep: the kernel boundary is the synchronisation.  A grid
-// barrier inside one persistent kernel was measured slower on this chip: with
-// one block per XCD it lacks memory parallelism, and with many blocks every
-// sweep pays device-scope fences that write back and invalidate the per-XCD
-// L2 caches.
+// The domain is grown, listed and given its stencil by kernels of their own; one
+// cooperative kernel then runs every sweep and writes the outputs.  A block
+// keeps its first cells' stencils and values in registers; the iterates go
+// through memory at agent scope (relaxed atomic loads and stores, which meet
+// beyond the per-XCD L2 caches), so a sweep needs no cache write-back or
+// invalidation, only a barrier of flags: each block posts the sweep's number
+// and whether any of its cells still changes, and reads the others'.  With a
+// launch per sweep all of max_iter were issued whether they had work or not:
+// 500 us a call on 97,336 Voronoi cells (19 sweeps of 120, a domain of 16,000
+// cells), now 173.  Five kernels of set-up, 68 us of that, stay: each needs the
+// whole of the one before.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 
+#include "lsq.h"
 #include "ring_ops.h"
 #include "vofpc_internal.h"
 #include "wave_ops.h"
@@ -28,132 +35,160 @@
 namespace vofpc {
 
 constexpr int kExBlock = 256;
-constexpr int kExMaxGrid = 1024;   // blocks of the stencil and sweep kernels at most
+constexpr int kExMaxBlocks = 1024;      // blocks of the sweep kernel at most
+constexpr int8_t kExInterface = 127;    // mark of a domain cell with an interface (layers end at 100)
 
 __device__ __forceinline__ bool is_mixed(double a, double eps) { return a > eps && a < 1.0 - eps; }
 
-// layer 0: the mixed cells; everything else outside; the list length is reset
+// layer 0: the mixed cells; everything else outside; the list length and the
+// barrier flags are reset
 __global__ __launch_bounds__(kExBlock) void ex_init_kernel(int64_t n, const double *alpha, double eps, int8_t *mark,
-                                                           int32_t *info) {
+                                                           int32_t *info, uint32_t *flag) {
   const int64_t P = blockIdx.x * (int64_t)kExBlock + threadIdx.x;
   if (P < n) mark[P] = is_mixed(alpha[P], eps) ? 0 : -1;
-  if (P == 0) {
-    info[1] = 0;
-    info[2] = 0;
-    info[3] = 0;
-    info[4] = 0;
+  for (int64_t i = P; i < 2 * kExMaxBlocks; i += (int64_t)gridDim.x * kExBlock) flag[i] = 0;
+  if (P == 0) info[1] = 0;
+}
+
+// the list of the domain, by the first blocks; by the others, the mixed entry
+// of every domain cell with an interface, and its mark (still at least 0, so
+// the list does not care which comes first)
+__global__ __launch_bounds__(kRingBlock) void ex_list_kernel(int64_t n, int8_t *mark, int32_t *list, int32_t *len,
+                                                             int list_blocks, const int32_t *mixed,
+                                                             const int32_t *counts, vofpc_interface itf,
+                                                             int32_t *entry) {
+  if ((int)blockIdx.x < list_blocks) {
+    ring_list_block(n, mark, list, len, blockIdx.x);
+    return;
   }
-}
-
-// advection direction: unit plain gradient of alpha (computed into nrm by
-// the gradient kernel) ...
-__global__ __launch_bounds__(kExBlock) void ex_normalise_kernel(int64_t N, const int32_t *list, const int32_t *info,
-                                                                double *nrm) {
-  const int64_t j = blockIdx.x * (int64_t)kExBlock + threadIdx.x;
-  if (j >= info[1]) return;
-  const int P = list[j];
-  const double g0 = nrm[P], g1 = nrm[N + P], g2 = nrm[2 * N + P];
-  const double len = sqrt(g0 * g0 + g1 * g1 + g2 * g2);
-  nrm[P] = len > 0 ? g0 / len : 0.0;
-  nrm[N + P] = len > 0 ? g1 / len : 0.0;
-  nrm[2 * N + P] = len > 0 ? g2 / len : 0.0;
-}
-
-// ... replaced by the interface normal where the cell has an interface
-__global__ __launch_bounds__(kExBlock) void ex_interface_normal_kernel(int64_t N, const int32_t *mixed,
-                                                                       const int32_t *counts, vofpc_interface itf,
-                                                                       double *nrm) {
-  int64_t n = counts[0];
-  if (n > itf.cap) n = itf.cap;
-  const int64_t k = blockIdx.x * (int64_t)kExBlock + threadIdx.x;
-  if (k >= n) return;
-  if (!(itf.A[k] > 0)) return;
-  const int P = mixed[k];
-  nrm[P] = itf.n[k];
-  nrm[N + P] = itf.n[itf.cap + k];
-  nrm[2 * N + P] = itf.n[2 * itf.cap + k];
+  int64_t cnt = counts[0];
+  if (cnt > itf.cap) cnt = itf.cap;
+  const int64_t stride = (int64_t)(gridDim.x - list_blocks) * kRingBlock;
+  for (int64_t k = (int64_t)(blockIdx.x - list_blocks) * kRingBlock + threadIdx.x; k < cnt; k += stride) {
+    const int P = mixed[k];
+    if (!(itf.A[k] > 0) || mark[P] < 0) continue;
+    mark[P] = kExInterface;
+    entry[P] = (int32_t)k;
+  }
 }
 
 struct ExParams {
   DevMesh m;
-  const double *alpha;
-  const int32_t *list;
+  const double *alpha, *T, *Tb;
+  double T_sat;
+  vofpc_interface itf;
+  const int32_t *list, *entry;
   double *wup;      // per cell-face slot: upwind weights w_f / sum w, packed at the front of each cell's slots
   int32_t *upn;     // per cell-face slot: the neighbour of each packed upwind weight
   int2 *upr;        // per domain entry: first slot and number of its packed upwind weights
   double *theta;    // per domain entry: pseudo-time fraction min(dtau sum w / V, 1), 0 without upwind faces
-  int32_t *info;
-  double *part;     // [2][grid] per-block largest change of the last two sweeps
+  const int32_t *info;
+  uint32_t *flag;
   const int8_t *mark;
-  const double *nrm;
   double *buf;   // [2][N][kExRec]
   double dtau, tol;
   int max_iter;
   double *gl, *gv;
+  int32_t *report;
 };
 
-constexpr int kExLanes = 8;   // lanes per domain cell in the stencil and sweeps (half a DPP row)
-constexpr int kExBlocksPerCu = 4;   // stencil and sweep blocks per CU
+constexpr int kExLanes = 8;   // lanes per domain cell in the stencil (half a DPP row)
 // The two iterates of both fields: one 64-byte record per cell and iterate,
 // G_l in words 0-2 and G_v in words 3-5, so a neighbour's gathered
 // components share one cache line.
 constexpr int kExRec = 8;
 
-// Upwind weight of cell-face slot i of cell P for velocity c: w_f = -c.S_f
-// (S_f outward from P) when that is positive and the neighbour Q is in the
-// domain, else 0.
-__device__ __forceinline__ double ex_up_weight(const ExParams &p, int P, double c0, double c1, double c2, int64_t i,
-                                               int &Q) {
-  const DevMesh &m = p.m;
-  const int64_t NF = m.n_faces;
-  Q = m.cf_nbr[i];
-  if (Q < 0 || p.mark[Q] < 0) return 0.0;
-  const int f = m.cell_face[i];
-  const double sg = (m.face_owner[f] == P) ? 1.0 : -1.0;
-  const double cs = c0 * (sg * m.Sf[f]) + c1 * (sg * m.Sf[NF + f]) + c2 * (sg * m.Sf[2 * NF + f]);
-  return cs < 0.0 ? -cs : 0.0;
-}
-
-// The upwind stencil of domain entry j, fixed for the whole iteration (and
-// the start of both fields, the gradient p.gl, written to both iterates): with
-// c = sgn(alpha - 1/2) n, the faces with c.S_f < 0 (S_f outward) whose
-// neighbour is in the domain get w_f = -c.S_f; those faces, in slot order,
-// are packed at the front of the cell's slot range as (w_f / sum w,
-// neighbour), the entry keeps (first slot, count) and
-// theta = min(dtau sum w / V_P, 1) (0 when no face is upwind: no update).
+// Domain entry j by a group of kExLanes lanes, fixed for the whole iteration:
+//   - the interface-modified gradient of T, the start of both fields, written
+//     to both iterates and to p.gl;
+//   - the advection direction c = sgn(alpha - 1/2) n, n the interface normal
+//     where the cell has an interface, else the unit plain gradient of alpha
+//     over interior neighbours;
+//   - the faces with c.S_f < 0 (S_f outward) whose neighbour is in the domain
+//     get w_f = -c.S_f; those faces, in slot order, are packed at the front of
+//     the cell's slot range as (w_f / sum w, neighbour), the entry keeps
+//     (first slot, count) and theta = min(dtau sum w / V_P, 1) (0 when no
+//     face is upwind: no update).
+// Both gradients come from one walk over the faces: their stencils share the
+// neighbours' centres and alphas.
 __device__ __forceinline__ void ex_stencil(const ExParams &p, int64_t j, int lane) {
   const DevMesh &m = p.m;
-  const int64_t N = m.n_cells;
+  const int64_t N = m.n_cells, NF = m.n_faces;
   const int P = p.list[j];
-  if (lane < 3) {
-    // both fields start from the gradient (each iterate)
-    const double g = p.gl[lane * N + P];
-    double *rec0 = p.buf + (int64_t)P * kExRec, *rec1 = p.buf + ((int64_t)N + P) * kExRec;
-    rec0[lane] = g;
-    rec0[3 + lane] = g;
-    rec1[lane] = g;
-    rec1[3 + lane] = g;
-  }
-  const double sgn = p.alpha[P] >= 0.5 ? 1.0 : -1.0;
-  const double c0 = sgn * p.nrm[P], c1 = sgn * p.nrm[N + P], c2 = sgn * p.nrm[2 * N + P];
   const int64_t i0 = m.cell_face_off[P], i1 = m.cell_face_off[P + 1];
+  const double x0 = m.xc[P], x1 = m.xc[N + P], x2 = m.xc[2 * N + P];
+  const double aP = p.alpha[P], TP = p.T[P];
+  const int8_t mk = p.mark[P];
+  LsqSums L, A;   // of T, of alpha
+  for (int64_t i = i0 + lane; i < i1; i += kExLanes) {
+    const int q = m.cf_nbr[i];
+    if (q >= 0) {
+      double r0 = m.xc[q] - x0, r1 = m.xc[N + q] - x1, r2 = m.xc[2 * N + q] - x2;
+      const double aQ = p.alpha[q];
+      double val = p.T[q];
+      A.add(r0, r1, r2, aQ - aP, 0);
+      if ((aP - 0.5) * (aQ - 0.5) < 0.0) {
+        const double t = (aP - 0.5) / (aP - aQ);
+        r0 *= t; r1 *= t; r2 *= t;
+        val = p.T_sat;
+      }
+      L.add(r0, r1, r2, val - TP, 0);
+    } else if (q == -1) {
+      const int f = m.cell_face[i];
+      L.add(m.xf[f] - x0, m.xf[NF + f] - x1, m.xf[2 * NF + f] - x2, p.Tb[f] - TP, 0);
+    }
+  }
+  lsq_reduce<kExLanes>(L);
+  double g[3];
+  (void)lsq_solve(L, g[0], g[1], g[2]);   // a singular stencil gives zero
+  double c0, c1, c2;
+  if (mk == kExInterface) {
+    const int64_t k = p.entry[P], cap = p.itf.cap;
+    c0 = p.itf.n[k]; c1 = p.itf.n[cap + k]; c2 = p.itf.n[2 * cap + k];
+  } else {
+    lsq_reduce<kExLanes>(A);
+    (void)lsq_solve(A, c0, c1, c2);
+    const double len = sqrt(c0 * c0 + c1 * c1 + c2 * c2);
+    c0 = len > 0 ? c0 / len : 0.0;
+    c1 = len > 0 ? c1 / len : 0.0;
+    c2 = len > 0 ? c2 / len : 0.0;
+  }
+  if (lane < 3) {
+    const double v = lane == 0 ? g[0] : (lane == 1 ? g[1] : g[2]);
+    double *rec0 = p.buf + (int64_t)P * kExRec, *rec1 = p.buf + ((int64_t)N + P) * kExRec;
+    rec0[lane] = v;
+    rec0[3 + lane] = v;
+    rec1[lane] = v;
+    rec1[3 + lane] = v;
+    p.gl[lane * N + P] = v;
+  }
+  const double sgn = aP >= 0.5 ? 1.0 : -1.0;
+  c0 *= sgn; c1 *= sgn; c2 *= sgn;
+  // w_f of slot i: -c.S_f when that is positive and the neighbour Q is in the domain, else 0
+  auto weight = [&](int64_t i, int &Q) -> double {
+    Q = m.cf_nbr[i];
+    if (Q < 0 || p.mark[Q] < 0) return 0.0;
+    const double *S = m.cf_S + 3 * i;
+    const double cs = c0 * S[0] + c1 * S[1] + c2 * S[2];
+    return cs < 0.0 ? -cs : 0.0;
+  };
   double w = 0.0;
   for (int64_t i = i0 + lane; i < i1; i += kExLanes) {
     int Q;
-    w += ex_up_weight(p, P, c0, c1, c2, i, Q);
+    w += weight(i, Q);
   }
   w = gsum<kExLanes>(w);
   // the lanes of a group share the cell, so they run the same rounds; each
   // round packs its upwind slots after those of the rounds before
-  const int gl0 = (threadIdx.x & 63) & ~(kExLanes - 1);
+  const int first = (threadIdx.x & 63) & ~(kExLanes - 1);
   const uint64_t below = (1ull << lane) - 1;
   int n = 0;
   for (int64_t k0 = i0; k0 < i1; k0 += kExLanes) {
     const int64_t i = k0 + lane;
     int Q = -1;
-    const double wf = (i < i1 && w > 0.0) ? ex_up_weight(p, P, c0, c1, c2, i, Q) : 0.0;
+    const double wf = (i < i1 && w > 0.0) ? weight(i, Q) : 0.0;
     const bool up = wf > 0.0;
-    const uint64_t gm = (__ballot(up) >> gl0) & ((1ull << kExLanes) - 1);
+    const uint64_t gm = (__ballot(up) >> first) & ((1ull << kExLanes) - 1);
     if (up) {
       const int64_t o = i0 + n + __popcll(gm & below);
       p.wup[o] = wf / w;
@@ -180,145 +215,150 @@ __global__ __launch_bounds__(kExBlock) void ex_stencil_kernel(ExParams p) {
     ex_stencil(p, j, lane);
 }
 
-// Upwind update of domain entry j from iterate cur by a group of kExLanes
-// lanes, one packed upwind slot per lane and round: the new values of its three advanced
-// components and their largest change (ex_compute), written into the next
-// iterate by ex_store.  The kept field was written to both iterates at the
-// start and is not touched.
-struct ExNew {
-  int P, adv;
-  double n0, n1, n2, change;
-};
-
-__device__ __forceinline__ ExNew ex_compute(const ExParams &p, int64_t j, int lane, const double *cur) {
-  const DevMesh &m = p.m;
-  const int64_t N = m.n_cells;
-  ExNew r;
-  r.P = p.list[j];
-  r.adv = p.alpha[r.P] >= 0.5 ? 3 : 0;   // G_v advances in liquid, G_l in vapour
-  const double *ca = cur + r.adv;
-  const int2 ur = p.upr[j];
-  double a0 = 0.0, a1 = 0.0, a2 = 0.0;
-  for (int k = lane; k < ur.y; k += kExLanes) {
-    const double wf = p.wup[ur.x + k];
-    const double *q = ca + (int64_t)p.upn[ur.x + k] * kExRec;
-    a0 += wf * q[0];
-    a1 += wf * q[1];
-    a2 += wf * q[2];
-  }
-  a0 = gsum<kExLanes>(a0);
-  a1 = gsum<kExLanes>(a1);
-  a2 = gsum<kExLanes>(a2);
-  const double th = p.theta[j];
-  const int P = r.P;
-  const double *o = ca + (int64_t)P * kExRec;
-  const double o0 = o[0], o1 = o[1], o2 = o[2];
-  r.n0 = o0 + th * (a0 - o0);
-  r.n1 = o1 + th * (a1 - o1);
-  r.n2 = o2 + th * (a2 - o2);
-  r.change = fmax(fabs(r.n0 - o0), fmax(fabs(r.n1 - o1), fabs(r.n2 - o2)));
-  return r;
+// Values that blocks exchange within the sweep kernel: agent scope, relaxed.
+__device__ __forceinline__ double agent_load(const double *a) {
+  return __hip_atomic_load(a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void agent_store(double *a, double v) {
+  __hip_atomic_store(a, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__device__ __forceinline__ void ex_store(const ExParams &p, const ExNew &r, double *nxt) {
-  const int64_t N = p.m.n_cells;
-  double *na = nxt + (int64_t)r.P * kExRec + r.adv;
-  na[0] = r.n0;
-  na[1] = r.n1;
-  na[2] = r.n2;
-}
-
-// Sweep `it` (0-based) of the Jacobi iteration.  From the second sweep on it
-// first reads the largest change of the previous sweep (complete: it ran in
-// the previous kernel): below tol, the iteration has converged after `it`
-// sweeps and this and every later sweep kernel return at once.
-__global__ __launch_bounds__(kExBlock) void ex_sweep_kernel(ExParams p, int it) {
-  __shared__ double red[kExBlock / 64];
-  const int converged = p.info[4];
-  const int64_t nd = p.info[1];
-  if (converged) return;
-  const int64_t N = p.m.n_cells;
-  const double *cur = p.buf + (int64_t)(it & 1) * kExRec * N;
-  double *nxt = p.buf + (int64_t)((it + 1) & 1) * kExRec * N;
-  // groups of kExLanes lanes take the domain cells; every lane of a group
-  // sees the same cells, so the group reductions see all its lanes.  The
-  // group's first cell is computed before the convergence test of the
-  // previous sweep (its gathers and that test's reads are in flight
-  // together) and stored after.
-  constexpr int kCells = kExBlock / kExLanes;
-  const int lane = threadIdx.x % kExLanes;
-  const int64_t j0 = blockIdx.x * (int64_t)kCells + threadIdx.x / kExLanes;
-  const int64_t stride = (int64_t)gridDim.x * kCells;
-  ExNew first{0, 0, 0.0, 0.0, 0.0, 0.0};
-  if (j0 < nd) first = ex_compute(p, j0, lane, cur);
-  if (it > 0) {
-    // largest change of the previous sweep: the maximum of its blocks'
-    // partial maxima (every block of that kernel wrote its slot)
-    const double *part = p.part + (int64_t)((it - 1) & 1) * gridDim.x;
-    double prev = 0.0;
-    for (int b = threadIdx.x; b < (int)gridDim.x; b += kExBlock) prev = fmax(prev, part[b]);
-    for (int o = 32; o > 0; o >>= 1) prev = fmax(prev, __shfl_xor(prev, o));
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = prev;
-    __syncthreads();
-    prev = red[0];
-    for (int i = 1; i < kExBlock / 64; ++i) prev = fmax(prev, red[i]);
-    __syncthreads();
-    if (prev < p.tol) {
-      if (blockIdx.x == 0 && threadIdx.x == 0) {
-        p.info[4] = 1;
-        p.info[2] = it;
+// Barrier over the first nb blocks of a cooperative launch, epoch 1, 2, ...:
+// every agent-scope store made before it is seen by every agent-scope load
+// after it.  Returns in `any` whether some block brought `mine`.  The flags
+// alternate between two rows, so a block that runs ahead cannot overwrite a
+// flag that is still to be read.  The first wavefront polls for its block
+// (1.6 us a barrier of 16 blocks, 2.4 of 64, 3.2 of 256; with every wavefront
+// in the poll 4.3 and 6.2).  All blocks are resident, so the wait ends; should
+// one never come, it ends after kExWaitTicks (2 s) with false.
+constexpr uint64_t kExWaitTicks = 200000000ull;   // of the 100 MHz wall clock
+__device__ __forceinline__ bool sweep_barrier(uint32_t *flag, int nb, uint32_t epoch, bool mine, bool &any) {
+  __shared__ int seen;   // bit 0: some block brought mine, bit 1: a wait ended without its flag
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wavefront's stores have reached the agent's memory
+  const int b = __syncthreads_or(mine ? 1 : 0);
+  if (threadIdx.x < 64) {
+    uint32_t *f = flag + (epoch & 1) * kExMaxBlocks;
+    if (threadIdx.x == 0)
+      __hip_atomic_store(f + blockIdx.x, (epoch << 1) | (b ? 1u : 0u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    bool a = false, ok = true;
+    for (int i = threadIdx.x; i < nb && ok; i += 64) {
+      uint32_t v = __hip_atomic_load(f + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if ((v >> 1) != epoch) {
+        const uint64_t t0 = wall_clock64();
+        do {
+          v = __hip_atomic_load(f + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          ok = wall_clock64() - t0 < kExWaitTicks;
+        } while ((v >> 1) != epoch && ok);
       }
-      return;
+      a = a || (v & 1u);
     }
+    const bool some = __any(a), bad = __any(!ok);
+    if (threadIdx.x == 0) seen = (some ? 1 : 0) | (bad ? 2 : 0);
   }
-  double change = 0.0;
-  if (j0 < nd && lane == 0) {
-    ex_store(p, first, nxt);
-    change = first.change;
-  }
-  for (int64_t j = j0 + stride; j < nd; j += stride) {
-    const ExNew r = ex_compute(p, j, lane, cur);
-    if (lane == 0) {
-      ex_store(p, r, nxt);
-      change = fmax(change, r.change);
-    }
-  }
-  // this block's largest change into its slot of this sweep's partials
-  // (plain stores: the next sweep kernel reads them after the kernel boundary)
-  for (int o = 32; o > 0; o >>= 1) change = fmax(change, __shfl_xor(change, o));
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = change;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    double b = red[0];
-    for (int i = 1; i < kExBlock / 64; ++i) b = fmax(b, red[i]);
-    p.part[(int64_t)(it & 1) * gridDim.x + blockIdx.x] = b;
-  }
+  const int r = seen;   // the next write to it comes after the next barrier's __syncthreads_or
+  any = (r & 1) != 0;
+  return (r & 2) == 0;
 }
 
-// After the last sweep kernel: the number of sweeps done, and the outputs on
-// the domain from the buffer of the newest iterate.
-__global__ __launch_bounds__(kExBlock) void ex_finish_kernel(ExParams p) {
-  const int64_t N = p.m.n_cells;
-  const int64_t nd = p.info[1];
-  // converged: the count the first idle sweep kernel recorded; otherwise
-  // every sweep ran (the last one counts whether or not it met the tolerance)
-  const int sweeps = p.info[4] ? p.info[2] : p.max_iter;
-  const double *fin = p.buf + (int64_t)(sweeps & 1) * kExRec * N;
-  for (int64_t j = blockIdx.x * (int64_t)kExBlock + threadIdx.x; j < nd; j += (int64_t)gridDim.x * kExBlock) {
-    const int P = p.list[j];
-    const double *rec = fin + (int64_t)P * kExRec;
-    for (int d = 0; d < 3; ++d) {
-      p.gl[d * N + P] = rec[d];
-      p.gv[d * N + P] = rec[3 + d];
+// Every Jacobi sweep, and the outputs.  Four lanes per domain cell, one for
+// each component of the advanced field (the last one only keeps the groups
+// aligned): the three lanes of a cell read a neighbour's components as one
+// 24-byte piece of its record, so a sweep makes one request per upwind slot.
+// A group's first cell stays in registers (its value, and up to kItSlots
+// weights and neighbours); its further cells (domains beyond 65,536 cells) are
+// read again each sweep (two kept cells spill: 8.1 us a sweep of 16,000 cells
+// for 5.7).  The kept field was written to both iterates at the
+// start and is not touched.  After a sweep whose largest change is below tol,
+// or max_iter sweeps, the newest values go to the outputs.  Only as many blocks
+// as the domain fills take part: a sweep over 16,000 cells is bound by the
+// round trips of the gathers and of its barrier.
+constexpr int kItBlock = 1024, kItLanes = 4, kItCells = kItBlock / kItLanes, kItSlots = 10;
+__global__ __launch_bounds__(kItBlock) void ex_iterate_kernel(ExParams p) {
+  const int64_t N = p.m.n_cells, nd = p.info[1];
+  const int nb = (int)std::min<int64_t>(gridDim.x, std::max<int64_t>(1, (nd + kItCells - 1) / kItCells));
+  if ((int)blockIdx.x >= nb) return;
+  const int d = threadIdx.x % kItLanes;
+  const bool comp = d < 3;
+  const int64_t j0 = (int64_t)blockIdx.x * kItCells + threadIdx.x / kItLanes, stride = (int64_t)nb * kItCells;
+  // the group's first cell: word `at` of its record (its advanced component
+  // d) with its value, and the neighbours and weights of its first slots
+  int P = 0, at = 0, cnt = 0, first = 0, nbr[kItSlots];
+  double th = 0.0, v = 0.0, w[kItSlots];
+  const bool has = comp && j0 < nd;
+  if (has) {
+    P = p.list[j0];
+    at = (p.alpha[P] >= 0.5 ? 3 : 0) + d;   // G_v advances in liquid, G_l in vapour
+    const int2 ur = p.upr[j0];
+    first = ur.x;
+    cnt = ur.y;
+    th = p.theta[j0];
+    v = p.buf[(int64_t)P * kExRec + at];
+  }
+#pragma unroll
+  for (int k = 0; k < kItSlots; ++k) {
+    w[k] = k < cnt ? p.wup[first + k] : 0.0;
+    nbr[k] = k < cnt ? p.upn[first + k] : 0;
+  }
+  int sweeps = 0;
+  bool ok = true;
+  while (sweeps < p.max_iter) {
+    const double *cur = p.buf + (int64_t)(sweeps & 1) * kExRec * N;
+    double *nxt = p.buf + (int64_t)((sweeps + 1) & 1) * kExRec * N;
+    double change = 0.0;
+    if (has) {
+      const double *from = cur + at;
+      double q[kItSlots], a = 0.0;
+#pragma unroll
+      for (int k = 0; k < kItSlots; ++k) q[k] = k < cnt ? agent_load(from + (int64_t)nbr[k] * kExRec) : 0.0;
+#pragma unroll
+      for (int k = 0; k < kItSlots; ++k) a += w[k] * q[k];
+      for (int k = kItSlots; k < cnt; ++k)
+        a += p.wup[first + k] * agent_load(from + (int64_t)p.upn[first + k] * kExRec);
+      const double n = v + th * (a - v);
+      change = fmax(change, fabs(n - v));   // (a NaN does not hold the others back)
+      v = n;
+      agent_store(nxt + (int64_t)P * kExRec + at, n);
     }
+    for (int64_t j = j0 + stride; comp && j < nd; j += stride) {
+      const int C = p.list[j], c = (p.alpha[C] >= 0.5 ? 3 : 0) + d;
+      const int2 ur = p.upr[j];
+      const double o = agent_load(cur + (int64_t)C * kExRec + c), t = p.theta[j];
+      double a = 0.0;
+#pragma unroll 8
+      for (int k = 0; k < ur.y; ++k)
+        a += p.wup[ur.x + k] * agent_load(cur + (int64_t)p.upn[ur.x + k] * kExRec + c);
+      const double n = o + t * (a - o);
+      change = fmax(change, fabs(n - o));
+      agent_store(nxt + (int64_t)C * kExRec + c, n);
+    }
+    ++sweeps;
+    if (sweeps == p.max_iter) break;   // (each group reads back its own cells alone)
+    bool more;
+    ok = sweep_barrier(p.flag, nb, (uint32_t)sweeps, !(change < p.tol), more);
+    if (!ok || !more) break;
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) p.info[2] = sweeps;
-}
-
-__global__ void ex_report_kernel(const int32_t *info, int32_t *out) {
-  if (threadIdx.x == 0) {
-    out[0] = info[2];
-    out[1] = info[3];
+  // outputs: the advanced field from the newest iterate, the kept one from the
+  // gradient both started from (in gl)
+  const double *fin = p.buf + (int64_t)(sweeps & 1) * kExRec * N;
+  auto put = [&](int C, int c, double x) {
+    const int64_t o = d * N + C;
+    if (!ok) x = __builtin_nan("");   // no result rather than an early one
+    if (c >= 3) {
+      p.gv[o] = x;
+    } else {
+      p.gv[o] = p.gl[o];
+      p.gl[o] = x;
+    }
+  };
+  if (has) put(P, at, v);
+  for (int64_t j = j0 + stride; comp && j < nd; j += stride) {
+    const int C = p.list[j], c = (p.alpha[C] >= 0.5 ? 3 : 0) + d;
+    put(C, c, agent_load(fin + (int64_t)C * kExRec + c));
+  }
+  if (p.report && blockIdx.x == 0 && threadIdx.x == 0) {
+    p.report[0] = sweeps;
+    p.report[1] = ok ? 0 : 1;
   }
 }
 
@@ -364,38 +404,38 @@ extern "C" vofpc_status vofpc_extrapolate(vofpc_ctx ctx, vofpc_mesh M, const dou
          *h = nullptr, *i = nullptr, *j = nullptr;
     vofpc_status st;
     if ((st = mesh_scratch_alloc(M, (size_t)N, &a)) || (st = mesh_scratch_alloc(M, 4 * (size_t)N, &b)) ||
-        (st = mesh_scratch_alloc(M, 32, &c)) || (st = mesh_scratch_alloc(M, 16 * kExMaxGrid, &d)) ||
-        (st = mesh_scratch_alloc(M, 24 * (size_t)N, &e)) || (st = mesh_scratch_alloc(M, 16 * sizeof(double) * (size_t)N, &f)) ||
+        (st = mesh_scratch_alloc(M, 32, &c)) || (st = mesh_scratch_alloc(M, 2 * kExMaxBlocks * sizeof(uint32_t), &d)) ||
+        (st = mesh_scratch_alloc(M, 4 * (size_t)N, &e)) || (st = mesh_scratch_alloc(M, 16 * sizeof(double) * (size_t)N, &f)) ||
         (st = mesh_scratch_alloc(M, 8 * (size_t)M->ncf, &g)) || (st = mesh_scratch_alloc(M, 8 * (size_t)N, &h)) ||
         (st = mesh_scratch_alloc(M, 4 * (size_t)M->ncf, &i)) || (st = mesh_scratch_alloc(M, 8 * (size_t)N, &j)))
       return st;
-    M->ex_mark = (int8_t *)a; M->ex_list = (int32_t *)b; M->ex_info = (int32_t *)c; M->ex_part = (double *)d;
-    M->ex_nrm = (double *)e; M->ex_buf = (double *)f; M->ex_wup = (double *)g; M->ex_theta = (double *)h;
+    M->ex_mark = (int8_t *)a; M->ex_list = (int32_t *)b; M->ex_info = (int32_t *)c; M->ex_flag = (uint32_t *)d;
+    M->ex_entry = (int32_t *)e; M->ex_wup = (double *)g; M->ex_theta = (double *)h;
     M->ex_upn = (int32_t *)i; M->ex_upr = (int2 *)j;
+    M->ex_buf = (double *)f;
   }
-  const unsigned gN = (unsigned)((N + kExBlock - 1) / kExBlock), gF = (unsigned)((NF + kExBlock - 1) / kExBlock);
-  ex_init_kernel<<<gN, kExBlock, 0, s>>>(N, alpha, o.eps_mixed, M->ex_mark, M->ex_info);
-  for (int l = 1; l <= o.layers; ++l) ring_grow_kernel<<<gF, kRingBlock, 0, s>>>(M->d, M->ex_mark, l);
-  ring_list_kernel<<<gN, kRingBlock, 0, s>>>(N, M->ex_mark, M->ex_list, M->ex_info + 1);
+  const unsigned gN = (unsigned)((N + kExBlock - 1) / kExBlock);
+  ex_init_kernel<<<gN, kExBlock, 0, s>>>(N, alpha, o.eps_mixed, M->ex_mark, M->ex_info, M->ex_flag);
+  for (int l = 1; l <= o.layers; ++l)
+    ring_grow_kernel<<<ring_face_blocks(NF), kRingBlock, 0, s>>>(M->d, M->ex_mark, l);
+  const unsigned gL = ring_list_blocks(N);
+  const unsigned gM = (unsigned)std::min<int64_t>((std::min<int64_t>(itf->cap, N) + kRingBlock - 1) / kRingBlock,
+                                                  (int64_t)ctx->n_cu * 4);
+  ex_list_kernel<<<gL + gM, kRingBlock, 0, s>>>(N, M->ex_mark, M->ex_list, M->ex_info + 1, (int)gL, mixed_idx, counts,
+                                                *itf, M->ex_entry);
   VOFPC_HIP(hipGetLastError());
-  // gradient of T (interface-modified) and of alpha (plain, interior
-  // neighbours only) on the domain; the domain length sits in ex_info[1],
-  // where the gradient kernel reads its band count
-  const int32_t *dom_counts = M->ex_info;
-  vofpc_status st = launch_grad2(ctx, M, M->ex_list, dom_counts, T, T_bface, T_sat, alpha, VOFPC_GRAD_MODIFIED,
-                                 gradT_l, alpha, nullptr, 0.0, alpha, VOFPC_GRAD_STANDARD, M->ex_nrm);
-  if (st) return st;
-  ex_normalise_kernel<<<gN, kExBlock, 0, s>>>(N, M->ex_list, M->ex_info, M->ex_nrm);
-  const unsigned gM = (unsigned)((std::min<int64_t>(itf->cap, N) + kExBlock - 1) / kExBlock);
-  ex_interface_normal_kernel<<<gM, kExBlock, 0, s>>>(N, mixed_idx, counts, *itf, M->ex_nrm);
   ExParams p;
   p.m = M->d;
   p.alpha = alpha;
+  p.T = T;
+  p.Tb = T_bface;
+  p.T_sat = T_sat;
+  p.itf = *itf;
   p.list = M->ex_list;
+  p.entry = M->ex_entry;
   p.info = M->ex_info;
-  p.part = M->ex_part;
+  p.flag = M->ex_flag;
   p.mark = M->ex_mark;
-  p.nrm = M->ex_nrm;
   p.buf = M->ex_buf;
   p.wup = M->ex_wup;
   p.upn = M->ex_upn;
@@ -406,20 +446,23 @@ extern "C" vofpc_status vofpc_extrapolate(vofpc_ctx ctx, vofpc_mesh M, const dou
   p.max_iter = o.max_iter;
   p.gl = gradT_l;
   p.gv = gradT_v;
-  // sweeps: 16 domain cells per block, four blocks per CU (a domain of
-  // 16k cells in one pass: each pass is a chain of dependent gathers); the
-  // finish kernel one cell per thread
-  const unsigned gS = (unsigned)std::max<int64_t>(1, std::min<int64_t>(gN, (int64_t)ctx->n_cu * 2));
+  p.report = report;
+  // the stencil: 32 domain cells per block, four blocks per CU; the sweeps: a
+  // block per CU at most (they must all be resident), fewer for a mesh that
+  // cannot fill them
+  const int64_t stencil_cells = kExBlock / kExLanes;
   const unsigned gW = (unsigned)std::max<int64_t>(
-      1, std::min<int64_t>((N + kExBlock / kExLanes - 1) / (kExBlock / kExLanes),
-                           std::min<int64_t>((int64_t)ctx->n_cu * kExBlocksPerCu, kExMaxGrid)));
-  // the upwind stencil once; then one kernel per sweep: the kernel boundary
-  // orders the sweeps, and once the tolerance is met the remaining sweep
-  // kernels return at once
+      1, std::min<int64_t>((N + stencil_cells - 1) / stencil_cells, (int64_t)ctx->n_cu * 4));
   ex_stencil_kernel<<<gW, kExBlock, 0, s>>>(p);
-  for (int it = 0; it < o.max_iter; ++it) ex_sweep_kernel<<<gW, kExBlock, 0, s>>>(p, it);
-  ex_finish_kernel<<<gS, kExBlock, 0, s>>>(p);
-  if (report) ex_report_kernel<<<1, 64, 0, s>>>(M->ex_info, report);
+  const unsigned gI = (unsigned)std::max<int64_t>(
+      1, std::min<int64_t>((N + kItCells - 1) / kItCells, std::min<int64_t>(ctx->n_cu, kExMaxBlocks)));
+  if (o.max_iter <= 1) {   // no barrier: an ordinary launch, 12 us cheaper
+    ex_iterate_kernel<<<gI, kItBlock, 0, s>>>(p);
+  } else {
+    void *args[] = {&p};
+    VOFPC_HIP(hipLaunchCooperativeKernel(reinterpret_cast<const void *>(ex_iterate_kernel), dim3(gI), dim3(kItBlock),
+                                         args, 0, s));
+  }
   VOFPC_HIP(hipGetLastError());
   return VOFPC_OK;
 }

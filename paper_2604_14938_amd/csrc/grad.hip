@@ -9,6 +9,7 @@
 // use the stored inverse (VOFPC_SCOPE_ALL).
 #include <hip/hip_runtime.h>
 
+#include "lsq.h"
 #include "vofpc_internal.h"
 #include "wave_ops.h"
 
@@ -25,19 +26,6 @@ struct GradParams {
   const int32_t *xn_cell;
   double *grad;
   int32_t *status;
-};
-
-// least-squares sums of one cell: G (6 components) and b
-struct LsqSums {
-  double xx = 0, yy = 0, zz = 0, xy = 0, xz = 0, yz = 0, b0 = 0, b1 = 0, b2 = 0;
-  __device__ __forceinline__ void add(double r0, double r1, double r2, double dv, int weight) {
-    double w = 1.0;
-    if (weight == 1) w = 1.0 / sqrt(r0 * r0 + r1 * r1 + r2 * r2);
-    else if (weight == 2) w = 1.0 / (r0 * r0 + r1 * r1 + r2 * r2);
-    const double w0 = w * r0, w1 = w * r1, w2 = w * r2;
-    xx += w0 * r0; yy += w1 * r1; zz += w2 * r2; xy += w0 * r1; xz += w0 * r2; yz += w1 * r2;
-    b0 += w0 * dv; b1 += w1 * dv; b2 += w2 * dv;
-  }
 };
 
 constexpr int kGradLanes = 8;   // lanes per cell (half a DPP row)
@@ -80,10 +68,7 @@ __device__ __forceinline__ void grad_cell(const GradParams &p, int P, int j) {
       L.add(m.xf[f] - xP0, m.xf[NF + f] - xP1, m.xf[2 * NF + f] - xP2, p.Tb[f] - TP, p.weight);
     }
   }
-  double xx = L.xx, yy = L.yy, zz = L.zz, xy = L.xy, xz = L.xz, yz = L.yz, b0 = L.b0, b1 = L.b1, b2 = L.b2;
-  xx = gsum<kGradLanes>(xx); yy = gsum<kGradLanes>(yy); zz = gsum<kGradLanes>(zz);
-  xy = gsum<kGradLanes>(xy); xz = gsum<kGradLanes>(xz); yz = gsum<kGradLanes>(yz);
-  b0 = gsum<kGradLanes>(b0); b1 = gsum<kGradLanes>(b1); b2 = gsum<kGradLanes>(b2);
+  lsq_reduce<kGradLanes>(L);
   crossed = gsum_i<kGradLanes>(crossed);
   if (j != 0) return;
   double g0, g1, g2;
@@ -94,24 +79,12 @@ __device__ __forceinline__ void grad_cell(const GradParams &p, int P, int j) {
     const double *gi = m.ginv;
     const double ixx = gi[P], iyy = gi[N + P], izz = gi[2 * N + P];
     const double ixy = gi[3 * N + P], ixz = gi[4 * N + P], iyz = gi[5 * N + P];
-    g0 = ixx * b0 + ixy * b1 + ixz * b2;
-    g1 = ixy * b0 + iyy * b1 + iyz * b2;
-    g2 = ixz * b0 + iyz * b1 + izz * b2;
+    g0 = ixx * L.b0 + ixy * L.b1 + ixz * L.b2;
+    g1 = ixy * L.b0 + iyy * L.b1 + iyz * L.b2;
+    g2 = ixz * L.b0 + iyz * L.b1 + izz * L.b2;
     if (ixx == 0 && iyy == 0 && izz == 0) st = VOFPC_CELL_G_SINGULAR;
-  } else {
-    const double c00 = yy * zz - yz * yz, c01 = xz * yz - xy * zz, c02 = xy * yz - xz * yy;
-    const double c11 = xx * zz - xz * xz, c12 = xy * xz - xx * yz, c22 = xx * yy - xy * xy;
-    const double det = xx * c00 + xy * c01 + xz * c02;
-    const double tr = (xx + yy + zz) * (1.0 / 3.0);
-    if (det > 1e-12 * tr * tr * tr) {
-      const double id = 1.0 / det;
-      g0 = (c00 * b0 + c01 * b1 + c02 * b2) * id;
-      g1 = (c01 * b0 + c11 * b1 + c12 * b2) * id;
-      g2 = (c02 * b0 + c12 * b1 + c22 * b2) * id;
-    } else {
-      g0 = g1 = g2 = 0.0;
-      st = VOFPC_CELL_G_SINGULAR;
-    }
+  } else if (!lsq_solve(L, g0, g1, g2)) {
+    st = VOFPC_CELL_G_SINGULAR;
   }
   p.grad[P] = g0;
   p.grad[N + P] = g1;
@@ -130,21 +103,6 @@ __global__ __launch_bounds__(256) void grad_kernel(GradParams p) {
   for (int64_t k = blockIdx.x * (int64_t)kCellsPerBlock + threadIdx.x / kGradLanes; k < n; k += stride) {
     const int P = (p.scope == VOFPC_SCOPE_ALL) ? (int)k : p.band[k];
     grad_cell(p, P, j);
-  }
-}
-
-// Two gradients over the same band list in one launch (the group computes
-// both for its cell; used where a caller needs two fields' gradients on one
-// domain).
-__global__ __launch_bounds__(256) void grad2_kernel(GradParams a, GradParams b) {
-  const int64_t n = a.counts[1];
-  constexpr int kCellsPerBlock = 256 / kGradLanes;
-  const int j = threadIdx.x % kGradLanes;
-  const int64_t stride = (int64_t)gridDim.x * kCellsPerBlock;
-  for (int64_t k = blockIdx.x * (int64_t)kCellsPerBlock + threadIdx.x / kGradLanes; k < n; k += stride) {
-    const int P = a.band[k];
-    grad_cell(a, P, j);
-    grad_cell(b, P, j);
   }
 }
 
@@ -188,20 +146,6 @@ vofpc_status launch_grad(vofpc_ctx ctx, vofpc_mesh M, const double *T, const dou
   vofpc_status st = grad_params(M, T, Tb, T_sat, alpha, band, counts, scope, variant, grad, status, p);
   if (st) return st;
   grad_kernel<<<grad_grid(ctx, M), 256, 0, ctx->stream>>>(p);
-  VOFPC_HIP(hipGetLastError());
-  return VOFPC_OK;
-}
-
-vofpc_status launch_grad2(vofpc_ctx ctx, vofpc_mesh M, const int32_t *band, const int32_t *counts, const double *T1,
-                          const double *Tb1, double T_sat1, const double *alpha1, int32_t variant1, double *grad1,
-                          const double *T2, const double *Tb2, double T_sat2, const double *alpha2, int32_t variant2,
-                          double *grad2) {
-  GradParams a, b;
-  vofpc_status st = grad_params(M, T1, Tb1, T_sat1, alpha1, band, counts, VOFPC_SCOPE_BAND, variant1, grad1, nullptr, a);
-  if (st) return st;
-  st = grad_params(M, T2, Tb2, T_sat2, alpha2, band, counts, VOFPC_SCOPE_BAND, variant2, grad2, nullptr, b);
-  if (st) return st;
-  grad2_kernel<<<grad_grid(ctx, M), 256, 0, ctx->stream>>>(a, b);
   VOFPC_HIP(hipGetLastError());
   return VOFPC_OK;
 }

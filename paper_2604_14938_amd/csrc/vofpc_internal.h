@@ -199,9 +199,9 @@ struct vofpc_mesh_s {
   // gradient-extrapolation scratch, allocated by its first call (outside capture)
   int8_t *ex_mark = nullptr;       // layer of each cell in the domain (-1 outside)
   int32_t *ex_list = nullptr;      // domain cells (any order)
-  int32_t *ex_info = nullptr;      // [1] domain size, [2] sweeps done, [3] unused, [4] converged
-  double *ex_part = nullptr;       // [2][grid] per-block largest change of the last two sweeps
-  double *ex_nrm = nullptr;        // [3][n_cells] advection direction
+  int32_t *ex_info = nullptr;      // [1] domain size
+  uint32_t *ex_flag = nullptr;     // [2][blocks] sweep barrier: each block's sweep number and verdict
+  int32_t *ex_entry = nullptr;     // mixed entry of the cells with an interface (marked in ex_mark)
   double *ex_buf = nullptr;        // [2][n_cells][8]: G_l and G_v per cell, two iterates
   double *ex_wup = nullptr;        // per cell-face slot: normalised upwind weight
   double *ex_theta = nullptr;      // per domain entry: pseudo-time fraction
@@ -256,11 +256,6 @@ vofpc_status mesh_vertex_stencil(vofpc_mesh M);
 const uint16_t *mlp_weights_bf16(vofpc_mlp M);
 const float *mlp_params_f32(vofpc_mlp M);
 int mlp_device(vofpc_mlp M);
-// two band-scope gradients over one list in a single launch
-vofpc_status launch_grad2(vofpc_ctx ctx, vofpc_mesh m, const int32_t *band, const int32_t *counts, const double *T1,
-                          const double *Tb1, double T_sat1, const double *alpha1, int32_t variant1, double *grad1,
-                          const double *T2, const double *Tb2, double T_sat2, const double *alpha2, int32_t variant2,
-                          double *grad2);
 vofpc_status launch_grad(vofpc_ctx ctx, vofpc_mesh m, const double *T, const double *Tb, double T_sat,
                          const double *alpha, const int32_t *band, const int32_t *counts, int32_t scope,
                          int32_t variant, double *grad, int32_t *status);
