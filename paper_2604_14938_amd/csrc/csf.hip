@@ -213,12 +213,13 @@ __global__ __launch_bounds__(kCsfBlock) void csf_step2_kernel(DevMesh m, const i
   CSF_CELL_LOOP {
     const int P = list[j_];
     const double n0 = n[P], n1 = n[N + P], n2 = n[2 * N + P];
-    const double x0 = m.xc[P], x1 = m.xc[N + P], x2 = m.xc[2 * N + P];
+    const double4 xP = m.xr[P];
     double num = 0.0, den = 0.0;
     for (int64_t i = m.cell_face_off[P] + lane; i < m.cell_face_off[P + 1]; i += kCsfLanes) {
       const int Q = m.cf_nbr[i];
       if (Q < 0) continue;
-      const double s0 = m.xc[Q] - x0, s1 = m.xc[N + Q] - x1, s2 = m.xc[2 * N + Q] - x2;
+      const double4 xQ = m.xr[Q];
+      const double s0 = xQ.x - xP.x, s1 = xQ.y - xP.y, s2 = xQ.z - xP.z;
       const double len = sqrt(s0 * s0 + s1 * s1 + s2 * s2);
       const double c = fabs((n0 * s0 + n1 * s1 + n2 * s2) / len);
       const double c2 = c * c, c4 = c2 * c2;

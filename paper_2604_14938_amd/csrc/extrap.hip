@@ -20,7 +20,7 @@
 // invalidation, only a barrier of flags: each block posts the sweep's number
 // and whether any of its cells still changes, and reads the others'.  With a
 // launch per sweep all of max_iter were issued whether they had work or not:
-// 500 us a call on 97,336 Voronoi cells (19 sweeps of 120, a domain of 16,000
+// 500 us a call on 194,672 Voronoi cells (19 sweeps of 120, a domain of 16,000
 // cells), now 173.  Five kernels of set-up, 68 us of that, stay: each needs the
 // whole of the one before.
 #include <hip/hip_runtime.h>
@@ -116,14 +116,15 @@ __device__ __forceinline__ void ex_stencil(const ExParams &p, int64_t j, int lan
   const int64_t N = m.n_cells, NF = m.n_faces;
   const int P = p.list[j];
   const int64_t i0 = m.cell_face_off[P], i1 = m.cell_face_off[P + 1];
-  const double x0 = m.xc[P], x1 = m.xc[N + P], x2 = m.xc[2 * N + P];
+  const double4 xP = m.xr[P];
   const double aP = p.alpha[P], TP = p.T[P];
   const int8_t mk = p.mark[P];
   LsqSums L, A;   // of T, of alpha
   for (int64_t i = i0 + lane; i < i1; i += kExLanes) {
     const int q = m.cf_nbr[i];
     if (q >= 0) {
-      double r0 = m.xc[q] - x0, r1 = m.xc[N + q] - x1, r2 = m.xc[2 * N + q] - x2;
+      const double4 xQ = m.xr[q];
+      double r0 = xQ.x - xP.x, r1 = xQ.y - xP.y, r2 = xQ.z - xP.z;
       const double aQ = p.alpha[q];
       double val = p.T[q];
       A.add(r0, r1, r2, aQ - aP, 0);
@@ -135,7 +136,7 @@ __device__ __forceinline__ void ex_stencil(const ExParams &p, int64_t j, int lan
       L.add(r0, r1, r2, val - TP, 0);
     } else if (q == -1) {
       const int f = m.cell_face[i];
-      L.add(m.xf[f] - x0, m.xf[NF + f] - x1, m.xf[2 * NF + f] - x2, p.Tb[f] - TP, 0);
+      L.add(m.xf[f] - xP.x, m.xf[NF + f] - xP.y, m.xf[2 * NF + f] - xP.z, p.Tb[f] - TP, 0);
     }
   }
   lsq_reduce<kExLanes>(L);

@@ -2,12 +2,17 @@
 // modification of Sec. 2.4.4) and the mass transfer rate (Eq. mass_transfer,
 // Eq. latent_source).
 //
-// Eight lanes per cell, faces dealt round the lanes.  The gradient gathers, for every
-// face of the cell, the neighbour centroid, alpha and T (or the boundary face
-// centroid and value), so the least-squares matrix is accumulated from data
-// the right-hand side needs anyway; cells without a crossing face may instead
-// use the stored inverse (VOFPC_SCOPE_ALL).
+// A group of lanes per cell, faces dealt round the lanes.  The gradient gathers,
+// for every face of the cell, the neighbour centroid (one 32-byte record), alpha
+// and T, or the boundary face centroid and value, and accumulates the
+// least-squares matrix beside the right-hand side; solving it in registers is
+// cheaper than reading a stored inverse (48 bytes a cell).  Every cell of
+// 1,953,125 hexahedra: 66 us, 3.2 TB/s of the 211 MB it must move (197 us with
+// eight lanes a cell, of which two idled, the centroids in three arrays, the
+// inverse read and each third cache line stored by one lane of eight).
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
 
 #include "lsq.h"
 #include "vofpc_internal.h"
@@ -28,81 +33,82 @@ struct GradParams {
   int32_t *status;
 };
 
-constexpr int kGradLanes = 8;   // lanes per cell (half a DPP row)
-
-// Gradient of cell P by a group of kGradLanes lanes: lane j takes faces j,
-// j + kGradLanes, ...; the least-squares sums are reduced over the group.
+// Gradient of cell P by a group of W lanes: lane j takes faces j, j + W, ...,
+// kAhead of them at a time, whose gathers are in flight together; the
+// least-squares sums are reduced over the group.
+template <int W>
 __device__ __forceinline__ void grad_cell(const GradParams &p, int P, int j) {
+  constexpr int kAhead = W >= 8 ? 2 : 4;   // (two rounds of eight: most polyhedra)
   const DevMesh &m = p.m;
   const int64_t N = m.n_cells, NF = m.n_faces;
-  const double xP0 = m.xc[P], xP1 = m.xc[N + P], xP2 = m.xc[2 * N + P];
+  const double4 xP = m.xr[P];
   const double aP = p.alpha[P], TP = p.T[P];
   const bool modify = p.variant != VOFPC_GRAD_STANDARD;
   const bool printed = p.variant == VOFPC_GRAD_PRINTED;
   LsqSums L;
-  int crossed = 0;
-  // an interior neighbour q: the centre connection, shortened to the
-  // alpha-interpolated crossing held at T_sat where the interface cuts it
-  auto interior = [&](int q) {
-    double r0 = m.xc[q] - xP0, r1 = m.xc[N + q] - xP1, r2 = m.xc[2 * N + q] - xP2;
-    const double aQ = p.alpha[q];
-    double val = p.T[q];
-    if (modify && (aP - 0.5) * (aQ - 0.5) < 0.0) {
-      const double t = printed ? fabs(aQ - 0.5) / fabs(aP - aQ) : (aP - 0.5) / (aP - aQ);
-      r0 *= t; r1 *= t; r2 *= t;
-      val = p.T_sat;
-      crossed = 1;
+  auto walk = [&](const int32_t *nbr, int64_t i0, int64_t i1, bool inner, bool bounds) {
+    for (int64_t i = i0 + j; i < i1; i += W * kAhead) {
+      int q[kAhead];
+      double4 x[kAhead];
+      double aQ[kAhead], tQ[kAhead];
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k) q[k] = i + k * W < i1 ? nbr[i + k * W] : -3;
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k) {
+        const int c = q[k] >= 0 ? q[k] : P;   // (the cell itself: read, not used)
+        x[k] = m.xr[c];
+        aQ[k] = p.alpha[c];
+        tQ[k] = p.T[c];
+      }
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k) {
+        if (q[k] >= 0) {
+          if (!inner) continue;
+          // the centre connection, shortened to the alpha-interpolated
+          // crossing held at T_sat where the interface cuts it
+          double r0 = x[k].x - xP.x, r1 = x[k].y - xP.y, r2 = x[k].z - xP.z, val = tQ[k];
+          if (modify && (aP - 0.5) * (aQ[k] - 0.5) < 0.0) {
+            const double t = printed ? fabs(aQ[k] - 0.5) / fabs(aP - aQ[k]) : (aP - 0.5) / (aP - aQ[k]);
+            r0 *= t; r1 *= t; r2 *= t;
+            val = p.T_sat;
+          }
+          L.add(r0, r1, r2, val - TP, p.weight);
+        } else if (q[k] == -1 && bounds) {
+          const int f = m.cell_face[i + k * W];
+          L.add(m.xf[f] - xP.x, m.xf[NF + f] - xP.y, m.xf[2 * NF + f] - xP.z, p.Tb[f] - TP, p.weight);
+        }
+      }
     }
-    L.add(r0, r1, r2, val - TP, p.weight);
   };
-  const int64_t i0 = m.cell_face_off[P], i1 = m.cell_face_off[P + 1];
-  if (p.xn_off) {
-    for (int64_t i = p.xn_off[P] + j; i < p.xn_off[P + 1]; i += kGradLanes) interior(p.xn_cell[i]);
-  }
-  for (int64_t i = i0 + j; i < i1; i += kGradLanes) {
-    const int q = m.cf_nbr[i];
-    if (q >= 0) {
-      if (!p.xn_off) interior(q);
-    } else if (q == -1 && p.Tb) {   // no boundary values given: interior neighbours only
-      const int f = m.cell_face[i];
-      L.add(m.xf[f] - xP0, m.xf[NF + f] - xP1, m.xf[2 * NF + f] - xP2, p.Tb[f] - TP, p.weight);
-    }
-  }
-  lsq_reduce<kGradLanes>(L);
-  crossed = gsum_i<kGradLanes>(crossed);
+  if (p.xn_off) walk(p.xn_cell, p.xn_off[P], p.xn_off[P + 1], true, false);
+  // (no boundary values given: interior neighbours only)
+  if (!p.xn_off || p.Tb) walk(m.cf_nbr, m.cell_face_off[P], m.cell_face_off[P + 1], !p.xn_off, p.Tb != nullptr);
+  lsq_reduce<W>(L);
   if (j != 0) return;
   double g0, g1, g2;
-  int st = VOFPC_CELL_OK;
-  // the stored inverse holds the face stencil with boundary values: usable
-  // for the plain variant when boundary values are given
-  if (p.scope == VOFPC_SCOPE_ALL && !crossed && p.weight == 0 && !p.xn_off && p.Tb) {
-    const double *gi = m.ginv;
-    const double ixx = gi[P], iyy = gi[N + P], izz = gi[2 * N + P];
-    const double ixy = gi[3 * N + P], ixz = gi[4 * N + P], iyz = gi[5 * N + P];
-    g0 = ixx * L.b0 + ixy * L.b1 + ixz * L.b2;
-    g1 = ixy * L.b0 + iyy * L.b1 + iyz * L.b2;
-    g2 = ixz * L.b0 + iyz * L.b1 + izz * L.b2;
-    if (ixx == 0 && iyy == 0 && izz == 0) st = VOFPC_CELL_G_SINGULAR;
-  } else if (!lsq_solve(L, g0, g1, g2)) {
-    st = VOFPC_CELL_G_SINGULAR;
-  }
+  const int st = lsq_solve(L, g0, g1, g2) ? VOFPC_CELL_OK : VOFPC_CELL_G_SINGULAR;
   p.grad[P] = g0;
   p.grad[N + P] = g1;
   p.grad[2 * N + P] = g2;
   if (p.status) p.status[P] = st;
 }
 
-// A block of 256 lanes serves 256 / kGradLanes cells at a time; every lane
-// of a group iterates the same cells, so the group's reductions see all its
-// lanes.
+// A block of 256 lanes serves 256 / W cells at a time; every lane of a group
+// iterates the same cells, so the group's reductions see all its lanes.  Blocks
+// go to the XCDs in turn (block b to XCD b % 8), so the blocks of one XCD take
+// one eighth of the cells in order: a neighbour's record is then mostly in
+// that XCD's own L2.
+template <int W>
 __global__ __launch_bounds__(256) void grad_kernel(GradParams p) {
   const int64_t n = (p.scope == VOFPC_SCOPE_ALL) ? p.m.n_cells : (int64_t)p.counts[1];
-  constexpr int kCellsPerBlock = 256 / kGradLanes;
-  const int j = threadIdx.x % kGradLanes;
-  const int64_t stride = (int64_t)gridDim.x * kCellsPerBlock;
-  for (int64_t k = blockIdx.x * (int64_t)kCellsPerBlock + threadIdx.x / kGradLanes; k < n; k += stride) {
-    const int P = (p.scope == VOFPC_SCOPE_ALL) ? (int)k : p.band[k];
-    grad_cell(p, P, j);
+  constexpr int kCells = 256 / W;
+  const int j = threadIdx.x % W;
+  const int64_t units = (n + kCells - 1) / kCells;
+  const int x = blockIdx.x % kXcd, per = (int)(gridDim.x / kXcd);   // gridDim.x is a multiple of kXcd
+  const int64_t last = units * (x + 1) / kXcd;
+  for (int64_t u = units * x / kXcd + blockIdx.x / kXcd; u < last; u += per) {
+    const int64_t k = u * kCells + threadIdx.x / W;
+    if (k < n) grad_cell<W>(p, (p.scope == VOFPC_SCOPE_ALL) ? (int)k : p.band[k], j);
   }
 }
 
@@ -132,11 +138,12 @@ static vofpc_status grad_params(vofpc_mesh M, const double *T, const double *Tb,
   return VOFPC_OK;
 }
 
-static unsigned grad_grid(vofpc_ctx ctx, vofpc_mesh M) {
-  int64_t grid = (M->d.n_cells + 15) / 16;
-  const int64_t cap = (int64_t)ctx->n_cu * 16;
+template <int W>
+static void grad_launch(vofpc_ctx ctx, const GradParams &p, int64_t cells) {
+  int64_t grid = ((cells + 256 / W - 1) / (256 / W) + kXcd - 1) / kXcd;   // blocks per XCD
+  const int64_t cap = (int64_t)ctx->n_cu * 8 / kXcd;
   if (grid > cap) grid = cap;
-  return (unsigned)(grid > 0 ? grid : 1);
+  grad_kernel<W><<<(unsigned)std::max<int64_t>(grid, 1) * kXcd, 256, 0, ctx->stream>>>(p);
 }
 
 vofpc_status launch_grad(vofpc_ctx ctx, vofpc_mesh M, const double *T, const double *Tb, double T_sat,
@@ -145,7 +152,24 @@ vofpc_status launch_grad(vofpc_ctx ctx, vofpc_mesh M, const double *T, const dou
   GradParams p;
   vofpc_status st = grad_params(M, T, Tb, T_sat, alpha, band, counts, scope, variant, grad, status, p);
   if (st) return st;
-  grad_kernel<<<grad_grid(ctx, M), 256, 0, ctx->stream>>>(p);
+  // Lanes per cell.  Every cell: one where the cells have about six faces and
+  // lie in order (their gathers coalesce), two for polyhedra; twice that for a
+  // mesh too small to fill the chip so.  The band: eight; its cells are few and
+  // scattered, a chain of gathers.  Microseconds with 1 / 2 / 4 / 8 lanes:
+  //   1,953,125 hexahedra, all cells   66 / 69 / 125 / 167
+  //   410,758 Voronoi cells, all       51 / 41 /  47 /  53
+  //   16,000 Voronoi cells, all        13 /  8 /   6 /   6
+  //   43,463 Voronoi cells of a band   15 / 11 / 9.4 / 10.2
+  //   the same, vertex stencil         21 / 16 / 13.3 / 13.6
+  const int64_t N = M->d.n_cells;
+  if (scope != VOFPC_SCOPE_ALL) {
+    grad_launch<8>(ctx, p, N);
+  } else {
+    const bool even = M->ncf <= 8 * N, small = N < 32768;
+    if (even && !small) grad_launch<1>(ctx, p, N);
+    else if (even || !small) grad_launch<2>(ctx, p, N);
+    else grad_launch<4>(ctx, p, N);
+  }
   VOFPC_HIP(hipGetLastError());
   return VOFPC_OK;
 }

@@ -73,7 +73,7 @@ __global__ void face_geom_kernel(DevMesh m, double *Sf, double *xf) {
 // mean of the face centroids) over the planar faces: V_f = (x_f - o).S_f / 3
 // with the pyramid centroid at o + 3/4 (x_f - o).
 __global__ void cell_geom_kernel(DevMesh m, const double *Sf, const double *xf, double *V, double *xc,
-                                 int32_t *bad) {
+                                 double4 *xr, int32_t *bad) {
   int64_t P = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (P >= m.n_cells) return;
   const int64_t NF = m.n_faces, N = m.n_cells;
@@ -97,38 +97,10 @@ __global__ void cell_geom_kernel(DevMesh m, const double *Sf, const double *xf, 
     m2 += vp * (o2 + 0.75 * d2);
   }
   V[P] = vol;
-  xc[P] = m0 / vol; xc[N + P] = m1 / vol; xc[2 * N + P] = m2 / vol;
+  const double4 r = make_double4(m0 / vol, m1 / vol, m2 / vol, 0.0);
+  xc[P] = r.x; xc[N + P] = r.y; xc[2 * N + P] = r.z;
+  xr[P] = r;
   if (!(vol > 0)) atomicExch(bad, 1);
-}
-
-// Stored inverse of the plain least-squares matrix G_P = sum r r^T over face
-// neighbours and value-boundary face centroids (App. B), six components.
-__global__ void ginv_kernel(DevMesh m, const double *xc, const double *xf, double *ginv) {
-  int64_t P = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (P >= m.n_cells) return;
-  const int64_t N = m.n_cells, NF = m.n_faces;
-  double px = xc[P], py = xc[N + P], pz = xc[2 * N + P];
-  double xx = 0, yy = 0, zz = 0, xy = 0, xz = 0, yz = 0;
-  for (int64_t i = m.cell_face_off[P]; i < m.cell_face_off[P + 1]; ++i) {
-    int q = m.cf_nbr[i];
-    double rx, ry, rz;
-    if (q >= 0) {
-      rx = xc[q] - px; ry = xc[N + q] - py; rz = xc[2 * N + q] - pz;
-    } else if (q == -1) {
-      int f = m.cell_face[i];
-      rx = xf[f] - px; ry = xf[NF + f] - py; rz = xf[2 * NF + f] - pz;
-    } else {
-      continue;
-    }
-    xx += rx * rx; yy += ry * ry; zz += rz * rz; xy += rx * ry; xz += rx * rz; yz += ry * rz;
-  }
-  double c00 = yy * zz - yz * yz, c01 = xz * yz - xy * zz, c02 = xy * yz - xz * yy;
-  double c11 = xx * zz - xz * xz, c12 = xy * xz - xx * yz, c22 = xx * yy - xy * xy;
-  double det = xx * c00 + xy * c01 + xz * c02;
-  double tr = (xx + yy + zz) * (1.0 / 3.0);
-  double id = (det > 1e-12 * tr * tr * tr) ? 1.0 / det : 0.0;
-  ginv[P] = c00 * id; ginv[N + P] = c11 * id; ginv[2 * N + P] = c22 * id;
-  ginv[3 * N + P] = c01 * id; ginv[4 * N + P] = c02 * id; ginv[5 * N + P] = c12 * id;
 }
 
 // Normalised inverse-distance weights 1/|x_v - x_c| of the cells sharing a
@@ -473,7 +445,7 @@ vofpc_status mesh_upload(vofpc_ctx ctx, const vofpc_mesh_desc *d, vofpc_mesh *ou
   COPY(xc, (const double *)nullptr, 3 * N, double);
   COPY(Sf, (const double *)nullptr, 3 * NF, double);
   COPY(xf, (const double *)nullptr, 3 * NF, double);
-  COPY(ginv, (const double *)nullptr, 6 * N, double);
+  COPY(xr, (const double4 *)nullptr, N, double4);
   COPY(cf_S, (const double *)nullptr, 3 * ncf, double);
   M->n_blk = (N + kCompactBlockCells - 1) / kCompactBlockCells;
   {
@@ -516,8 +488,8 @@ vofpc_status mesh_upload(vofpc_ctx ctx, const vofpc_mesh_desc *d, vofpc_mesh *ou
   const int B = 256;
   VOFPC_HIP(hipMemsetAsync(bad, 0, sizeof(int32_t), s));
   face_geom_kernel<<<(unsigned)((NF + B - 1) / B), B, 0, s>>>(m, (double *)m.Sf, (double *)m.xf);
-  cell_geom_kernel<<<(unsigned)((N + B - 1) / B), B, 0, s>>>(m, m.Sf, m.xf, (double *)m.V, (double *)m.xc, bad);
-  ginv_kernel<<<(unsigned)((N + B - 1) / B), B, 0, s>>>(m, m.xc, m.xf, (double *)m.ginv);
+  cell_geom_kernel<<<(unsigned)((N + B - 1) / B), B, 0, s>>>(m, m.Sf, m.xf, (double *)m.V, (double *)m.xc, (double4 *)m.xr,
+                                                            bad);
   slot_area_kernel<<<(unsigned)((N + B - 1) / B), B, 0, s>>>(m, (double *)m.cf_S);
   vertex_weight_kernel<<<(unsigned)((NV + B - 1) / B), B, 0, s>>>(m, m.xc, (double *)m.vc_w, (double *)m.vc_wmean);
   // smallest distance between the centres of two face neighbours (the
@@ -628,7 +600,7 @@ vofpc_status mesh_concat(vofpc_ctx ctx, const vofpc_mesh *ms, int32_t n, vofpc_m
   ALLOC(xc, 3 * N, double);
   ALLOC(Sf, 3 * NF, double);
   ALLOC(xf, 3 * NF, double);
-  ALLOC(ginv, 6 * N, double);
+  ALLOC(xr, N, double4);
   ALLOC(cf_S, 3 * ncf, double);
 #undef ALLOC
   M->n_blk = (N + kCompactBlockCells - 1) / kCompactBlockCells;
@@ -704,6 +676,7 @@ vofpc_status mesh_concat(vofpc_ctx ctx, const vofpc_mesh *ms, int32_t n, vofpc_m
     CC((double *)m.vc_w + bvc, a.vc_w, A.nvc, 0, 0);
     CC((double *)m.vc_wmean + bvc, a.vc_wmean, A.nvc, 0, 0);
     CC((double *)m.V + bN, a.V, n_, 0, 0);
+    CC((double *)m.xr + 4 * bN, (const double *)a.xr, 4 * n_, 0, 0);
     CC((double *)m.cf_S + 3 * bcf, a.cf_S, 3 * A.ncf, 0, 0);
     // structure-of-arrays fields, one component at a time
     for (int c = 0; c < 3; ++c) {
@@ -712,7 +685,6 @@ vofpc_status mesh_concat(vofpc_ctx ctx, const vofpc_mesh *ms, int32_t n, vofpc_m
       CC((double *)m.Sf + c * NF + bF, a.Sf + c * nf_, nf_, 0, 0);
       CC((double *)m.xf + c * NF + bF, a.xf + c * nf_, nf_, 0, 0);
     }
-    for (int c = 0; c < 6; ++c) CC((double *)m.ginv + c * N + bN, a.ginv + c * n_, n_, 0, 0);
     bN += n_; bF += nf_; bV += nv_;
     bcf += A.ncf; bfv += A.nfv; bcv += A.ncv; bcl += A.ncl; bvc += A.nvc;
   }

@@ -84,7 +84,8 @@ __device__ __forceinline__ bool face_coupling(const RobinParams &p, int C, doubl
   const int own = m.face_owner[f];
   const double aN = p.alpha[Qn];
   const double S0 = m.Sf[f], S1 = m.Sf[NF + f], S2 = m.Sf[2 * NF + f];
-  const double xN0 = m.xc[Qn], xN1 = m.xc[N + Qn], xN2 = m.xc[2 * N + Qn];
+  const double4 rN = m.xr[Qn];
+  const double xN0 = rN.x, xN1 = rN.y, xN2 = rN.z;
   double sN[3];
   area_vector(p, Qn, sN);
   const bool cross = (aC - 0.5) * (aN - 0.5) < 0.0;
@@ -139,7 +140,8 @@ __global__ __launch_bounds__(kRbBlock) void robin_kernel(RobinParams p) {
     if (k < nb) {
       C = p.band[k];
       aC = p.alpha[C];
-      xC[0] = m.xc[C]; xC[1] = m.xc[N + C]; xC[2] = m.xc[2 * N + C];
+      const double4 rC = m.xr[C];
+      xC[0] = rC.x; xC[1] = rC.y; xC[2] = rC.z;
       area_vector(p, C, sC);
       double sum = 0.0;
       for (int64_t i = m.cell_face_off[C] + lane; i < m.cell_face_off[C + 1]; i += kRbLanes) {

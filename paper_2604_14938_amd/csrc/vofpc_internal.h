@@ -74,7 +74,7 @@ struct DevMesh {
   const double *xc;    // [3][n_cells]
   const double *Sf;    // [3][n_faces]
   const double *xf;    // [3][n_faces]
-  const double *ginv;  // [6][n_cells] xx yy zz xy xz yz of the inverse
+  const double4 *xr;   // [n_cells]: the centre of each cell as one 32-byte record, for gathers
 };
 
 // cells per block of the compaction kernels (sizes a mesh's block arrays)

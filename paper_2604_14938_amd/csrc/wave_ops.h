@@ -59,9 +59,9 @@ __device__ __forceinline__ void pair_d(double v, double &lo, double &hi) {
 
 template <int W>
 __device__ __forceinline__ double gsum(double v) {
-  static_assert(W == 4 || W == 8 || W == 16 || W == 32 || W == 64, "group width");
-  v += dpp_d<kQuadXor1>(v);
-  v += dpp_d<kQuadXor2>(v);
+  static_assert(W == 1 || W == 2 || W == 4 || W == 8 || W == 16 || W == 32 || W == 64, "group width");
+  if constexpr (W >= 2) v += dpp_d<kQuadXor1>(v);
+  if constexpr (W >= 4) v += dpp_d<kQuadXor2>(v);
   if constexpr (W >= 8) v += dpp_d<kHalfMirror>(v);
   if constexpr (W >= 16) v += dpp_d<kRowMirror>(v);
   if constexpr (W >= 32) { double lo, hi; pair_d<16>(v, lo, hi); v = lo + hi; }
@@ -70,9 +70,9 @@ __device__ __forceinline__ double gsum(double v) {
 }
 template <int W>
 __device__ __forceinline__ int gsum_i(int v) {
-  static_assert(W == 4 || W == 8 || W == 16 || W == 32 || W == 64, "group width");
-  v += dpp_i<kQuadXor1>(v);
-  v += dpp_i<kQuadXor2>(v);
+  static_assert(W == 1 || W == 2 || W == 4 || W == 8 || W == 16 || W == 32 || W == 64, "group width");
+  if constexpr (W >= 2) v += dpp_i<kQuadXor1>(v);
+  if constexpr (W >= 4) v += dpp_i<kQuadXor2>(v);
   if constexpr (W >= 8) v += dpp_i<kHalfMirror>(v);
   if constexpr (W >= 16) v += dpp_i<kRowMirror>(v);
   if constexpr (W >= 32) { int lo, hi; pair_i<16>(v, lo, hi); v = lo + hi; }
