@@ -58,7 +58,7 @@ __global__ __launch_bounds__(kRingBlock) void ex_list_kernel(int64_t n, int8_t *
                                                              const int32_t *counts, vofpc_interface itf,
                                                              int32_t *entry) {
   if ((int)blockIdx.x < list_blocks) {
-    ring_list_block(n, mark, list, len, blockIdx.x);
+    ring_list_block(n, [&](int64_t P) { return mark[P] >= 0; }, list, len, blockIdx.x);
     return;
   }
   int64_t cnt = counts[0];

@@ -60,12 +60,13 @@ static inline unsigned ring_face_blocks(int64_t n_faces) {
   return (unsigned)std::max<int64_t>(1, (n_faces + per - 1) / per);
 }
 
-// list of the marked cells (in the order of the claims: users must not
+// list of the cells that in_list takes (in the order of the claims: users must not
 // depend on it); a tile of 16 cells a thread and one claim on the length in
 // *len per block of 4,096 cells (a claim per 256 cells: 6.2 us on 195k cells,
 // bound by the claims on one counter)
 constexpr int kRingTile = 16;
-static __device__ __forceinline__ void ring_list_block(int64_t n, const int8_t *mark, int32_t *list, int32_t *len,
+template <class In>
+static __device__ __forceinline__ void ring_list_block(int64_t n, In in_list, int32_t *list, int32_t *len,
                                                        int64_t block) {
   __shared__ int wave_tot[kRingBlock / 64];
   __shared__ int base;
@@ -75,7 +76,7 @@ static __device__ __forceinline__ void ring_list_block(int64_t n, const int8_t *
 #pragma unroll
   for (int t = 0; t < kRingTile; ++t) {
     const int64_t P = c0 + t * kRingBlock + threadIdx.x;
-    if (P < n && mark[P] >= 0) in |= 1u << t;
+    if (P < n && in_list(P)) in |= 1u << t;
   }
   int tot = 0;
 #pragma unroll
@@ -104,11 +105,6 @@ static __device__ __forceinline__ void ring_list_block(int64_t n, const int8_t *
 static inline unsigned ring_list_blocks(int64_t n) {
   const int64_t per = (int64_t)kRingBlock * kRingTile;
   return (unsigned)std::max<int64_t>(1, (n + per - 1) / per);
-}
-
-static __global__ __launch_bounds__(kRingBlock) void ring_list_kernel(int64_t n, const int8_t *mark, int32_t *list,
-                                                                      int32_t *len) {
-  ring_list_block(n, mark, list, len, blockIdx.x);
 }
 
 }  // namespace vofpc
