@@ -384,7 +384,7 @@ vofpc_status vofpc_extrap_opts_default(vofpc_extrap_opts *opts);
  * itf: the compaction and reconstruction of this alpha; opts may be NULL.
  * gradT_l, gradT_v: DEVICE [3][n_cells], written on D only.  report:
  * optional DEVICE int32[2] = (sweeps done, 0).  All sweeps run in one
- * cooperative kernel of at most one block per compute unit, which ends after
+ * persistent kernel of at most one block per compute unit, which ends after
  * the last one needed; a wait for another block that takes 2 seconds ends it
  * with NaN outputs and a 1 in report[1].  The first
  * call on a mesh allocates its scratch (mesh-owned) and must not be captured;

@@ -12,8 +12,8 @@
 //   face neighbours; stop at the first sweep whose largest change is below
 //   tol, or after max_iter sweeps.
 //
-// The domain is grown, listed and given its stencil by kernels of their own; one
-// cooperative kernel then runs every sweep and writes the outputs.  A block
+// The domain is grown, listed and given its stencil by kernels of their own;
+// one persistent kernel then runs every sweep and writes the outputs.  A block
 // keeps its first cells' stencils and values in registers; the iterates go
 // through memory at agent scope (relaxed atomic loads and stores, which meet
 // beyond the per-XCD L2 caches), so a sweep needs no cache write-back or
@@ -21,8 +21,8 @@
 // and whether any of its cells still changes, and reads the others'.  With a
 // launch per sweep all of max_iter were issued whether they had work or not:
 // 500 us a call on 194,672 Voronoi cells (19 sweeps of 120, a domain of 16,000
-// cells), now 173.  Five kernels of set-up, 68 us of that, stay: each needs the
-// whole of the one before.
+// cells), now 149.  Five kernels of set-up, 41 us of that, stay: each needs
+// the whole of the one before.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -36,6 +36,7 @@ namespace vofpc {
 
 constexpr int kExBlock = 256;
 constexpr int kExMaxBlocks = 1024;      // blocks of the sweep kernel at most
+constexpr int kExFlags = 2 * kExMaxBlocks + 2;   // two rows of barrier flags; blocks that came, blocks that take part
 constexpr int8_t kExInterface = 127;    // mark of a domain cell with an interface (layers end at 100)
 
 __device__ __forceinline__ bool is_mixed(double a, double eps) { return a > eps && a < 1.0 - eps; }
@@ -46,7 +47,7 @@ __global__ __launch_bounds__(kExBlock) void ex_init_kernel(int64_t n, const doub
                                                            int32_t *info, uint32_t *flag) {
   const int64_t P = blockIdx.x * (int64_t)kExBlock + threadIdx.x;
   if (P < n) mark[P] = is_mixed(alpha[P], eps) ? 0 : -1;
-  for (int64_t i = P; i < 2 * kExMaxBlocks; i += (int64_t)gridDim.x * kExBlock) flag[i] = 0;
+  for (int64_t i = P; i < kExFlags; i += (int64_t)gridDim.x * kExBlock) flag[i] = 0;
   if (P == 0) info[1] = 0;
 }
 
@@ -224,23 +225,59 @@ __device__ __forceinline__ void agent_store(double *a, double v) {
   __hip_atomic_store(a, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Barrier over the first nb blocks of a cooperative launch, epoch 1, 2, ...:
-// every agent-scope store made before it is seen by every agent-scope load
+// The blocks that take part in the sweeps: those that run by the time the first
+// of them closes the list, which is when all nb have come, or kExGatherTicks
+// after its own start; a block that comes later ends at once.  Every block that
+// another one waits for is therefore running, whatever else the chip is doing
+// and however few of them found room: an ordinary launch cannot be left
+// waiting for blocks that are not resident.  (A cooperative launch promises
+// residency for 20 to 30 us more, and 200 us when several processes share the
+// device.)  Returns this block's number (-1: it comes too late) and their count
+// in nb.
+constexpr uint64_t kExGatherTicks = 5000;   // 50 us of the 100 MHz wall clock
+__device__ __forceinline__ int gather_blocks(uint32_t *flag, int &nb) {
+  __shared__ int id, count;
+  if (threadIdx.x == 0) {
+    uint32_t *came = flag + 2 * kExMaxBlocks, *part = came + 1;
+    constexpr uint32_t kClosed = 0x80000000u;
+    const uint32_t k = __hip_atomic_fetch_add(came, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    int n = 0;
+    if (k == 0) {
+      const uint64_t t0 = wall_clock64();
+      while (__hip_atomic_load(came, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (uint32_t)nb &&
+             wall_clock64() - t0 < kExGatherTicks) {
+      }
+      n = (int)__hip_atomic_fetch_or(came, kClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(part, (uint32_t)n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else if (!(k & kClosed)) {   // the first block closes the list: a wait of kExGatherTicks at most
+      while ((n = (int)__hip_atomic_load(part, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0) {
+      }
+    }
+    id = n ? (int)k : -1;
+    count = n;
+  }
+  __syncthreads();
+  nb = count;
+  return id;
+}
+
+// Barrier over the nb blocks that take part (this one number id), epoch 1, 2,
+// ...: every agent-scope store made before it is seen by every agent-scope load
 // after it.  Returns in `any` whether some block brought `mine`.  The flags
 // alternate between two rows, so a block that runs ahead cannot overwrite a
 // flag that is still to be read.  The first wavefront polls for its block
 // (1.6 us a barrier of 16 blocks, 2.4 of 64, 3.2 of 256; with every wavefront
-// in the poll 4.3 and 6.2).  All blocks are resident, so the wait ends; should
-// one never come, it ends after kExWaitTicks (2 s) with false.
+// in the poll 4.3 and 6.2).  All blocks run, so the wait ends; should one never
+// come, it ends after kExWaitTicks (2 s) with false.
 constexpr uint64_t kExWaitTicks = 200000000ull;   // of the 100 MHz wall clock
-__device__ __forceinline__ bool sweep_barrier(uint32_t *flag, int nb, uint32_t epoch, bool mine, bool &any) {
+__device__ __forceinline__ bool sweep_barrier(uint32_t *flag, int id, int nb, uint32_t epoch, bool mine, bool &any) {
   __shared__ int seen;   // bit 0: some block brought mine, bit 1: a wait ended without its flag
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wavefront's stores have reached the agent's memory
   const int b = __syncthreads_or(mine ? 1 : 0);
   if (threadIdx.x < 64) {
     uint32_t *f = flag + (epoch & 1) * kExMaxBlocks;
     if (threadIdx.x == 0)
-      __hip_atomic_store(f + blockIdx.x, (epoch << 1) | (b ? 1u : 0u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(f + id, (epoch << 1) | (b ? 1u : 0u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     bool a = false, ok = true;
     for (int i = threadIdx.x; i < nb && ok; i += 64) {
       uint32_t v = __hip_atomic_load(f + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -277,11 +314,16 @@ __device__ __forceinline__ bool sweep_barrier(uint32_t *flag, int nb, uint32_t e
 constexpr int kItBlock = 1024, kItLanes = 4, kItCells = kItBlock / kItLanes, kItSlots = 10;
 __global__ __launch_bounds__(kItBlock) void ex_iterate_kernel(ExParams p) {
   const int64_t N = p.m.n_cells, nd = p.info[1];
-  const int nb = (int)std::min<int64_t>(gridDim.x, std::max<int64_t>(1, (nd + kItCells - 1) / kItCells));
-  if ((int)blockIdx.x >= nb) return;
+  int nb = (int)std::min<int64_t>(gridDim.x, std::max<int64_t>(1, (nd + kItCells - 1) / kItCells));
+  int id = (int)blockIdx.x;
+  if (id >= nb) return;
+  if (p.max_iter > 1) {   // (a single sweep has no barrier)
+    id = gather_blocks(p.flag, nb);
+    if (id < 0) return;
+  }
   const int d = threadIdx.x % kItLanes;
   const bool comp = d < 3;
-  const int64_t j0 = (int64_t)blockIdx.x * kItCells + threadIdx.x / kItLanes, stride = (int64_t)nb * kItCells;
+  const int64_t j0 = (int64_t)id * kItCells + threadIdx.x / kItLanes, stride = (int64_t)nb * kItCells;
   // the group's first cell: word `at` of its record (its advanced component
   // d) with its value, and the neighbours and weights of its first slots
   int P = 0, at = 0, cnt = 0, first = 0, nbr[kItSlots];
@@ -336,7 +378,7 @@ __global__ __launch_bounds__(kItBlock) void ex_iterate_kernel(ExParams p) {
     ++sweeps;
     if (sweeps == p.max_iter) break;   // (each group reads back its own cells alone)
     bool more;
-    ok = sweep_barrier(p.flag, nb, (uint32_t)sweeps, !(change < p.tol), more);
+    ok = sweep_barrier(p.flag, id, nb, (uint32_t)sweeps, !(change < p.tol), more);
     if (!ok || !more) break;
   }
   // outputs: the advanced field from the newest iterate, the kept one from the
@@ -357,7 +399,7 @@ __global__ __launch_bounds__(kItBlock) void ex_iterate_kernel(ExParams p) {
     const int C = p.list[j], c = (p.alpha[C] >= 0.5 ? 3 : 0) + d;
     put(C, c, agent_load(fin + (int64_t)C * kExRec + c));
   }
-  if (p.report && blockIdx.x == 0 && threadIdx.x == 0) {
+  if (p.report && id == 0 && threadIdx.x == 0) {
     p.report[0] = sweeps;
     p.report[1] = ok ? 0 : 1;
   }
@@ -405,7 +447,7 @@ extern "C" vofpc_status vofpc_extrapolate(vofpc_ctx ctx, vofpc_mesh M, const dou
          *h = nullptr, *i = nullptr, *j = nullptr;
     vofpc_status st;
     if ((st = mesh_scratch_alloc(M, (size_t)N, &a)) || (st = mesh_scratch_alloc(M, 4 * (size_t)N, &b)) ||
-        (st = mesh_scratch_alloc(M, 32, &c)) || (st = mesh_scratch_alloc(M, 2 * kExMaxBlocks * sizeof(uint32_t), &d)) ||
+        (st = mesh_scratch_alloc(M, 32, &c)) || (st = mesh_scratch_alloc(M, kExFlags * sizeof(uint32_t), &d)) ||
         (st = mesh_scratch_alloc(M, 4 * (size_t)N, &e)) || (st = mesh_scratch_alloc(M, 16 * sizeof(double) * (size_t)N, &f)) ||
         (st = mesh_scratch_alloc(M, 8 * (size_t)M->ncf, &g)) || (st = mesh_scratch_alloc(M, 8 * (size_t)N, &h)) ||
         (st = mesh_scratch_alloc(M, 4 * (size_t)M->ncf, &i)) || (st = mesh_scratch_alloc(M, 8 * (size_t)N, &j)))
@@ -457,13 +499,7 @@ extern "C" vofpc_status vofpc_extrapolate(vofpc_ctx ctx, vofpc_mesh M, const dou
   ex_stencil_kernel<<<gW, kExBlock, 0, s>>>(p);
   const unsigned gI = (unsigned)std::max<int64_t>(
       1, std::min<int64_t>((N + kItCells - 1) / kItCells, std::min<int64_t>(ctx->n_cu, kExMaxBlocks)));
-  if (o.max_iter <= 1) {   // no barrier: an ordinary launch, 12 us cheaper
-    ex_iterate_kernel<<<gI, kItBlock, 0, s>>>(p);
-  } else {
-    void *args[] = {&p};
-    VOFPC_HIP(hipLaunchCooperativeKernel(reinterpret_cast<const void *>(ex_iterate_kernel), dim3(gI), dim3(kItBlock),
-                                         args, 0, s));
-  }
+  ex_iterate_kernel<<<gI, kItBlock, 0, s>>>(p);
   VOFPC_HIP(hipGetLastError());
   return VOFPC_OK;
 }
