@@ -52,17 +52,22 @@
 // instead of 165 us (one cell per wavefront, recon.hip), 5,000 of 422k
 // hexahedra in 62 instead of 143 us.
 //
-// Search: Brent's method (Brent 1973, ch. 4) on r(s) = V(s)/V_P - alpha
-// over a bracket of [phi_min, phi_max] whose ends straddle the root: inverse
-// quadratic interpolation or the secant, the midpoint when the estimate
-// leaves the quarter of the bracket next to its better end or does not
-// shrink fast enough; one evaluation per step, the stopping rule of the
-// wavefront kernel.  A narrowed bracket [h_lo, h_hi] is first checked with
-// two evaluations: at its centre (the network's predicted isovalue), whose
-// residual gives the side of the root, and at its end on that side.  The
-// half on the root's side starts the method when that end is past the root;
-// otherwise the part of the full bracket beyond that end does (status
-// LEARNED_FALLBACK: the root is outside the bracket).
+// Search: the root of r(s) = V(s)/V_P - alpha in a bracket of [phi_min,
+// phi_max] whose ends straddle it.  The first cut is the quantile of alpha in a
+// model of the cell's volume over phi (quantile()), the second moves by the
+// difference of the quantiles of the volume found and of alpha; then the secant
+// and the inverse quadratic interpolation through the last three cuts, wherever
+// the bracket's other end is; the midpoint when the estimate leaves the bracket
+// or does not shrink fast enough (the rule of Brent 1973, ch. 4).  One evaluation
+// per step, the stopping rule of the wavefront kernel.  The mean number of cuts
+// is 5.2 for hexahedra and 6.1 for Voronoi cells (Brent's method from the ends of
+// the bracket: 8.8), the largest of 31,886 hexahedra 14 (41): a wavefront
+// waits for its slowest cell.  31,886 hexahedra, label pass: 114 us (174 us);
+// 24,431 Voronoi cells: 230 us (280 us).
+// A narrowed bracket [h_lo, h_hi] starts with a cut at its centre (the network's
+// predicted isovalue).  An isovalue found beyond its end on the root's side has
+// the status LEARNED_FALLBACK; the end itself needs no cut (113,584 cells with
+// the network: 5.2 cuts a cell for 6.1).
 //
 // Scheduling: a wavefront takes up to 64/G consecutive mixed entries (a
 // batch), stages them together, runs their searches side by side until the
@@ -153,6 +158,16 @@ __device__ __forceinline__ double iqi1(double x0, double f0, double x1, double f
   return x0 + qdiv((x2 - x0) * f0 * f1 * d01 - (x1 - x0) * f0 * f2 * d02, d01 * d02 * d12);
 }
 
+// Where a fraction x of a cell's volume lies above, in widths of [phi_min,
+// phi_max] from the mean vertex value: a quantile function with the contact of
+// a corner (x ~ distance^(1/0.3)) at both ends.  Fitted to the reconstructed
+// isovalues of hexahedra and Voronoi cells cut by bubbles: a mean error of
+// 0.03 and 0.06 widths, against 0.15 and 0.23 of the line through the ends.
+__device__ __forceinline__ float quantile_power(float x) { return __builtin_amdgcn_exp2f(0.3f * __builtin_amdgcn_logf(x)); }
+__device__ __forceinline__ float quantile(double x) {
+  const float hi = quantile_power((float)fmin(fmax(x, 0.0), 1.0)), lo = quantile_power((float)fmin(fmax(1.0 - x, 0.0), 1.0));
+  return 0.6f * (lo - hi);
+}
 
 // Sum over the group of one value per slot (item q + G t in slot t), added
 // in the order of the wavefront kernel's reductions (its lane i holds item
@@ -825,23 +840,37 @@ __device__ __forceinline__ void solve_cells(const ReconParams &p, typename Caps:
       for (int i = 0; i < n; ++i) fm += M.phi[M.lv[o + i][sl]][sl];
       return fm / (double)n;
     };
-    // One evaluation site; the phase decides where the next one is:
-    // the fixed isovalue, the centre of a narrowed bracket and then its
-    // end on the root's side, the search estimate, or the bracket end
-    // kept when the search cannot stop.
-    enum { kFixed, kHintMid, kHintUp, kHintDown, kStart, kSearch, kFinal };
+    // One evaluation site; the phase decides where the next one is: the
+    // fixed isovalue, the centre of a narrowed bracket (a team: and its
+    // ends), the search estimate, or the bracket end kept when the search
+    // cannot stop.
+    enum { kFixed, kHintMid, kStart, kSearch, kFinal };
     const double iVP = 1.0 / VP;
     const double tol = p.tol_rel * (a < 1.0 - a ? a : 1.0 - a);
-    // Brent's method (Brent 1973, ch. 4) on the residual r(s) = V(s)/V_P - alpha:
-    // xb is the bracket end of smaller |r|, xa the other end (before the
-    // start the lower and the upper end), xc the previous xb, xd the one
-    // before; the estimate is inverse quadratic interpolation through (xa,
-    // xb, xc) when the three residuals differ, else the secant through xa
-    // and xb, replaced by the midpoint when it falls outside the quarter of
-    // the bracket next to xb or does not shrink fast enough against the
-    // previous steps.
-    double xa = pmin, fa = 1.0 - a, xb = pmax, fb = -a, xc = 0, fcv = 0, xd = 0;
-    bool bis = true;
+    // The search on the residual r(s) = V(s)/V_P - alpha: [xa, xb] is the
+    // bracket (r > 0 at xa); one cell per group remembers its last three cuts
+    // (the newest is a bracket end, (xc, fcv) and (xd, fd) the two before it)
+    // and takes the inverse quadratic interpolation through them, with two
+    // cuts the secant, with one the distance between the quantiles of its
+    // volume and of alpha, with none the quantile of alpha; the midpoint of
+    // the bracket when that falls outside it or does not shrink fast enough
+    // against the steps before (the rule of Brent 1973, ch. 4).  In a team,
+    // (xc, fcv) is the cut of smallest residual off the bracket.
+    double xa = pmin, fa = 1.0 - a, xb = pmax, fb = -a, xc = 0, fcv = 0, xd = 0, fd = 0;
+    int cuts = 0, hside = 0;
+    bool bis = false;
+    const float qa = quantile(a);
+    double guess;
+    {
+      double ps = 0.0;
+#pragma unroll
+      for (int t = 0; t < KV; ++t)
+        if (q + t * G < nv) ps += pw[t];
+      const double W = pmax - pmin;
+      guess = tsum<G>(ps) / (double)nv + W * (double)qa;
+      guess = fmin(guess, pmax - 0.3 * W * (double)quantile_power((float)a));
+      guess = fmax(guess, pmin + 0.3 * W * (double)quantile_power((float)(1.0 - a)));
+    }
     // a jump of V: where a face with four or more crossings switches its
     // pairing (at its vertex-value mean) or a loop pinches at a vertex
     // (at that vertex's value), V may step over alpha V_P and the search
@@ -858,17 +887,6 @@ __device__ __forceinline__ void solve_cells(const ReconParams &p, typename Caps:
     double se;
     while (true) {
       if (ph >= kStart) {
-        if (ph == kStart && ts == 1) {
-          // the bracket [xa, xb] (full, or what the narrowed bracket's
-          // check left) starts the method
-          if (fabs(fa) < fabs(fb)) {
-            const double tx = xa, tf = fa;
-            xa = xb; fa = fb; xb = tx; fb = tf;
-          }
-          xc = xa; fcv = fa; xd = xa;
-          bis = true;
-          ph = kSearch;
-        }
         const double big = fabs(xa) > fabs(xb) ? fabs(xa) : fabs(xb);
         const bool collapsed = fabs(xb - xa) <= 2.0 * ulp_of(big);
         if (collapsed || it >= p.max_iter) {
@@ -879,11 +897,16 @@ __device__ __forceinline__ void solve_cells(const ReconParams &p, typename Caps:
           else if (fabs(b ? fb : fa) > 1e-10) st = VOFPC_CELL_NO_ROOT;
           ph = kFinal;
         } else {
-          const double blo = fmin(xa, xb), bhi = fmax(xa, xb), w = bhi - blo;
-          const bool three = fa != fcv && fb != fcv;
-          const double sec = xb - fb * qdiv(xb - xa, fb - fa), mid = xa + (xb - xa) * 0.5;
-          const double qi = iqi1(xa, fa, xb, fb, xc, fcv);
+          const double blo = xa, bhi = xb, w = xb - xa, mid = xa + w * 0.5;
+          // the points of the estimate: a group's last cuts; a team's bracket
+          // ends and its third point
+          const double x1 = ts == 1 && above ? xa : xb, f1 = ts == 1 && above ? fa : fb;
+          const double x2 = ts == 1 ? xc : xa, f2 = ts == 1 ? fcv : fa, x3 = ts == 1 ? xd : xc, f3 = ts == 1 ? fd : fcv;
+          const bool three = f1 != f3 && f2 != f3 && (ts > 1 || cuts > 2);
+          const double sec = x1 - f1 * qdiv(x1 - x2, f1 - f2);
+          const double qi = iqi1(x2, f2, x1, f1, x3, f3);
           bool look = false;
+          ph = ts == 1 ? kSearch : ph;
           if (ts == 1) {
             if (jnext) {
               // the double next to the tried value, on the root's side
@@ -892,14 +915,21 @@ __device__ __forceinline__ void solve_cells(const ReconParams &p, typename Caps:
             }
             if (!(jpin && se > blo && se < bhi)) {
               se = three ? qi : sec;
-              const double q0 = (3.0 * xa + xb) * 0.25;
-              const bool inside = q0 < xb ? (se > q0 && se < xb) : (se > xb && se < q0);
-              const double du = 4.0 * ulp_of(xb);
-              const double lastd = bis ? fabs(xb - xc) : fabs(xc - xd);
-              bis = !inside || fabs(se - xb) >= 0.5 * lastd || lastd < du;
-              if (bis) se = mid;
-              nbis = bis ? nbis + 1 : 0;
-              look = nbis >= 2 && it > 0;
+              if (cuts < 2)
+                se = cuts == 0 ? guess : x1 + (pmax - pmin) * (double)(qa - quantile(f1 + a));
+              const double lastd = bis ? fabs(x1 - x2) : fabs(x2 - x3);
+              bis = !(se > blo && se < bhi) || nbis >= 3 ||
+                    (cuts > 2 && (fabs(se - x1) >= 0.5 * lastd || lastd < 4.0 * ulp_of(x1)));
+              if (bis) {
+                // at a residual of rounding noise (the tolerance of a small
+                // alpha is below it): close in on the root from its near side,
+                // in growing steps, before halving the bracket
+                const bool near_a = fabs(fa) <= fabs(fb);
+                const double d = ldexp(ulp_of(x1), 3 + 2 * (nbis < 16 ? nbis : 16));
+                const bool noise = fmin(fabs(fa), fabs(fb)) < 0x1p-46 && d < 0.5 * w;
+                se = noise ? (near_a ? xa + d : xb - d) : mid;
+              }
+              look = nbis >= 2;
             }
             jpin = false;
           } else {
@@ -909,19 +939,19 @@ __device__ __forceinline__ void solve_cells(const ReconParams &p, typename Caps:
             // 4096th with sixteen); and points that divide the bracket evenly,
             // in place of those that fall outside it, and of all but the
             // estimate after a step that hardly lowered the residual
-            double e0 = ph != kStart && three ? qi : sec;
+            double e0 = ph == kStart ? guess : (three ? qi : sec);
             if (!(e0 > blo && e0 < bhi)) e0 = sec;
             if (!(e0 > blo && e0 < bhi)) e0 = mid;
             const int pairs = ts == 4 ? 1 : 6;
             const double du = 16.0 * ulp_of(e0);
             double d = ldexp(fabs(e0 - sec), ts == 4 ? -4 : 3 - 3 * ((g - 1) >> 1));
+            if (ph == kStart) d = ldexp(0.12 * w, ts == 4 ? 0 : 1 - ((g - 1) >> 1));
             d = d > du ? d : du;
-            const bool even = ph == kStart || nbis >= 1;
+            const bool even = nbis >= 1;
             se = g == 0 ? e0 : ((g & 1) ? e0 - d : e0 + d);
-            const double part = ph == kStart ? (double)(g + 1) / (double)(ts + 1)
-                                : (even || g <= 2 * pairs) ? (double)g / (double)ts
-                                                           : (double)(g - 2 * pairs) / (double)(ts - 2 * pairs);
-            if (ph == kStart || (even && g > 0) || g > 2 * pairs || !(se > blo && se < bhi)) se = blo + w * part;
+            const double part = (even || g <= 2 * pairs) ? (double)g / (double)ts
+                                                         : (double)(g - 2 * pairs) / (double)(ts - 2 * pairs);
+            if ((even && g > 0) || g > 2 * pairs || !(se > blo && se < bhi)) se = blo + w * part;
             look = nbis >= 2;
             ph = kSearch;
           }
@@ -971,7 +1001,7 @@ __device__ __forceinline__ void solve_cells(const ReconParams &p, typename Caps:
       } else if (ph == kFixed) {
         se = p.iso;
       } else if (ts == 1) {
-        se = M.hint[ph == kHintMid ? 0 : (ph == kHintUp ? 2 : 1)][sl];
+        se = M.hint[0][sl];
       } else {
         // a team checks the narrowed bracket in one step: its first cut and
         // both ends, and points inside it
@@ -1213,42 +1243,27 @@ __device__ __forceinline__ void solve_cells(const ReconParams &p, typename Caps:
         }
         break;
       }
-      if (ph < kStart) {
-        if (ph == kHintMid) {
-          // the residual at the centre tells the side of the root: that
-          // half of the bracket is checked by a cut at its end (which is
-          // the centre itself when the root lies beyond it)
-          const bool end = M.hint[r > 0 ? 2 : 1][sl] == se;
-          if (end && st == VOFPC_CELL_OK) st = VOFPC_CELL_LEARNED_FALLBACK;
-          ph = end ? kStart : (r > 0 ? kHintUp : kHintDown);
-        } else {
-          // the bracket holds when its end is past the root; otherwise the
-          // root lies beyond that end
-          if (!(ph == kHintUp ? r < 0 : r > 0) && st == VOFPC_CELL_OK) st = VOFPC_CELL_LEARNED_FALLBACK;
-          ph = kStart;
-        }
-        if (r > 0) {
-          xa = se; fa = r;
-        } else {
-          xb = se; fb = r;
-        }
-        continue;
+      if (ph == kHintMid) {
+        hside = r > 0 ? 2 : 1;   // the root's side of the centre
+        ph = kSearch;
       }
-      // keep the end across the root from the estimate; xb the end of
-      // smaller residual
+      // the cut becomes the bracket end of its sign and the newest of the
+      // remembered ones
+      xd = xc; fd = fcv;
+      xc = above ? xa : xb; fcv = above ? fa : fb;
+      ++cuts;
+      nbis = fabs(r) > 0.5 * fmin(fabs(fa), fabs(fb)) ? nbis + 1 : 0;
       above = r > 0;
-      xd = xc;
-      xc = xb; fcv = fb;
-      if ((fa > 0) != above) {
-        xb = se; fb = r;
-      } else {
+      if (above) {
         xa = se; fa = r;
-      }
-      if (fabs(fa) < fabs(fb)) {
-        const double tx = xa, tf = fa;
-        xa = xb; fa = fb; xb = tx; fb = tf;
+      } else {
+        xb = se; fb = r;
       }
     }
+    // the narrowed bracket did not hold the root: the isovalue lies beyond its
+    // end on the root's side
+    if (hside == 2 && se > M.hint[2][sl] && st == VOFPC_CELL_OK) st = VOFPC_CELL_LEARNED_FALLBACK;
+    if (hside == 1 && se < M.hint[1][sl] && st == VOFPC_CELL_OK) st = VOFPC_CELL_LEARNED_FALLBACK;
     if (M.fin[8][lead] != 0.0) {
       st = VOFPC_CELL_BAD_INPUT;
     } else {
@@ -1287,15 +1302,20 @@ __device__ __forceinline__ void solve_cells(const ReconParams &p, typename Caps:
   }
 }
 
-// A wavefront's groups work as teams while every cell still gets a wavefront,
-// or a team of four groups a quarter of one, in this many rounds: a step of a
-// team costs what a step of one cell does, and the groups it joins had no
-// cells of their own.  On a launch of 2,048 wavefronts, whole plain steps:
-// 2,832 Voronoi cells 106 us in two rounds of teams, 123 us without; 3,342
-// cells 109 and 168 us; 5,000 hexahedra in teams of four 62 us, 79 us without,
-// 107 us in teams of sixteen (three rounds); 226 hexahedra in teams of
-// sixteen 45 us, 71 us without.
-constexpr int kTeamWaves = 2;
+// A wavefront's groups work as teams while the wavefronts still take them in
+// this many rounds: a step of a team costs what a step of one cell does, and
+// the groups it joins had no cells of their own.  Builds of 16 lanes a cell:
+// two rounds of teams of four; of four lanes a cell: one round of teams of
+// sixteen, then one of teams of four.  Whole label passes on 2,048 wavefronts:
+// 3,342 Voronoi cells 105 us in two rounds of teams, 134 us without teams; 2,832
+// with the network 120 and 135; 226 hexahedra in teams of sixteen 38 us, 53 us
+// without; 3,200 hexahedra in teams of four 60 us, of sixteen (two rounds)
+// 73 us; 10,251 without teams 83 us, in two rounds of teams of four 102 us.
+template <int C>
+__device__ __forceinline__ int cells_per_wave(int64_t count, int64_t waves) {
+  if (C == 16) return count <= waves ? 1 : (count <= 4 * waves ? 4 : 16);
+  return count <= 2 * waves ? 1 : C;
+}
 
 // Waves per SIMD a build's register budget is sized for: at most 2 (256
 // VGPRs).  A third one leaves 168 VGPRs and spills in the search: 24,042
@@ -1336,9 +1356,7 @@ void recon_group_kernel(ReconParams p) {
   tm.base = tm.lane & ~(G - 1);
   // cells per batch, cw, and groups per cell, ts: with few cells the groups
   // of a wavefront form teams that cut one cell at ts isovalues per step
-  tm.cw = C;
-  if (count <= (int64_t)kTeamWaves * gridDim.x) tm.cw = 1;
-  else if (C == 16 && count <= (int64_t)4 * kTeamWaves * gridDim.x) tm.cw = 4;
+  tm.cw = cells_per_wave<C>(count, gridDim.x);
   tm.ts = C / tm.cw;
   tm.g = tm.sl & (tm.ts - 1);
   tm.lead = tm.sl - tm.g;
