@@ -1,12 +1,11 @@
 // Mixed-cell and gradient-band compaction: a side-bit pass and a face pass
-// for the band test (meshes with cells of at most eight faces test it in the
-// cell pass), a
-// cell pass with wavefront ballots and block totals, the exclusive prefix of
-// the block totals, and a scatter, giving stable (ascending) index lists and
-// their lengths in device memory.  Up to kScanBlocks blocks each scatter
-// block sums the totals before it itself (no extra launch); beyond that a
-// one-block scan kernel computes the prefix once, so the work stays linear
-// in the number of blocks.
+// for the band test (small meshes, and meshes with cells of at most eight
+// faces, test it in the cell pass), a cell pass with wavefront ballots and
+// block totals, the exclusive prefix of the block totals, and a scatter, giving
+// stable (ascending) index lists and their lengths in device memory.  Up to
+// kScanBlocks blocks each scatter block sums the totals before it itself (no
+// extra launch); beyond that a one-block scan kernel computes the prefix once,
+// so the work stays linear in the number of blocks.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -22,6 +21,13 @@ constexpr int kCompactBlock = kCompactBlockCells;
 constexpr int kWaves = kCompactBlock / 64;
 constexpr int64_t kScanBlocks = 4096;   // above this many blocks the prefix is scanned once
 constexpr int kScanThreads = 1024;
+// Meshes with cells of more than eight faces: up to this many cells the cell
+// pass alone (its reads of the neighbours scatter, but it is one launch), above
+// it the side-bit and face passes before a flag pass.  Whole compactions with
+// the cell pass and with the three passes: 16,000 Voronoi cells 8.4 and 13.5 us,
+// 71,874: 8.8 and 13.5, 194,672: 10.6 and 13.5, 410,758: 19.8 and 16.5,
+// 3,083,230 with hexahedra 67.5 and 62.
+constexpr int64_t kCellPassCells = 262144;
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
 
@@ -121,31 +127,41 @@ __global__ __launch_bounds__(kCompactBlock) void compact_flags_kernel(DevMesh m,
   }
 }
 
-// The same flags and totals without the face pass, for meshes whose cells
-// have at most eight faces (hexahedra): each cell tests the band over its own
-// face neighbours, the eight slots' loads in flight together.  With more
-// faces per cell these reads scatter and the face pass is faster.
-__global__ __launch_bounds__(kCompactBlock) void compact_cells_kernel(DevMesh m, const double *alpha, double eps,
-                                                                      uint8_t *flags, int32_t *blk_cnt,
-                                                                      int64_t n_blk) {
-  __shared__ int32_t wsum[2][kWaves];
-  const int64_t P = blockIdx.x * (int64_t)kCompactBlock + threadIdx.x;
+// The same flags and totals without the face pass: each cell tests the band
+// over its own face neighbours, with W lanes (one for hexahedra, two for
+// polyhedra: four are no faster), each with kAhead slots' loads in flight
+// together.
+template <int W>
+__global__ __launch_bounds__(kCompactBlock * W) void compact_cells_kernel(DevMesh m, const double *alpha, double eps,
+                                                                          uint8_t *flags, int32_t *blk_cnt,
+                                                                          int64_t n_blk) {
+  constexpr int kAhead = W == 1 ? 8 : 4, kW = kCompactBlock * W / 64;
+  __shared__ int32_t wsum[2][kW];
+  const int64_t P = blockIdx.x * (int64_t)kCompactBlock + threadIdx.x / W;
+  const int lane = threadIdx.x % W;
   bool mixed = false, band = false;
   if (P < m.n_cells) {
     const double a = alpha[P];
     mixed = (a > eps) && (a < 1.0 - eps);
     band = mixed;
-    const int64_t i0 = m.cell_face_off[P], i1 = m.cell_face_off[P + 1];
-    int q[8];
-    double aq[8];
+    const int64_t i1 = m.cell_face_off[P + 1];
+    for (int64_t i = m.cell_face_off[P] + lane; i < i1; i += W * kAhead) {
+      int q[kAhead];
+      double aq[kAhead];
 #pragma unroll
-    for (int t = 0; t < 8; ++t) q[t] = (i0 + t < i1) ? m.cf_nbr[i0 + t] : -1;
+      for (int t = 0; t < kAhead; ++t) q[t] = (i + t * W < i1) ? m.cf_nbr[i + t * W] : -1;
 #pragma unroll
-    for (int t = 0; t < 8; ++t) aq[t] = q[t] >= 0 ? alpha[q[t]] : 0.5;
+      for (int t = 0; t < kAhead; ++t) aq[t] = q[t] >= 0 ? alpha[q[t]] : 0.5;
 #pragma unroll
-    for (int t = 0; t < 8; ++t) band = band || ((a - 0.5) * (aq[t] - 0.5) < 0.0);
-    flags[P] = (uint8_t)((mixed ? 1 : 0) | (band ? 2 : 0));
+      for (int t = 0; t < kAhead; ++t) band = band || ((a - 0.5) * (aq[t] - 0.5) < 0.0);
+    }
   }
+  if constexpr (W > 1) {   // the cell's first lane speaks for it
+    const uint64_t any = __ballot(band) >> (lane_id() & ~(W - 1));
+    band = lane == 0 && (any & ((1ull << W) - 1)) != 0;
+    mixed = mixed && lane == 0;
+  }
+  if (lane == 0 && P < m.n_cells) flags[P] = (uint8_t)((mixed ? 1 : 0) | (band ? 2 : 0));
   uint64_t bm = __ballot(mixed), bb = __ballot(band);
   const int w = threadIdx.x >> 6;
   if (lane_id() == 0) {
@@ -155,7 +171,7 @@ __global__ __launch_bounds__(kCompactBlock) void compact_cells_kernel(DevMesh m,
   __syncthreads();
   if (threadIdx.x < 2) {
     int32_t t = 0;
-    for (int i = 0; i < kWaves; ++i) t += wsum[threadIdx.x][i];
+    for (int i = 0; i < kW; ++i) t += wsum[threadIdx.x][i];
     blk_cnt[threadIdx.x * n_blk + blockIdx.x] = t;
   }
 }
@@ -308,7 +324,9 @@ static vofpc_status compact_on(vofpc_ctx ctx, vofpc_mesh M, const double *alpha,
   const int64_t nb = M->n_blk;
   hipStream_t s = ctx->stream;
   if (M->max_nf <= 8) {
-    compact_cells_kernel<<<(unsigned)nb, kCompactBlock, 0, s>>>(M->d, alpha, eps, flags, blk_cnt, nb);
+    compact_cells_kernel<1><<<(unsigned)nb, kCompactBlock, 0, s>>>(M->d, alpha, eps, flags, blk_cnt, nb);
+  } else if (M->d.n_cells < kCellPassCells) {
+    compact_cells_kernel<2><<<(unsigned)nb, 2 * kCompactBlock, 0, s>>>(M->d, alpha, eps, flags, blk_cnt, nb);
   } else {
     compact_side_kernel<<<(unsigned)nb, kCompactBlock, 0, s>>>(M->d.n_cells, alpha, side);
     const int64_t per = (int64_t)kCompactBlock * kFaceRun;
