@@ -1162,6 +1162,12 @@ __device__ __forceinline__ void solve_cells(const ReconParams &p, typename Caps:
         // sample i of the team on the lanes i, i + ts, ... of every row
         const int i = lane & (ts - 1);
         const double sx = M.smp[0][lead + i], sr = M.smp[1][lead + i], ar = fabs(sr);
+        // reductions over the samples, and the first sample of which c holds;
+        // a row repeats four samples, so its quads have all of them
+        const int row = lane & ~15;
+        auto row_min = [&](double x) { return G == 16 || ts == 4 ? tmin<4>(x) : tmin<16>(x); };
+        auto row_max = [&](double x) { return G == 16 || ts == 4 ? tmax<4>(x) : tmax<16>(x); };
+        auto sample = [&](bool c) { return first_bit(group_bits<16>(c, row)) & (ts - 1); };
         if (done) {
           win = 0;
         } else {
@@ -1178,10 +1184,9 @@ __device__ __forceinline__ void solve_cells(const ReconParams &p, typename Caps:
               st = VOFPC_CELL_LEARNED_FALLBACK;
             }
           }
-          if (!done) {
-            const double m1 = tmin<16>(ar);
-            done = m1 <= tol;
-            win = tmin_i<16>(ar == m1 ? i : ts);
+          if (!done && group_bits<16>(ar <= tol, row) != 0) {
+            done = true;
+            win = sample(ar == row_min(ar));
           }
         }
         if (!done) {
@@ -1190,22 +1195,23 @@ __device__ __forceinline__ void solve_cells(const ReconParams &p, typename Caps:
           const double inf = __builtin_inf();
           const double plo = xa, pfl = fa, phi_ = xb, pfh = fb;
           const bool pos = sr > 0 && sx > plo && sx < phi_;
-          const double slo = tmax<16>(pos ? sx : -inf);
+          const double slo = row_max(pos ? sx : -inf);
           if (slo > plo) {
-            fa = tmin<16>(pos && sx == slo ? sr : inf);
+            fa = M.smp[1][lead + sample(pos && sx == slo)];
             xa = slo;
           }
           const bool neg = !(sr > 0) && sx > xa && sx < phi_;
-          const double shi = tmin<16>(neg ? sx : inf);
+          const double shi = row_min(neg ? sx : inf);
           if (shi < phi_) {
-            fb = tmax<16>(neg && sx == shi ? sr : -inf);
+            fb = M.smp[1][lead + sample(neg && sx == shi)];
             xb = shi;
           }
           const bool off = sx != xa && sx != xb;
-          double m3 = tmin<16>(off ? ar : inf);
+          double m3 = row_min(off ? ar : inf);
           if (m3 < inf) {
-            xc = tmin<16>(off && ar == m3 ? sx : inf);
-            fcv = tmin<16>(off && sx == xc ? sr : inf);
+            const int j = lead + sample(off && ar == m3);
+            xc = M.smp[0][j];
+            fcv = M.smp[1][j];
           }
           if (xa != plo && fabs(pfl) < m3) {
             m3 = fabs(pfl);
