@@ -65,9 +65,10 @@
 // waits for its slowest cell.  31,886 hexahedra, label pass: 114 us (174 us);
 // 24,431 Voronoi cells: 230 us (280 us).
 // A narrowed bracket [h_lo, h_hi] starts with a cut at its centre (the network's
-// predicted isovalue).  An isovalue found beyond its end on the root's side has
-// the status LEARNED_FALLBACK; the end itself needs no cut (113,584 cells with
-// the network: 5.2 cuts a cell for 6.1).
+// predicted isovalue; a team: and at a quarter of its width beside it).  An
+// isovalue found outside it has the status LEARNED_FALLBACK; the ends need no
+// cut (113,584 cells with the network: 5.2 cuts a cell for 6.1; 1,159 cells in
+// teams 8.5 for 8.9, counting a team's step as two).
 //
 // Scheduling: a wavefront takes up to 64/G consecutive mixed entries (a
 // batch), stages them together, runs their searches side by side until the
@@ -841,10 +842,9 @@ __device__ __forceinline__ void solve_cells(const ReconParams &p, typename Caps:
       return fm / (double)n;
     };
     // One evaluation site; the phase decides where the next one is: the
-    // fixed isovalue, the centre of a narrowed bracket (a team: and its
-    // ends), the search estimate, or the bracket end kept when the search
-    // cannot stop.
-    enum { kFixed, kHintMid, kStart, kSearch, kFinal };
+    // fixed isovalue, the first estimate, the search's, or the bracket end
+    // kept when the search cannot stop.
+    enum { kFixed, kStart, kSearch, kFinal };
     const double iVP = 1.0 / VP;
     const double tol = p.tol_rel * (a < 1.0 - a ? a : 1.0 - a);
     // The search on the residual r(s) = V(s)/V_P - alpha: [xa, xb] is the
@@ -857,19 +857,19 @@ __device__ __forceinline__ void solve_cells(const ReconParams &p, typename Caps:
     // against the steps before (the rule of Brent 1973, ch. 4).  In a team,
     // (xc, fcv) is the cut of smallest residual off the bracket.
     double xa = pmin, fa = 1.0 - a, xb = pmax, fb = -a, xc = 0, fcv = 0, xd = 0, fd = 0;
-    int cuts = 0, hside = 0;
+    int cuts = 0;
     bool bis = false;
     const float qa = quantile(a);
-    double guess;
-    {
+    if (!hint) {
       double ps = 0.0;
 #pragma unroll
       for (int t = 0; t < KV; ++t)
         if (q + t * G < nv) ps += pw[t];
       const double W = pmax - pmin;
-      guess = tsum<G>(ps) / (double)nv + W * (double)qa;
+      double guess = tsum<G>(ps) / (double)nv + W * (double)qa;
       guess = fmin(guess, pmax - 0.3 * W * (double)quantile_power((float)a));
       guess = fmax(guess, pmin + 0.3 * W * (double)quantile_power((float)(1.0 - a)));
+      M.hint[0][sl] = guess;   // the first cut, in the place of a narrowed bracket's centre
     }
     // a jump of V: where a face with four or more crossings switches its
     // pairing (at its vertex-value mean) or a loop pinches at a vertex
@@ -883,7 +883,7 @@ __device__ __forceinline__ void solve_cells(const ReconParams &p, typename Caps:
     double xj = 0.0;
     int jtries = 0, nbis = 0;   // nbis in a team: steps in a row that hardly lowered the residual
     bool jnext = false, jpin = false, above = false;   // above: the last residual was positive
-    int ph = p.fixed_iso ? kFixed : (hint ? kHintMid : kStart);
+    int ph = p.fixed_iso ? kFixed : kStart;
     double se;
     while (true) {
       if (ph >= kStart) {
@@ -916,7 +916,7 @@ __device__ __forceinline__ void solve_cells(const ReconParams &p, typename Caps:
             if (!(jpin && se > blo && se < bhi)) {
               se = three ? qi : sec;
               if (cuts < 2)
-                se = cuts == 0 ? guess : x1 + (pmax - pmin) * (double)(qa - quantile(f1 + a));
+                se = cuts == 0 ? M.hint[0][sl] : x1 + (pmax - pmin) * (double)(qa - quantile(f1 + a));
               const double lastd = bis ? fabs(x1 - x2) : fabs(x2 - x3);
               bis = !(se > blo && se < bhi) || nbis >= 3 ||
                     (cuts > 2 && (fabs(se - x1) >= 0.5 * lastd || lastd < 4.0 * ulp_of(x1)));
@@ -939,13 +939,16 @@ __device__ __forceinline__ void solve_cells(const ReconParams &p, typename Caps:
             // 4096th with sixteen); and points that divide the bracket evenly,
             // in place of those that fall outside it, and of all but the
             // estimate after a step that hardly lowered the residual
-            double e0 = ph == kStart ? guess : (three ? qi : sec);
+            double e0 = ph == kStart ? M.hint[0][sl] : (three ? qi : sec);
             if (!(e0 > blo && e0 < bhi)) e0 = sec;
             if (!(e0 > blo && e0 < bhi)) e0 = mid;
             const int pairs = ts == 4 ? 1 : 6;
             const double du = 16.0 * ulp_of(e0);
             double d = ldexp(fabs(e0 - sec), ts == 4 ? -4 : 3 - 3 * ((g - 1) >> 1));
-            if (ph == kStart) d = ldexp(0.12 * w, ts == 4 ? 0 : 1 - ((g - 1) >> 1));
+            if (ph == kStart) {   // what the first estimate is worth
+              d = hint ? 0.25 * (M.hint[2][sl] - M.hint[1][sl]) : 0.12 * w;
+              d = ldexp(d, ts == 4 ? 0 : 1 - ((g - 1) >> 1));
+            }
             d = d > du ? d : du;
             const bool even = nbis >= 1;
             se = g == 0 ? e0 : ((g & 1) ? e0 - d : e0 + d);
@@ -998,15 +1001,8 @@ __device__ __forceinline__ void solve_cells(const ReconParams &p, typename Caps:
             }
           }
         }
-      } else if (ph == kFixed) {
-        se = p.iso;
-      } else if (ts == 1) {
-        se = M.hint[0][sl];
       } else {
-        // a team checks the narrowed bracket in one step: its first cut and
-        // both ends, and points inside it
-        const double hl = M.hint[1][sl], hh = M.hint[2][sl];
-        se = g < 3 ? M.hint[g][sl] : hl + (hh - hl) * ((double)(g - 2) / (double)(ts - 2));
+        se = p.iso;
       }
       // ---- the evaluation at se: edges
       double vf = 0.0;
@@ -1171,19 +1167,6 @@ __device__ __forceinline__ void solve_cells(const ReconParams &p, typename Caps:
         if (done) {
           win = 0;
         } else {
-          if (ph == kHintMid) {
-            // the residual at the first cut tells the side of the root; the
-            // bracket holds when its end on that side is past the root
-            const double rm = M.smp[1][lead];
-            const int end = rm > 0 ? 2 : 1;
-            const double re = M.smp[1][lead + end];
-            if (fabs(rm) <= tol || fabs(re) <= tol) {
-              done = true;
-              win = fabs(rm) <= tol ? 0 : end;
-            } else if (!(rm > 0 ? re < 0 : re > 0) && st == VOFPC_CELL_OK) {
-              st = VOFPC_CELL_LEARNED_FALLBACK;
-            }
-          }
           if (!done && group_bits<16>(ar <= tol, row) != 0) {
             done = true;
             win = sample(ar == row_min(ar));
@@ -1209,9 +1192,8 @@ __device__ __forceinline__ void solve_cells(const ReconParams &p, typename Caps:
           const bool off = sx != xa && sx != xb;
           double m3 = row_min(off ? ar : inf);
           if (m3 < inf) {
-            const int j = lead + sample(off && ar == m3);
-            xc = M.smp[0][j];
-            fcv = M.smp[1][j];
+            xc = row_min(off && ar == m3 ? sx : inf);
+            fcv = M.smp[1][lead + sample(off && sx == xc)];
           }
           if (xa != plo && fabs(pfl) < m3) {
             m3 = fabs(pfl);
@@ -1221,10 +1203,6 @@ __device__ __forceinline__ void solve_cells(const ReconParams &p, typename Caps:
             xc = phi_; fcv = pfh;
           }
           nbis = fmin(fabs(fa), fabs(fb)) > 0.25 * fmin(fabs(pfl), fabs(pfh)) ? nbis + 1 : 0;
-          if (ph == kHintMid) {
-            nbis = 0;
-            ph = kSearch;
-          }
           wave_sync();
           continue;
         }
@@ -1249,10 +1227,6 @@ __device__ __forceinline__ void solve_cells(const ReconParams &p, typename Caps:
         }
         break;
       }
-      if (ph == kHintMid) {
-        hside = r > 0 ? 2 : 1;   // the root's side of the centre
-        ph = kSearch;
-      }
       // the cut becomes the bracket end of its sign and the newest of the
       // remembered ones
       xd = xc; fd = fcv;
@@ -1266,10 +1240,8 @@ __device__ __forceinline__ void solve_cells(const ReconParams &p, typename Caps:
         xb = se; fb = r;
       }
     }
-    // the narrowed bracket did not hold the root: the isovalue lies beyond its
-    // end on the root's side
-    if (hside == 2 && se > M.hint[2][sl] && st == VOFPC_CELL_OK) st = VOFPC_CELL_LEARNED_FALLBACK;
-    if (hside == 1 && se < M.hint[1][sl] && st == VOFPC_CELL_OK) st = VOFPC_CELL_LEARNED_FALLBACK;
+    // the narrowed bracket did not hold the root
+    if (hint && st == VOFPC_CELL_OK && (se < M.hint[1][sl] || se > M.hint[2][sl])) st = VOFPC_CELL_LEARNED_FALLBACK;
     if (M.fin[8][lead] != 0.0) {
       st = VOFPC_CELL_BAD_INPUT;
     } else {
