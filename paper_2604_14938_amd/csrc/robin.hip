@@ -9,11 +9,12 @@
 // t = (a_P - 1/2)/(a_P - a_Q)) measured along the face normal, and A_int,f the
 // face-normal projection of the two cells' interface area vectors A n.
 //
-// Three small kernels: the mixed list is scattered into a per-mesh map
-// cell -> entry (so a face can find both cells' interfaces), a row of 16
-// lanes per band entry (one face per lane) sums its side of every detached
-// face and the owner side appends the face record, and the map is cleared
-// again (it stays -1 between calls).
+// Two small kernels: the mixed list is scattered into a per-mesh map cell ->
+// entry (so a face can find both cells' interfaces), and a row of 16 lanes per
+// band entry (one face per lane) sums its side of every detached face and the
+// owner side appends the face record.  The map keeps what earlier calls left
+// in it: an entry counts only if the list holds the cell there now, which
+// costs a gather in place of a launch that cleared the map.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -27,23 +28,24 @@ constexpr int kRbBlock = 256;
 constexpr int kRbLanes = 16;   // lanes per band cell (one DPP row)
 
 __global__ __launch_bounds__(256) void robin_map_kernel(const int32_t *mixed, const int32_t *counts, int64_t cap,
-                                                        int32_t *entry, int32_t value_is_index, int32_t *n_face) {
+                                                        int32_t *entry, int32_t *n_face) {
   int64_t n = counts[0];
   if (n > cap) n = cap;
   const int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (k < n) entry[mixed[k]] = value_is_index ? (int32_t)k : -1;
+  if (k < n) entry[mixed[k]] = (int32_t)k;
   if (n_face && k == 0) *n_face = 0;
 }
 
 struct RobinParams {
   DevMesh m;
   const double *alpha;
-  const int32_t *band;
+  const int32_t *band, *mixed;
   const int32_t *counts;
   const int32_t *entry;
   vofpc_interface itf;
   double k_l, k_v;
   double *a_diag;
+  int64_t n_mixed;   // entries in the list (set by the kernel)
   int64_t face_cap;
   int32_t *face_idx;
   double *face_a, *face_d, *face_area;
@@ -53,7 +55,7 @@ struct RobinParams {
 // interface area vector A n of a cell (zero without an interface)
 __device__ __forceinline__ void area_vector(const RobinParams &p, int C, double *s) {
   const int e = p.entry[C];
-  if (e < 0) {
+  if (e < 0 || e >= p.n_mixed || p.mixed[e] != C) {
     s[0] = s[1] = s[2] = 0.0;
     return;
   }
@@ -127,6 +129,7 @@ __global__ __launch_bounds__(kRbBlock) void robin_kernel(RobinParams p) {
   const DevMesh &m = p.m;
   const int64_t N = m.n_cells;
   const int64_t nb = p.counts[1];
+  p.n_mixed = p.counts[0] < p.itf.cap ? p.counts[0] : p.itf.cap;
   const int lane = threadIdx.x % kRbLanes;
   const int wl = threadIdx.x & 63, wave = threadIdx.x >> 6;
   // a row of 16 lanes per band cell, one face per lane; the block walks the
@@ -223,11 +226,13 @@ extern "C" vofpc_status vofpc_robin(vofpc_ctx ctx, vofpc_mesh M, const double *a
   }
   const int64_t cap = std::min<int64_t>(itf->cap, N);
   const unsigned gM = (unsigned)std::max<int64_t>(1, (cap + 255) / 256);
-  robin_map_kernel<<<gM, 256, 0, s>>>(mixed_idx, counts, itf->cap, M->rb_entry, 1, n_face);
+  robin_map_kernel<<<gM, 256, 0, s>>>(mixed_idx, counts, itf->cap, M->rb_entry, n_face);
   RobinParams p;
   p.m = M->d;
   p.alpha = alpha;
   p.band = band_idx;
+  p.mixed = mixed_idx;
+  p.n_mixed = 0;
   p.counts = counts;
   p.entry = M->rb_entry;
   p.itf = *itf;
@@ -244,7 +249,6 @@ extern "C" vofpc_status vofpc_robin(vofpc_ctx ctx, vofpc_mesh M, const double *a
   const unsigned gB = (unsigned)std::max<int64_t>(
       1, std::min<int64_t>((N + cells_per_block - 1) / cells_per_block, (int64_t)ctx->n_cu * 4));
   robin_kernel<<<gB, kRbBlock, 0, s>>>(p);
-  robin_map_kernel<<<gM, 256, 0, s>>>(mixed_idx, counts, itf->cap, M->rb_entry, 0, nullptr);
   VOFPC_HIP(hipGetLastError());
   return VOFPC_OK;
 }

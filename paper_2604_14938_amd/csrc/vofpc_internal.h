@@ -207,7 +207,8 @@ struct vofpc_mesh_s {
   double *ex_theta = nullptr;      // per domain entry: pseudo-time fraction
   int32_t *ex_upn = nullptr;       // per cell-face slot: neighbour of a packed upwind weight
   int2 *ex_upr = nullptr;          // per domain entry: first slot and count of its upwind weights
-  // interface coupling: mixed entry of each cell (-1 between calls)
+  // interface coupling: mixed entry of each cell, as the last calls left it
+  // (-1 at first); it holds where the list has the cell at that entry
   int32_t *rb_entry = nullptr;
   // curvature scratch: [3][n_cells] (smoothing ping-pong, raw and step-1
   // curvature), and the ring of every cell
