@@ -117,10 +117,8 @@ typedef struct {
 } vofpc_mesh_desc;
 
 /* Validate and upload a mesh, then compute its geometry on the device: cell
- * volumes V and centroids x_P, face area vectors S_f and area centroids x_f,
- * the stored inverse least-squares matrix of every cell (six components of
- * the symmetric inverse, App. B) and the inverse-distance weights that carry
- * cell values to vertices.  Synchronises the context stream.  Returns
+ * volumes V and centroids x_P, face area vectors S_f and area centroids x_f
+ * and the inverse-distance weights that carry cell values to vertices.  Synchronises the context stream.  Returns
  * VOFPC_E_MESH for inconsistent topology, open or inverted cells. */
 vofpc_status vofpc_mesh_upload(vofpc_ctx ctx, const vofpc_mesh_desc *desc, vofpc_mesh *out);
 /* Disjoint union of n uploaded meshes (multi-instance batches, several
@@ -329,9 +327,8 @@ vofpc_status vofpc_autotune(vofpc_ctx ctx, vofpc_mesh mesh, const double *alpha,
 /* Interface-modified least-squares gradient of T (App. B with Sec. 2.4.4).
  * T: DEVICE [n_cells]; T_bface: DEVICE [n_faces] (values used on faces with
  * face_bc == 1); alpha: DEVICE [n_cells]; band_idx/counts from
- * vofpc_compact (ignored for VOFPC_SCOPE_ALL).  Band cells build their
- * least-squares matrix on the fly; other cells use the stored inverse (plain
- * variants without flags only; with a flag every cell builds its own).
+ * vofpc_compact (ignored for VOFPC_SCOPE_ALL).  Every cell builds its
+ * least-squares matrix (App. B) from the stencil that its right-hand side reads.
  * variant: VOFPC_GRAD_MODIFIED/STANDARD/PRINTED, optionally or-ed with one
  * weight flag and VOFPC_GRAD_VERTEX_STENCIL; anything else is
  * VOFPC_E_INVALID_ARG.  The first call with the vertex stencil on a mesh

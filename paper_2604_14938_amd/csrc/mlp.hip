@@ -555,10 +555,12 @@ __global__ __launch_bounds__(64) void features_kernel(DevMesh m, const double *a
 
 using namespace vofpc;
 
+constexpr int kW2t = (kParams + 63) / 64 * 64;   // words before the transposed W2: whole 128-byte lines
+
 struct vofpc_mlp_s {
   vofpc_ctx ctx;
   float *master = nullptr;
-  uint16_t *wb = nullptr, *w2t = nullptr;   // BF16 parameters; W2 transposed
+  uint16_t *wb = nullptr, *w2t = nullptr;   // BF16 parameters; W2 transposed, behind them
   float *m = nullptr, *v = nullptr;
   float *partial = nullptr;
   int max_blocks = 0;
@@ -581,16 +583,15 @@ extern "C" vofpc_status vofpc_mlp_create(vofpc_ctx ctx, int64_t max_batch, vofpc
   if (hipMalloc(&M->master, sizeof(float) * kParams) != hipSuccess ||
       hipMalloc(&M->m, sizeof(float) * kParams) != hipSuccess ||
       hipMalloc(&M->v, sizeof(float) * kParams) != hipSuccess ||
-      hipMalloc(&M->wb, sizeof(uint16_t) * kParams) != hipSuccess ||
-      hipMalloc(&M->w2t, sizeof(uint16_t) * kHid * kHid) != hipSuccess ||
+      hipMalloc(&M->wb, sizeof(uint16_t) * (kW2t + kHid * kHid)) != hipSuccess ||
       hipMalloc(&M->partial, sizeof(float) * (size_t)M->max_blocks * (kParams + 1)) != hipSuccess) {
     vofpc_mlp_destroy(M);
     set_error("mlp_create: hipMalloc failed");
     return VOFPC_E_OOM;
   }
+  M->w2t = M->wb + kW2t;
   VOFPC_HIP(hipMemset(M->master, 0, sizeof(float) * kParams));
-  VOFPC_HIP(hipMemset(M->wb, 0, sizeof(uint16_t) * kParams));
-  VOFPC_HIP(hipMemset(M->w2t, 0, sizeof(uint16_t) * kHid * kHid));
+  VOFPC_HIP(hipMemset(M->wb, 0, sizeof(uint16_t) * (kW2t + kHid * kHid)));
   VOFPC_HIP(hipMemset(M->m, 0, sizeof(float) * kParams));
   VOFPC_HIP(hipMemset(M->v, 0, sizeof(float) * kParams));
   M->t = 0;
@@ -603,7 +604,7 @@ extern "C" vofpc_status vofpc_mlp_destroy(vofpc_mlp M) {
   if (!M) return VOFPC_OK;
   (void)hipSetDevice(M->ctx->device);
   (void)hipFree(M->master); (void)hipFree(M->wb); (void)hipFree(M->m); (void)hipFree(M->v);
-  (void)hipFree(M->w2t); (void)hipFree(M->partial);
+  (void)hipFree(M->partial);
   delete M;
   return VOFPC_OK;
 }

@@ -176,9 +176,9 @@ class Context:
         _check(lib.vofpc_ctx_time_classes(self.h, int(bool(enable))), "vofpc_ctx_time_classes")
 
     def class_ms(self) -> tuple:
-        """Durations (ms) of the class kernels of the latest reconstruction
-        and of their bracket passes (learned form), -1 where none ran
-        (vofpc_ctx_class_ms): (kernels[4], passes[4])."""
+        """Durations (ms) of the class kernels of the latest reconstruction,
+        -1 where none ran (vofpc_ctx_class_ms): (kernels[4], passes[4]); the
+        passes are -1, the network runs inside the kernels."""
         a = (ctypes.c_float * 8)()
         _check(lib.vofpc_ctx_class_ms(self.h, a), "vofpc_ctx_class_ms")
         v = [float(x) for x in a]
