@@ -701,7 +701,7 @@ __device__ __forceinline__ void solve_cells(const ReconParams &p, typename Caps:
     }
   }
   // ---- phase 2: the narrowed bracket of every cell with a vertex field,
-  // from the network or the caller
+  // from the network or the caller (a fixed isovalue has no search and none)
   bool hint = false;
   if constexpr (NET) {
     double nlo = __builtin_nan(""), nhi = __builtin_nan("");   // none where the network does not run
@@ -722,7 +722,7 @@ __device__ __forceinline__ void solve_cells(const ReconParams &p, typename Caps:
         nlo = sh - dl;
         nhi = sh + dl;
         const double hl = nlo > pmin ? nlo : pmin, hh = nhi < pmax ? nhi : pmax;
-        hint = hl <= hh;
+        hint = hl <= hh && !p.fixed_iso;
         M.hint[0][sl] = sh < hl ? hl : (sh > hh ? hh : sh);
         M.hint[1][sl] = hl;
         M.hint[2][sl] = hh;
@@ -734,7 +734,7 @@ __device__ __forceinline__ void solve_cells(const ReconParams &p, typename Caps:
     }
     wave_sync();
   } else {
-    if (active && have_field && p.use_hint) {
+    if (active && have_field && p.use_hint && !p.fixed_iso) {
       double hl = p.hint_lo[k], hh = p.hint_hi[k];
       if (!isnan(hl) && !isnan(hh)) {
         hl = hl > pmin ? hl : pmin;
