@@ -226,7 +226,8 @@ vofpc_status vofpc_compact_noalloc(vofpc_ctx ctx, vofpc_mesh mesh, const double 
 typedef struct {
   double eps_mixed;   /* mixed when eps < alpha < 1-eps (default 1e-8) */
   double tol_rel;     /* stop when |V/V_P - alpha| <= tol_rel min(alpha,1-alpha) (1e-13) */
-  int32_t max_iter;   /* volume evaluations per cell before VOFPC_CELL_MAX_ITER (100) */
+  int32_t max_iter;   /* volume evaluations per cell, counted as in vofpc_interface.iters,
+                       * before VOFPC_CELL_MAX_ITER (100) */
   int32_t vertex_mode;/* VOFPC_VERTEX_* */
   int32_t fixed_iso;  /* nonzero: no root-find, cut at `iso` (paper's isoap mode) */
   int32_t bracket;    /* VOFPC_BRACKET_* */
@@ -248,8 +249,10 @@ typedef struct {
   double *d;          /* n . (x_P - c_int), positive when x_P is in the liquid */
   double *alpha_got;  /* V_liq(s)/V_P */
   int32_t *status;    /* VOFPC_CELL_* */
-  int32_t *iters;     /* volume evaluations spent (4 or 16 isovalues cut side by side by a
-                       * group flavour count as 2 or 4, the halvings they stand for) */
+  int32_t *iters;     /* volume evaluations spent: 1 for a fixed isovalue; 4 or 16 isovalues
+                       * that a group flavour cuts side by side in a step of the search
+                       * (launches that do not fill the chip) count as 2 or 4, the halvings
+                       * they stand for, also against max_iter */
   int64_t cap;
 } vofpc_interface;
 

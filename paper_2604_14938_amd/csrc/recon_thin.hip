@@ -582,7 +582,7 @@ struct Build {
 struct Team {
   int lane, sl, q, base;   // lane, its group, its place in the group, the group's first lane
   int cw, ts, g, lead;     // g: the group's place in its team, lead: the team's first group
-  int weight;              // evaluations a step counts as
+  int weight;              // evaluations a step of the search counts as
 };
 
 // A mixed entry and its cell's place in the mesh arrays.
@@ -1146,7 +1146,7 @@ __device__ __forceinline__ void solve_cells(const ReconParams &p, typename Caps:
       const double V = (vf + Vi) * (1.0 / 6.0);
       double frac = V * iVP;
       frac = fma(fma(-VP, frac, V), iVP, frac);
-      it += tm.weight;
+      it += ph == kSearch ? tm.weight : 1;   // a fixed isovalue and the end kept are one cut
       const double r = frac - a;
       bool done = ph == kFixed || ph == kFinal;
       int win = g;   // the group whose cut ends the search

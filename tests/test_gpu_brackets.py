@@ -1,6 +1,6 @@
-"""The status of a reconstruction that is given a bracket per cell and a fixed
-isovalue, where no search runs.  One cell per group and in teams, against the
-oracle."""
+"""The status and the evaluation count of a reconstruction that is given a
+bracket per cell and a fixed isovalue, where no search runs.  One cell per group
+and in teams, against the oracle."""
 import numpy as np
 import pytest
 
@@ -63,3 +63,9 @@ def test_a_fixed_isovalue_is_not_judged_by_the_bracket(V, kind, form):  # noqa: 
         parity.check_interface(wl, {k: (v[..., cut] if k in PER_CELL else v) for k, v in g.items()}, rec)
 
     _fixed_iso(V, kind, form, check)
+
+
+@pytest.mark.parametrize("kind", ["hex", "voronoi"])
+def test_a_fixed_isovalue_is_one_evaluation(V, kind):  # noqa: F811
+    _fixed_iso(V, kind, "hint",
+               lambda m, g, wl, rec: np.testing.assert_array_equal(g["iters"], rec["iters"][g["mixed_idx"]]))
