@@ -273,12 +273,13 @@ typedef struct {
  * oracle's bisection may stop at another one of the same window.
  * hint_lo/hint_hi: DEVICE [cap] per mixed entry, read only when
  * opts->bracket is VOFPC_BRACKET_HINT (NaN entries: plain search, no flag):
- * the bracket, clipped to [phi_min, phi_max], is checked with two cuts, at
- * its centre and at its end on the side of the root that the centre's
- * residual gives.  When that end is past the root the search goes on in
- * the half between them; otherwise it goes on beyond that end and the cell
- * is flagged VOFPC_CELL_LEARNED_FALLBACK.  The flag therefore marks exactly
- * the cells whose root lies outside the clipped bracket (V(s) decreasing),
+ * the bracket, clipped to [phi_min, phi_max], is cut at its centre first, and
+ * at an end before the search leaves it there (the wavefront flavours: at the
+ * end on the side of the root that the centre's residual gives, at once).  An
+ * end that meets the tolerance is a result.  When the end is past the root the
+ * search goes on inside the bracket; otherwise it goes on beyond that end and
+ * the cell is flagged VOFPC_CELL_LEARNED_FALLBACK.  The flag therefore marks
+ * exactly the cells whose root lies outside the clipped bracket (V(s) decreasing),
  * as a cut at both ends would. */
 vofpc_status vofpc_reconstruct(vofpc_ctx ctx, vofpc_mesh mesh, const double *alpha, const int32_t *mixed_idx,
                                const int32_t *counts, const vofpc_recon_opts *opts, const double *hint_lo,

@@ -65,10 +65,10 @@
 // waits for its slowest cell.  31,886 hexahedra, label pass: 114 us (174 us);
 // 24,431 Voronoi cells: 230 us (280 us).
 // A narrowed bracket [h_lo, h_hi] starts with a cut at its centre (the network's
-// predicted isovalue; a team: and at a quarter of its width beside it).  An
-// isovalue found outside it has the status LEARNED_FALLBACK; the ends need no
-// cut (113,584 cells with the network: 5.2 cuts a cell for 6.1; 1,159 cells in
-// teams 8.5 for 8.9, counting a team's step as two).
+// predicted isovalue; a team: and at its ends).  A step that would leave the
+// bracket cuts the end it would pass instead; an isovalue found outside has the
+// status LEARNED_FALLBACK.  So the flag says that a cut at the end is short of
+// the root, as if both ends had been cut, and most cells cut none.
 //
 // Scheduling: a wavefront takes up to 64/G consecutive mixed entries (a
 // batch), stages them together, runs their searches side by side until the
@@ -1003,6 +1003,18 @@ __device__ __forceinline__ void solve_cells(const ReconParams &p, typename Caps:
               ++jtries;
             }
           }
+          if (hint) {
+            // a step that would leave the narrowed bracket cuts its end first:
+            // the bracket ends then meet the tolerance, hold the root or are
+            // known to be short of it.  A team cuts both ends in its first step.
+            const double hl = M.hint[1][sl], hh = M.hint[2][sl];
+            const bool lo_open = hl > blo && hl < bhi, hi_open = hh > blo && hh < bhi;
+            const bool at_lo = lo_open && (ts == 1 ? se < hl : g == 1), at_hi = hi_open && (ts == 1 ? se > hh : g == 2);
+            if (at_lo || at_hi) {
+              se = at_lo ? hl : hh;
+              jnext = jpin = false;
+            }
+          }
         }
       } else {
         se = p.iso;
@@ -1172,7 +1184,10 @@ __device__ __forceinline__ void solve_cells(const ReconParams &p, typename Caps:
         } else {
           if (!done && group_bits<16>(ar <= tol, row) != 0) {
             done = true;
-            win = sample(ar == row_min(ar));
+            // (the smallest residual; inside the narrowed bracket if one is)
+            const bool in = ar <= tol && !(hint && (sx < M.hint[1][sl] || sx > M.hint[2][sl]));
+            const double least = group_bits<16>(in, row) != 0 ? row_min(in ? ar : __builtin_inf()) : row_min(ar);
+            win = sample(ar == least && (in || group_bits<16>(in, row) == 0));
           }
         }
         if (!done) {

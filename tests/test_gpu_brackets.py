@@ -1,6 +1,7 @@
 """The status and the evaluation count of a reconstruction that is given a
-bracket per cell and a fixed isovalue, where no search runs.  One cell per group
-and in teams, against the oracle."""
+bracket per cell: with a fixed isovalue, where no search runs, and where an end
+of the bracket is the isovalue itself.  One cell per group and in teams, against
+the oracle."""
 import numpy as np
 import pytest
 
@@ -69,3 +70,54 @@ def test_a_fixed_isovalue_is_not_judged_by_the_bracket(V, kind, form):  # noqa: 
 def test_a_fixed_isovalue_is_one_evaluation(V, kind):  # noqa: F811
     _fixed_iso(V, kind, "hint",
                lambda m, g, wl, rec: np.testing.assert_array_equal(g["iters"], rec["iters"][g["mixed_idx"]]))
+
+
+@pytest.mark.parametrize("kind", ["hex", "voronoi"])
+def test_brackets_that_end_at_the_isovalue(V, kind):  # noqa: F811
+    """Brackets from, to and about the isovalue of the plain search hold it
+    (an end whose volume meets the tolerance is a result); brackets beside it
+    do not, unless nothing of them lies in the cell's range."""
+    import torch
+    from paper_2604_14938_amd import runner
+    wl, _ = _case(kind)
+    om = oracle.OMesh(wl.mesh)
+    geom = oracle.geometry(om)
+    run = runner.PathRun(wl, ctx=V.Context(0, stream=torch.cuda.Stream()))
+    run.step()
+    full = run.results()
+    b, M = run.buf, full["n_mixed"]
+    feat = torch.empty(M, 32, dtype=torch.float32, device=run.dev)
+    rng = torch.empty(M, 2, dtype=torch.float64, device=run.dev)
+    V.features(run.ctx, run.mesh, run.alpha, b.mixed_idx, b.counts, feat, rng)
+    torch.cuda.synchronize()
+    W = rng[:, 1].cpu().numpy()
+    opts = V.recon_opts(bracket=V.BRACKET_HINT)
+    for m in COUNTS:
+        m = m or M
+        cnt = torch.tensor([m, full["n_band"]], dtype=torch.int32, device=run.dev)
+        torch.cuda.synchronize()
+        V.reconstruct(run.ctx, run.mesh, run.alpha, b.mixed_idx, cnt, b.itf)
+        plain = _first(run.results(), m)
+        s, w, idx, ok = plain["s"], 0.02 * W[:m], plain["mixed_idx"], plain["status"] == V.CELL_OK
+        a = wl.alpha[idx]
+        # where the search ended within the tolerance, not at adjacent doubles
+        met = ok & (np.abs(plain["alpha_got"] - a) <= 1e-13 * np.minimum(a, 1.0 - a))
+        assert met.mean() > 0.95
+        for name, lo, hi in (("from", s, s + w), ("to", s - w, s), ("point", s, s), ("about", s - w, s + 0.7 * w),
+                             ("above", s + 0.1 * w, s + w), ("below", s - w, s - 0.1 * w)):
+            print(f"[gpu-case] brackets {kind} {name}: {m} of {M} cells", flush=True)
+            l, h = (torch.as_tensor(x, dtype=torch.float64, device=run.dev) for x in (lo, hi))
+            torch.cuda.synchronize()
+            V.reconstruct(run.ctx, run.mesh, run.alpha, b.mixed_idx, cnt, b.itf, opts, l, h)
+            g = _first(run.results(), m)
+            if name in ("from", "to", "point"):
+                want = np.full(m, V.CELL_OK)
+            else:
+                dl, dh = np.full(wl.mesh.n_cells, np.nan), np.full(wl.mesh.n_cells, np.nan)
+                dl[idx], dh[idx] = lo, hi
+                want = oracle.reconstruct(om, wl.alpha, geom, hint_lo=dl, hint_hi=dh, cells=idx)["status"][idx]
+                assert ((want == V.CELL_LEARNED_FALLBACK).mean() > 0.5) == (name != "about")
+            wrong = np.nonzero((met if name in ("from", "to", "point") else ok) & (g["status"] != want))[0]
+            assert wrong.size == 0, (name, m, wrong.size, idx[wrong[:4]], g["status"][wrong[:4]], want[wrong[:4]])
+            np.testing.assert_allclose(g["alpha_got"][ok], a[ok], rtol=0, atol=1e-12)
+    run.close()
