@@ -386,8 +386,8 @@ vofpc_status vofpc_extrap_opts_default(vofpc_extrap_opts *opts);
  * gradT_l, gradT_v: DEVICE [3][n_cells], written on D only.  report:
  * optional DEVICE int32[2] = (sweeps done, 0).  All sweeps run in one
  * persistent kernel of at most one block per compute unit, which ends after
- * the last one needed; a wait for another block that takes 2 seconds ends it
- * with NaN outputs and a 1 in report[1].  The first
+ * the last one needed; a block that waits for another one for seconds gives up,
+ * with NaN outputs on its cells and a 1 in report[1].  The first
  * call on a mesh allocates its scratch (mesh-owned) and must not be captured;
  * later calls are graph-capturable.  Calls on one mesh must not overlap. */
 vofpc_status vofpc_extrapolate(vofpc_ctx ctx, vofpc_mesh mesh, const double *alpha, const double *T,

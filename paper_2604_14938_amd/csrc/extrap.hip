@@ -29,26 +29,26 @@
 
 #include "lsq.h"
 #include "ring_ops.h"
+#include "sweep_sync.h"
 #include "vofpc_internal.h"
 #include "wave_ops.h"
 
 namespace vofpc {
 
 constexpr int kExBlock = 256;
-constexpr int kExMaxBlocks = 1024;      // blocks of the sweep kernel at most
-constexpr int kExFlags = 2 * kExMaxBlocks + 2;   // two rows of barrier flags; blocks that came, blocks that take part
 constexpr int8_t kExInterface = 127;    // mark of a domain cell with an interface (layers end at 100)
 
 __device__ __forceinline__ bool is_mixed(double a, double eps) { return a > eps && a < 1.0 - eps; }
 
-// layer 0: the mixed cells; everything else outside; the list length and the
-// barrier flags are reset
+// layer 0: the mixed cells; everything else outside; the list length, the
+// barrier flags and the report are reset
 __global__ __launch_bounds__(kExBlock) void ex_init_kernel(int64_t n, const double *alpha, double eps, int8_t *mark,
-                                                           int32_t *info, uint32_t *flag) {
+                                                           int32_t *info, uint32_t *flag, int32_t *report) {
   const int64_t P = blockIdx.x * (int64_t)kExBlock + threadIdx.x;
   if (P < n) mark[P] = is_mixed(alpha[P], eps) ? 0 : -1;
-  for (int64_t i = P; i < kExFlags; i += (int64_t)gridDim.x * kExBlock) flag[i] = 0;
+  for (int64_t i = P; i < kSyncWords; i += (int64_t)gridDim.x * kExBlock) flag[i] = 0;
   if (P == 0) info[1] = 0;
+  if (P < 2 && report) report[P] = 0;
 }
 
 // the list of the domain, by the first blocks; by the others, the mixed entry
@@ -238,7 +238,7 @@ constexpr uint64_t kExGatherTicks = 5000;   // 50 us of the 100 MHz wall clock
 __device__ __forceinline__ int gather_blocks(uint32_t *flag, int &nb) {
   __shared__ int id, count;
   if (threadIdx.x == 0) {
-    uint32_t *came = flag + 2 * kExMaxBlocks, *part = came + 1;
+    uint32_t *came = flag + 2 * kSyncRow, *part = came + 1;
     constexpr uint32_t kClosed = 0x80000000u;
     const uint32_t k = __hip_atomic_fetch_add(came, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     int n = 0;
@@ -261,37 +261,33 @@ __device__ __forceinline__ int gather_blocks(uint32_t *flag, int &nb) {
   return id;
 }
 
+// The lanes of a wavefront and its agent-scope accesses for the flags.
+struct WaveSync {
+  static constexpr int kLanes = 64;
+  __device__ __forceinline__ int lane() const { return threadIdx.x & 63; }
+  __device__ __forceinline__ uint32_t load(const uint32_t *a) const {
+    return __hip_atomic_load(a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __device__ __forceinline__ void store(uint32_t *a, uint32_t v) const {
+    __hip_atomic_store(a, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __device__ __forceinline__ bool any(bool b) const { return __any(b); }
+};
+
 // Barrier over the nb blocks that take part (this one number id), epoch 1, 2,
 // ...: every agent-scope store made before it is seen by every agent-scope load
-// after it.  Returns in `any` whether some block brought `mine`.  The flags
-// alternate between two rows, so a block that runs ahead cannot overwrite a
-// flag that is still to be read.  The first wavefront polls for its block
-// (1.6 us a barrier of 16 blocks, 2.4 of 64, 3.2 of 256; with every wavefront
-// in the poll 4.3 and 6.2).  All blocks run, so the wait ends; should one never
-// come, it ends after kExWaitTicks (2 s) with false.
-constexpr uint64_t kExWaitTicks = 200000000ull;   // of the 100 MHz wall clock
+// after it.  Returns in `any` whether some block brought `mine`.  The first
+// wavefront polls for its block (1.6 us a barrier of 16 blocks, 2.4 of 64, 3.2
+// of 256; with every wavefront in the poll 4.3 and 6.2).  All blocks run, so the
+// wait ends; should a flag never come, it ends with false (kSyncWaitPolls).
 __device__ __forceinline__ bool sweep_barrier(uint32_t *flag, int id, int nb, uint32_t epoch, bool mine, bool &any) {
   __shared__ int seen;   // bit 0: some block brought mine, bit 1: a wait ended without its flag
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wavefront's stores have reached the agent's memory
   const int b = __syncthreads_or(mine ? 1 : 0);
   if (threadIdx.x < 64) {
-    uint32_t *f = flag + (epoch & 1) * kExMaxBlocks;
-    if (threadIdx.x == 0)
-      __hip_atomic_store(f + id, (epoch << 1) | (b ? 1u : 0u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    bool a = false, ok = true;
-    for (int i = threadIdx.x; i < nb && ok; i += 64) {
-      uint32_t v = __hip_atomic_load(f + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if ((v >> 1) != epoch) {
-        const uint64_t t0 = wall_clock64();
-        do {
-          v = __hip_atomic_load(f + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          ok = wall_clock64() - t0 < kExWaitTicks;
-        } while ((v >> 1) != epoch && ok);
-      }
-      a = a || (v & 1u);
-    }
-    const bool some = __any(a), bad = __any(!ok);
-    if (threadIdx.x == 0) seen = (some ? 1 : 0) | (bad ? 2 : 0);
+    bool some;
+    const bool ok = sync_barrier(WaveSync(), flag, id, nb, epoch, b != 0, some);
+    if (threadIdx.x == 0) seen = (some ? 1 : 0) | (ok ? 0 : 2);
   }
   __syncthreads();
   const int r = seen;   // the next write to it comes after the next barrier's __syncthreads_or
@@ -399,9 +395,9 @@ __global__ __launch_bounds__(kItBlock) void ex_iterate_kernel(ExParams p) {
     const int C = p.list[j], c = (p.alpha[C] >= 0.5 ? 3 : 0) + d;
     put(C, c, agent_load(fin + (int64_t)C * kExRec + c));
   }
-  if (p.report && id == 0 && threadIdx.x == 0) {
-    p.report[0] = sweeps;
-    p.report[1] = ok ? 0 : 1;
+  if (p.report && threadIdx.x == 0) {
+    if (id == 0) p.report[0] = sweeps;
+    if (!ok) p.report[1] = 1;   // (any block's; reset by ex_init_kernel)
   }
 }
 
@@ -447,7 +443,7 @@ extern "C" vofpc_status vofpc_extrapolate(vofpc_ctx ctx, vofpc_mesh M, const dou
          *h = nullptr, *i = nullptr, *j = nullptr;
     vofpc_status st;
     if ((st = mesh_scratch_alloc(M, (size_t)N, &a)) || (st = mesh_scratch_alloc(M, 4 * (size_t)N, &b)) ||
-        (st = mesh_scratch_alloc(M, 32, &c)) || (st = mesh_scratch_alloc(M, kExFlags * sizeof(uint32_t), &d)) ||
+        (st = mesh_scratch_alloc(M, 32, &c)) || (st = mesh_scratch_alloc(M, kSyncWords * sizeof(uint32_t), &d)) ||
         (st = mesh_scratch_alloc(M, 4 * (size_t)N, &e)) || (st = mesh_scratch_alloc(M, 16 * sizeof(double) * (size_t)N, &f)) ||
         (st = mesh_scratch_alloc(M, 8 * (size_t)M->ncf, &g)) || (st = mesh_scratch_alloc(M, 8 * (size_t)N, &h)) ||
         (st = mesh_scratch_alloc(M, 4 * (size_t)M->ncf, &i)) || (st = mesh_scratch_alloc(M, 8 * (size_t)N, &j)))
@@ -458,7 +454,7 @@ extern "C" vofpc_status vofpc_extrapolate(vofpc_ctx ctx, vofpc_mesh M, const dou
     M->ex_buf = (double *)f;
   }
   const unsigned gN = (unsigned)((N + kExBlock - 1) / kExBlock);
-  ex_init_kernel<<<gN, kExBlock, 0, s>>>(N, alpha, o.eps_mixed, M->ex_mark, M->ex_info, M->ex_flag);
+  ex_init_kernel<<<gN, kExBlock, 0, s>>>(N, alpha, o.eps_mixed, M->ex_mark, M->ex_info, M->ex_flag, report);
   for (int l = 1; l <= o.layers; ++l)
     ring_grow_kernel<<<ring_face_blocks(NF), kRingBlock, 0, s>>>(M->d, M->ex_mark, l);
   const unsigned gL = ring_list_blocks(N);
@@ -498,7 +494,7 @@ extern "C" vofpc_status vofpc_extrapolate(vofpc_ctx ctx, vofpc_mesh M, const dou
       1, std::min<int64_t>((N + stencil_cells - 1) / stencil_cells, (int64_t)ctx->n_cu * 4));
   ex_stencil_kernel<<<gW, kExBlock, 0, s>>>(p);
   const unsigned gI = (unsigned)std::max<int64_t>(
-      1, std::min<int64_t>((N + kItCells - 1) / kItCells, std::min<int64_t>(ctx->n_cu, kExMaxBlocks)));
+      1, std::min<int64_t>((N + kItCells - 1) / kItCells, std::min<int64_t>(ctx->n_cu, kSyncMaxBlocks)));
   ex_iterate_kernel<<<gI, kItBlock, 0, s>>>(p);
   VOFPC_HIP(hipGetLastError());
   return VOFPC_OK;
