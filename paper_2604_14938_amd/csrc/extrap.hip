@@ -225,42 +225,6 @@ __device__ __forceinline__ void agent_store(double *a, double v) {
   __hip_atomic_store(a, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// The blocks that take part in the sweeps: those that run by the time the first
-// of them closes the list, which is when all nb have come, or kExGatherTicks
-// after its own start; a block that comes later ends at once.  Every block that
-// another one waits for is therefore running, whatever else the chip is doing
-// and however few of them found room: an ordinary launch cannot be left
-// waiting for blocks that are not resident.  (A cooperative launch promises
-// residency for 20 to 30 us more, and 200 us when several processes share the
-// device.)  Returns this block's number (-1: it comes too late) and their count
-// in nb.
-constexpr uint64_t kExGatherTicks = 5000;   // 50 us of the 100 MHz wall clock
-__device__ __forceinline__ int gather_blocks(uint32_t *flag, int &nb) {
-  __shared__ int id, count;
-  if (threadIdx.x == 0) {
-    uint32_t *came = flag + 2 * kSyncRow, *part = came + 1;
-    constexpr uint32_t kClosed = 0x80000000u;
-    const uint32_t k = __hip_atomic_fetch_add(came, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    int n = 0;
-    if (k == 0) {
-      const uint64_t t0 = wall_clock64();
-      while (__hip_atomic_load(came, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (uint32_t)nb &&
-             wall_clock64() - t0 < kExGatherTicks) {
-      }
-      n = (int)__hip_atomic_fetch_or(came, kClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(part, (uint32_t)n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    } else if (!(k & kClosed)) {   // the first block closes the list: a wait of kExGatherTicks at most
-      while ((n = (int)__hip_atomic_load(part, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0) {
-      }
-    }
-    id = n ? (int)k : -1;
-    count = n;
-  }
-  __syncthreads();
-  nb = count;
-  return id;
-}
-
 // The lanes of a wavefront and its agent-scope accesses for the flags.
 struct WaveSync {
   static constexpr int kLanes = 64;
@@ -271,26 +235,60 @@ struct WaveSync {
   __device__ __forceinline__ void store(uint32_t *a, uint32_t v) const {
     __hip_atomic_store(a, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
+  __device__ __forceinline__ uint32_t fetch_add(uint32_t *a, uint32_t v) const {
+    return __hip_atomic_fetch_add(a, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __device__ __forceinline__ uint32_t fetch_or(uint32_t *a, uint32_t v) const {
+    return __hip_atomic_fetch_or(a, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
   __device__ __forceinline__ bool any(bool b) const { return __any(b); }
+  __device__ __forceinline__ int first(int v) const { return __builtin_amdgcn_readfirstlane(v); }
 };
+
+// The blocks that take part in the sweeps (sweep_sync.h), of an ordinary launch:
+// a cooperative one promises residency for 20 to 30 us more, and 200 us when
+// several processes share the device.  This block's number, or -1; the sweeps
+// done before it takes part and the number of blocks then.
+__device__ __forceinline__ int sweep_enter(uint32_t *flag, int want, int &sweeps, int &nb) {
+  __shared__ int in[3];
+  if (threadIdx.x < 64) {
+    int e, n;
+    const int id = sync_enter(WaveSync(), flag, want, e, n);
+    if (threadIdx.x == 0) {
+      in[0] = id;
+      in[1] = e;
+      in[2] = n;
+    }
+  }
+  __syncthreads();
+  sweeps = in[1];
+  nb = in[2];
+  return in[0];
+}
 
 // Barrier over the nb blocks that take part (this one number id), epoch 1, 2,
 // ...: every agent-scope store made before it is seen by every agent-scope load
-// after it.  Returns in `any` whether some block brought `mine`.  The first
-// wavefront polls for its block (1.6 us a barrier of 16 blocks, 2.4 of 64, 3.2
-// of 256; with every wavefront in the poll 4.3 and 6.2).  All blocks run, so the
-// wait ends; should a flag never come, it ends with false (kSyncWaitPolls).
-__device__ __forceinline__ bool sweep_barrier(uint32_t *flag, int id, int nb, uint32_t epoch, bool mine, bool &any) {
-  __shared__ int seen;   // bit 0: some block brought mine, bit 1: a wait ended without its flag
+// after it.  Returns in `any` whether some block brought `mine`, and in `next`
+// the number of blocks of the next sweep.  The first wavefront polls for its
+// block (1.6 us a barrier of 16 blocks, 2.4 of 64, 3.2 of 256; with every
+// wavefront in the poll 4.3 and 6.2).  All blocks run, so the wait ends; should a
+// flag never come, it ends with false (kSyncWaitPolls).
+__device__ __forceinline__ bool sweep_barrier(uint32_t *flag, int id, int nb, int want, uint32_t epoch, bool mine,
+                                              bool &any, int &next) {
+  __shared__ int seen[2];   // bit 0: some block brought mine, bit 1: a wait ended without its flag; the next blocks
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wavefront's stores have reached the agent's memory
   const int b = __syncthreads_or(mine ? 1 : 0);
   if (threadIdx.x < 64) {
     bool some;
-    const bool ok = sync_barrier(WaveSync(), flag, id, nb, epoch, b != 0, some);
-    if (threadIdx.x == 0) seen = (some ? 1 : 0) | (ok ? 0 : 2);
+    const bool ok = sync_barrier(WaveSync(), flag, id, nb, want, epoch, b != 0, some);
+    if (threadIdx.x == 0) {
+      seen[0] = (some ? 1 : 0) | (ok ? 0 : 2);
+      seen[1] = nb;
+    }
   }
   __syncthreads();
-  const int r = seen;   // the next write to it comes after the next barrier's __syncthreads_or
+  const int r = seen[0];   // the next write to it comes after the next barrier's __syncthreads_or
+  next = seen[1];
   any = (r & 1) != 0;
   return (r & 2) == 0;
 }
@@ -306,20 +304,23 @@ __device__ __forceinline__ bool sweep_barrier(uint32_t *flag, int id, int nb, ui
 // start and is not touched.  After a sweep whose largest change is below tol,
 // or max_iter sweeps, the newest values go to the outputs.  Only as many blocks
 // as the domain fills take part: a sweep over 16,000 cells is bound by the
-// round trips of the gathers and of its barrier.
+// round trips of the gathers and of its barrier.  A block's first cells depend
+// on its number alone; its further cells on how many blocks sweep, which grows
+// when blocks come late, so those are read from memory at every sweep.
 constexpr int kItBlock = 1024, kItLanes = 4, kItCells = kItBlock / kItLanes, kItSlots = 10;
 __global__ __launch_bounds__(kItBlock) void ex_iterate_kernel(ExParams p) {
   const int64_t N = p.m.n_cells, nd = p.info[1];
-  int nb = (int)std::min<int64_t>(gridDim.x, std::max<int64_t>(1, (nd + kItCells - 1) / kItCells));
-  int id = (int)blockIdx.x;
-  if (id >= nb) return;
+  const int want = (int)std::min<int64_t>(gridDim.x, std::max<int64_t>(1, (nd + kItCells - 1) / kItCells));
+  int id = (int)blockIdx.x, nb = want, sweeps = 0;
+  if (id >= want) return;
   if (p.max_iter > 1) {   // (a single sweep has no barrier)
-    id = gather_blocks(p.flag, nb);
+    id = sweep_enter(p.flag, want, sweeps, nb);
     if (id < 0) return;
   }
   const int d = threadIdx.x % kItLanes;
   const bool comp = d < 3;
-  const int64_t j0 = (int64_t)id * kItCells + threadIdx.x / kItLanes, stride = (int64_t)nb * kItCells;
+  const int64_t j0 = (int64_t)id * kItCells + threadIdx.x / kItLanes;
+  int64_t stride = (int64_t)nb * kItCells;
   // the group's first cell: word `at` of its record (its advanced component
   // d) with its value, and the neighbours and weights of its first slots
   int P = 0, at = 0, cnt = 0, first = 0, nbr[kItSlots];
@@ -332,14 +333,14 @@ __global__ __launch_bounds__(kItBlock) void ex_iterate_kernel(ExParams p) {
     first = ur.x;
     cnt = ur.y;
     th = p.theta[j0];
-    v = p.buf[(int64_t)P * kExRec + at];
+    v = agent_load(p.buf + (int64_t)(sweeps & 1) * kExRec * N + (int64_t)P * kExRec + at);
   }
 #pragma unroll
   for (int k = 0; k < kItSlots; ++k) {
     w[k] = k < cnt ? p.wup[first + k] : 0.0;
     nbr[k] = k < cnt ? p.upn[first + k] : 0;
   }
-  int sweeps = 0;
+  int in = nb;   // blocks let in, as the leader knows it
   bool ok = true;
   while (sweeps < p.max_iter) {
     const double *cur = p.buf + (int64_t)(sweeps & 1) * kExRec * N;
@@ -374,9 +375,12 @@ __global__ __launch_bounds__(kItBlock) void ex_iterate_kernel(ExParams p) {
     ++sweeps;
     if (sweeps == p.max_iter) break;   // (each group reads back its own cells alone)
     bool more;
-    ok = sweep_barrier(p.flag, id, nb, (uint32_t)sweeps, !(change < p.tol), more);
+    ok = sweep_barrier(p.flag, id, nb, want, (uint32_t)sweeps, !(change < p.tol), more, in);
     if (!ok || !more) break;
+    nb = in;
+    stride = (int64_t)nb * kItCells;
   }
+  if (id == 0 && in < want && threadIdx.x < 64) sync_close(WaveSync(), p.flag, in);
   // outputs: the advanced field from the newest iterate, the kept one from the
   // gradient both started from (in gl)
   const double *fin = p.buf + (int64_t)(sweeps & 1) * kExRec * N;
@@ -487,8 +491,7 @@ extern "C" vofpc_status vofpc_extrapolate(vofpc_ctx ctx, vofpc_mesh M, const dou
   p.gv = gradT_v;
   p.report = report;
   // the stencil: 32 domain cells per block, four blocks per CU; the sweeps: a
-  // block per CU at most (they must all be resident), fewer for a mesh that
-  // cannot fill them
+  // block per CU at most, fewer for a mesh that cannot fill them
   const int64_t stencil_cells = kExBlock / kExLanes;
   const unsigned gW = (unsigned)std::max<int64_t>(
       1, std::min<int64_t>((N + stencil_cells - 1) / stencil_cells, (int64_t)ctx->n_cu * 4));

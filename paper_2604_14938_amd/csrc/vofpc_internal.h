@@ -200,7 +200,7 @@ struct vofpc_mesh_s {
   int8_t *ex_mark = nullptr;       // layer of each cell in the domain (-1 outside)
   int32_t *ex_list = nullptr;      // domain cells (any order)
   int32_t *ex_info = nullptr;      // [1] domain size
-  uint32_t *ex_flag = nullptr;     // sweep barrier: [2][blocks] each block's sweep number and verdict; blocks that take part
+  uint32_t *ex_flag = nullptr;     // the sweep kernel's flags between its blocks (sweep_sync.h)
   int32_t *ex_entry = nullptr;     // mixed entry of the cells with an interface (marked in ex_mark)
   double *ex_buf = nullptr;        // [2][n_cells][8]: G_l and G_v per cell, two iterates
   double *ex_wup = nullptr;        // per cell-face slot: normalised upwind weight

@@ -1,6 +1,7 @@
 """The flags by which the extrapolation's blocks step through the sweeps, with
-host threads for blocks: a flag that arrives with the last poll counts, all
-blocks get the same verdict, and a wait for a missing block ends."""
+host threads for blocks: a flag that arrives with the last poll counts, a wait
+for a missing block ends, and blocks that come late take part from the next
+sweep, or end when the sweeps are over."""
 import os
 import subprocess
 
