@@ -493,78 +493,129 @@ __device__ __forceinline__ void cell_features(TM &M, int sl, int q, const ReconP
     M.net.x[sl][i] = net::from_bf16(net::to_bf16(net::feature(i, a, sorted, nv, lsum, pmin, Wd, ns, amin, amax, nf)));
 }
 
-// kB hidden units of one layer for a cell shared by W lanes: unit W (j0 + b)
-// + l for slot b of lane l, its BF16 weights against the cell's LDS row, FP32
-// FMAs in input order.
-template <int W, int KIN, int kB>
-__device__ __forceinline__ void net_units(const uint16_t *wts, const float *x, int l, int j0, float (&z)[kB]) {
+// ------------------------------------------------------------- the network
+// Output 0 of the network for the cells of a wavefront, every sum in the order
+// of the wavefront kernel's row_forward, so all flavours predict the same bits.
+// The products go through the FP32 matrix instructions of one step (K = 1): each
+// result is one fused multiply-add a step, as the chain of v_fma_f32 that
+// row_forward runs (BF16 weights and activations are exact in FP32; compared
+// over ordinary, wide, denormal and cancelling operands: no bit differs).
+// Lane l holds the weights of unit l as operand A, so a wavefront reads the
+// weights once for all its cells and unpacks each once.  With the units dealt to
+// a cell's lanes and the products on the vector ALU a step over 113,584 cells took
+// 777 us, now 673; one over 366,598 cells 2,141 us, now 1,905 (the class
+// kernels alone: 151,485 hexahedra 419, now 303; 214,287 Voronoi cells 1,392, now
+// 1,278).
+
+// the two BF16 values of a word
+__device__ __forceinline__ float bf16_low(uint32_t w) { return __uint_as_float(w << 16); }
+__device__ __forceinline__ float bf16_high(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
+
+// z += W x over one layer of K inputs: w the weights of unit `lane`, x the row
+// of this lane's column (4 or 16 cells); step(a, b, z) one matrix instruction
+template <int K, class Acc, class Step>
+__device__ __forceinline__ void net_layer(const uint16_t *wts, const float *x, int lane, Acc &z, Step step) {
+  const uint4 *w = reinterpret_cast<const uint4 *>(wts + lane * K);
+  uint4 r[K / 8];
 #pragma unroll
-  for (int b = 0; b < kB; ++b) z[b] = 0.f;
-  // (with four units a lane four rounds' weights in flight: 113,584 cells with
-  // the network 725 us a step, 748 with two rounds, 747 with eight; one unit
-  // a lane: two, 115 us for 119 on 2,832 cells)
-#pragma unroll(kB > 1 ? 4 : 2)
-  for (int i = 0; i < KIN / 8; ++i) {
+  for (int i = 0; i < K / 8; ++i) r[i] = w[i];
+#pragma unroll
+  for (int i = 0; i < K / 8; ++i) {
     const float4 xa = *reinterpret_cast<const float4 *>(x + 8 * i), xb = *reinterpret_cast<const float4 *>(x + 8 * i + 4);
-    const float xv[8] = {xa.x, xa.y, xa.z, xa.w, xb.x, xb.y, xb.z, xb.w};
-#pragma unroll
-    for (int b = 0; b < kB; ++b) {
-      const uint4 w = *reinterpret_cast<const uint4 *>(wts + (int64_t)((j0 + b) * W + l) * KIN + 8 * i);
-      const uint32_t wv[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-      for (int h = 0; h < 4; ++h) {
-        z[b] = __builtin_fmaf(__uint_as_float(wv[h] << 16), xv[2 * h], z[b]);
-        z[b] = __builtin_fmaf(__uint_as_float(wv[h] & 0xffff0000u), xv[2 * h + 1], z[b]);
-      }
-    }
+    step(bf16_low(r[i].x), xa.x, z);
+    step(bf16_high(r[i].x), xa.y, z);
+    step(bf16_low(r[i].y), xa.z, z);
+    step(bf16_high(r[i].y), xa.w, z);
+    step(bf16_low(r[i].z), xb.x, z);
+    step(bf16_high(r[i].z), xb.y, z);
+    step(bf16_low(r[i].w), xb.z, z);
+    step(bf16_high(r[i].w), xb.w, z);
   }
 }
+__device__ __forceinline__ float net_act(float z) { return net::from_bf16(net::to_bf16(net::act_tanh(z))); }
 
-// Forward pass of one cell by the W lanes that share it (4, 16 or the whole
-// wavefront; l: the lane among them; x, h: the cell's rows): the arithmetic of
-// the wavefront kernel's row_forward, unit by unit and in its summation
-// order, so both predict the same bits.  Returns output 0.
-template <int W>
-__device__ __forceinline__ float net_forward(const float *x, float *hrow, int l, const uint16_t *wb,
+// sum over the four units 4i .. 4i + 3 of the third layer's terms
+__device__ __forceinline__ float net_quad(const uint16_t *wb, const float *master, int u, const float (&z)[4]) {
+  using namespace net;
+  const f32x4 b = *reinterpret_cast<const f32x4 *>(master + oB2 + u);
+  const uint2 w = *reinterpret_cast<const uint2 *>(wb + oW3 + u);
+  return (bf16_low(w.x) * net_act(z[0] + b[0]) + bf16_high(w.x) * net_act(z[1] + b[1])) +
+         (bf16_low(w.y) * net_act(z[2] + b[2]) + bf16_high(w.y) * net_act(z[3] + b[3]));
+}
+
+// Four cells, v_mfma_f32_4x4x1_16b_f32: lane l has cell l % 4 (its rows x and
+// h) and, as results, the units 4 (l / 4) + j, j = 0 .. 3.
+__device__ __forceinline__ float net_four(const float *x, float *h, int lane, const uint16_t *wb, const float *master) {
+  using namespace net;
+  auto step = [](float a, float b, f32x4 &z) { z = __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, z, 0, 0, 0); };
+  const int u = lane & ~3;
+  f32x4 z = {0.f, 0.f, 0.f, 0.f};
+  net_layer<kIn>(wb + oW1, x, lane, z, step);
+  const f32x4 b1 = *reinterpret_cast<const f32x4 *>(master + oB1 + u);
+  f32x4 a;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) a[j] = net_act(z[j] + b1[j]);
+  *reinterpret_cast<f32x4 *>(h + u) = a;
+  wave_sync();
+  z = f32x4{0.f, 0.f, 0.f, 0.f};
+  net_layer<kHid>(wb + oW2, h, lane, z, step);
+  const float zq[4] = {z[0], z[1], z[2], z[3]};
+  // the quads of units are 4 lanes apart: sums over lanes l ^ 4, l ^ 8 (two
+  // mirrors each), and the rows of 16 lanes
+  auto mirror = [](float v, auto ctrl) {
+    return __builtin_bit_cast(float, dpp_i<decltype(ctrl)::value>(__builtin_bit_cast(int, v)));
+  };
+  std::integral_constant<int, kHalfMirror> half;
+  std::integral_constant<int, kRowMirror> whole;
+  std::integral_constant<int, 0x1B> quad;   // lanes 3, 2, 1, 0 of each quad
+  float v = net_quad(wb, master, u, zq);
+  v += mirror(mirror(v, half), quad);
+  v += mirror(mirror(v, whole), half);
+  return cross_sum_f<32>(cross_sum_f<16>(v)) + master[oB3];
+}
+
+// Sixteen cells, v_mfma_f32_16x16x1_4b_f32: lane l has cell l % 16 and the units
+// 16 b + 4 (l / 16) + j.
+__device__ __forceinline__ float net_sixteen(const float *x, float *h, int lane, const uint16_t *wb,
                                              const float *master) {
   using namespace net;
-  static_assert(W == 4 || W == 16 || W == 64, "a quad, a row or a wavefront per cell");
-  constexpr int KU = kHid / W, kB = KU < 4 ? KU : 4;
-#pragma unroll 1
-  for (int j0 = 0; j0 < KU; j0 += kB) {
-    float z[kB];
-    net_units<W, kIn, kB>(wb + oW1, x, l, j0, z);
+  typedef float f32x16 __attribute__((ext_vector_type(16)));
+  auto step = [](float a, float b, f32x16 &z) { z = __builtin_amdgcn_mfma_f32_16x16x1f32(a, b, z, 0, 0, 0); };
+  const int u = 4 * (lane >> 4);
+  f32x16 z = 0.f;
+  net_layer<kIn>(wb + oW1, x, lane, z, step);
 #pragma unroll
-    for (int b = 0; b < kB; ++b) {
-      const int u = (j0 + b) * W + l;
-      hrow[u] = from_bf16(to_bf16(act_tanh(z[b] + master[oB1 + u])));
-    }
+  for (int b = 0; b < 4; ++b) {
+    const f32x4 b1 = *reinterpret_cast<const f32x4 *>(master + oB1 + 16 * b + u);
+    f32x4 a;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) a[j] = net_act(z[4 * b + j] + b1[j]);
+    *reinterpret_cast<f32x4 *>(h + 16 * b + u) = a;
   }
   wave_sync();
-  float row[4] = {0.f, 0.f, 0.f, 0.f};   // sums over the rows of 16 units
-#pragma unroll 1
-  for (int j0 = 0; j0 < KU; j0 += kB) {
-    float z[kB], o[kB];
-    net_units<W, kHid, kB>(wb + oW2, hrow, l, j0, z);
+  z = 0.f;
+  net_layer<kHid>(wb + oW2, h, lane, z, step);
+  float row[4];
 #pragma unroll
-    for (int b = 0; b < kB; ++b) {
-      const int u = (j0 + b) * W + l;
-      o[b] = from_bf16(wb[oW3 + u]) * from_bf16(to_bf16(act_tanh(z[b] + master[oB2 + u])));
-    }
-    if constexpr (W == 64) {          // row r of the wavefront holds row r
-      return wave_sum_f(o[0]) + master[oB3];
-    } else if constexpr (W == 16) {   // a block is every unit, slot b row b
-#pragma unroll
-      for (int b = 0; b < kB; ++b) row[b] = row_sum_f(o[b]);
-    } else {                          // a block is one row of 16 units
-#pragma unroll
-      for (int b = 0; b < kB; ++b) o[b] = quad_sum_f(o[b]);
-      const float s = (o[0] + o[1]) + (o[2] + o[3]);
-#pragma unroll
-      for (int b = 0; b < 4; ++b) row[b] = b * kB == j0 ? s : row[b];
-    }
+  for (int b = 0; b < 4; ++b) {
+    const float zq[4] = {z[4 * b], z[4 * b + 1], z[4 * b + 2], z[4 * b + 3]};
+    row[b] = cross_sum_f<32>(cross_sum_f<16>(net_quad(wb, master, 16 * b + u, zq)));
   }
   return ((row[0] + row[1]) + (row[2] + row[3])) + master[oB3];
+}
+
+// One cell, one unit a lane: the vector ALU (a matrix instruction has four cells
+// at least).
+__device__ __forceinline__ float net_one(const float *x, float *h, int lane, const uint16_t *wb, const float *master) {
+  using namespace net;
+  auto step = [](float a, float b, float &z) { z = __builtin_fmaf(a, b, z); };
+  float z = 0.f;
+  net_layer<kIn>(wb + oW1, x, lane, z, step);
+  h[lane] = net_act(z + master[oB1 + lane]);
+  wave_sync();
+  z = 0.f;
+  net_layer<kHid>(wb + oW2, h, lane, z, step);
+  return wave_sum_f(from_bf16(wb[oW3 + lane]) * net_act(z + master[oB2 + lane])) + master[oB3];
 }
 
 // Largest cell of a build (vertices, faces, loop positions, edges), its
@@ -705,17 +756,25 @@ __device__ __forceinline__ void solve_cells(const ReconParams &p, typename Caps:
   bool hint = false;
   if constexpr (NET) {
     double nlo = __builtin_nan(""), nhi = __builtin_nan("");   // none where the network does not run
-    if (active && have_field && st == VOFPC_CELL_OK) {         // degenerate fields skip the network
-      const double Wd = pmax - pmin;
-      cell_features<G, KF, KV>(M, sl, q, p, P, a, nv, nf, f0, pmin, Wd);
-      wave_sync();
-      float u;
-      if (cw == 1)
-        u = net_forward<64>(M.net.x[0], M.net.h[0], lane, p.net_wb, p.net_master);
-      else if (G == 4 && ts == 1)
-        u = net_forward<4>(M.net.x[sl], M.net.h[sl], q, p.net_wb, p.net_master);
-      else
-        u = net_forward<16>(M.net.x[lead], M.net.h[lead], lane & 15, p.net_wb, p.net_master);
+    const bool row = active && have_field && st == VOFPC_CELL_OK;   // degenerate fields skip the network
+    const double Wd = pmax - pmin;
+    if (row) cell_features<G, KF, KV>(M, sl, q, p, P, a, nv, nf, f0, pmin, Wd);
+    wave_sync();
+    // all lanes: the cells of a tile are its columns, each by itself, and those
+    // without a row are not used
+    float u = 0.f;
+    if (__any(row)) {
+      if (cw == 1) {
+        u = net_one(M.net.x[0], M.net.h[0], lane, p.net_wb, p.net_master);
+      } else if (cw == 4) {
+        const int at = (lane & 3) * ts;
+        u = __shfl(net_four(M.net.x[at], M.net.h[at], lane, p.net_wb, p.net_master), lead / ts);
+      } else {
+        if constexpr (C == 16)
+          u = __shfl(net_sixteen(M.net.x[lane & 15], M.net.h[lane & 15], lane, p.net_wb, p.net_master), sl);
+      }
+    }
+    if (row) {
       if (!isnan(u)) {
         const double uc = u < 0.f ? 0.0 : (u > 1.f ? 1.0 : (double)u);
         const double sh = pmin + uc * Wd, dl = p.net_delta * Wd;

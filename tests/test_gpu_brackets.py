@@ -121,3 +121,39 @@ def test_brackets_that_end_at_the_isovalue(V, kind):  # noqa: F811
             assert wrong.size == 0, (name, m, wrong.size, idx[wrong[:4]], g["status"][wrong[:4]], want[wrong[:4]])
             np.testing.assert_allclose(g["alpha_got"][ok], a[ok], rtol=0, atol=1e-12)
     run.close()
+
+
+@pytest.mark.parametrize("kind,tune", [("hex", None), ("voronoi", None), ("voronoi", (12, 3, 26, 3))])
+def test_the_network_predicts_the_same_bits(V, kind, tune):  # noqa: F811
+    """The brackets of one, four and sixteen cells per wavefront against those
+    of the wavefront kernel, bit for bit."""
+    import torch
+    from paper_2604_14938_amd import runner, train
+    wl, _ = _case(kind)
+    params, scale, _ = train.load()
+    run = runner.PathRun(wl, ctx=V.Context(0, stream=torch.cuda.Stream()))
+    mlp = V.Mlp(run.ctx)
+    mlp.set_params(params)
+    run.step()
+    full = run.results()
+    b, M = run.buf, full["n_mixed"]
+
+    def brackets(m):
+        lo, hi = (torch.zeros(M, dtype=torch.float64, device=run.dev) for _ in range(2))
+        cnt = torch.tensor([m, full["n_band"]], dtype=torch.int32, device=run.dev)
+        torch.cuda.synchronize()
+        V.reconstruct_learned(run.ctx, run.mesh, run.alpha, b.mixed_idx, cnt, b.itf, mlp, scale, None, lo, hi)
+        torch.cuda.synchronize()
+        return lo[:m].cpu().numpy(), hi[:m].cpu().numpy()
+
+    group = run.mesh.classes()["tune"] if tune is None else list(tune)
+    run.mesh.set_tune([3, 3, 3, 3])
+    ref = brackets(M)
+    assert np.isfinite(ref[0]).mean() > 0.99
+    run.mesh.set_tune(group)
+    for m in (M, 5000, 3000, 900, 17, 1):
+        print(f"[gpu-case] network bits {kind} {tune}: {m} of {M} cells", flush=True)
+        for g, r in zip(brackets(m), ref):
+            np.testing.assert_array_equal(g, r[:m])
+    run.close()
+    mlp.close()
