@@ -488,7 +488,8 @@ __device__ __forceinline__ void cell_features(TM &M, int sl, int q, const ReconP
     if (q + k * G < nv) M.net.rank[r[k]][sl] = (uint8_t)(q + k * G);
   const double lsum = items_sum<G>(v);
   wave_sync();
-  auto sorted = [&](int i) { return M.phi[M.net.rank[i][sl]][sl]; };
+  // (ranks of values that are not numbers are not all written)
+  auto sorted = [&](int i) { return M.phi[min((int)M.net.rank[i][sl], nv - 1)][sl]; };
   for (int i = q; i < net::kIn; i += G)
     M.net.x[sl][i] = net::from_bf16(net::to_bf16(net::feature(i, a, sorted, nv, lsum, pmin, Wd, ns, amin, amax, nf)));
 }

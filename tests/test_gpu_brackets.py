@@ -157,3 +157,37 @@ def test_the_network_predicts_the_same_bits(V, kind, tune):  # noqa: F811
             np.testing.assert_array_equal(g, r[:m])
     run.close()
     mlp.close()
+
+
+@pytest.mark.parametrize("kind", ["hex", "voronoi"])
+def test_the_network_beside_fractions_that_are_no_numbers(V, kind):  # noqa: F811
+    """Cells next to a NaN fraction get no usable inputs and are searched as
+    without the network; the others do not notice."""
+    import dataclasses
+
+    import torch
+    from paper_2604_14938_amd import runner, train
+    base, _ = _case(kind)
+    alpha = base.alpha.copy()
+    mixed = np.nonzero((alpha > 1e-8) & (alpha < 1 - 1e-8))[0]
+    alpha[mixed[::101]] = np.nan
+    wl = dataclasses.replace(base, alpha=alpha)
+    params, scale, _ = train.load()
+    run = runner.PathRun(wl, ctx=V.Context(0, stream=torch.cuda.Stream()))
+    mlp = V.Mlp(run.ctx)
+    mlp.set_params(params)
+    run.step()
+    full = run.results()
+    b = run.buf
+    for m in (full["n_mixed"], 900):
+        print(f"[gpu-case] NaN fractions {kind}: {m} cells", flush=True)
+        cnt = torch.tensor([m, full["n_band"]], dtype=torch.int32, device=run.dev)
+        torch.cuda.synchronize()
+        V.reconstruct(run.ctx, run.mesh, run.alpha, b.mixed_idx, cnt, b.itf)
+        plain = _first(run.results(), m)["status"]
+        V.reconstruct_learned(run.ctx, run.mesh, run.alpha, b.mixed_idx, cnt, b.itf, mlp, scale)
+        st = _first(run.results(), m)["status"]
+        st = np.where((st == V.CELL_LEARNED_FALLBACK) & (plain == V.CELL_OK), plain, st)
+        np.testing.assert_array_equal(st, plain)
+    run.close()
+    mlp.close()
