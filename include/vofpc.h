@@ -304,9 +304,9 @@ vofpc_status vofpc_reconstruct_learned(vofpc_ctx ctx, vofpc_mesh mesh, const dou
  * than one flavour (see vofpc_mesh_set_tune: lanes per cell and register
  * budget), time every flavour on the mixed cells of `alpha` (DEVICE
  * [n_cells]; opts may be NULL) and keep the fastest in the mesh.
- * cache_path (optional, a text file): a line for the same device, CU count,
- * mesh sizes, class counts and options is used without timing
- * (*from_cache = 1); otherwise the choice is appended.  choice: optional
+ * cache_path (optional, a text file): a line for the same device, kernel
+ * revision, CU count, mesh sizes, class counts and options is used without
+ * timing (*from_cache = 1); otherwise the choice is appended.  choice: optional
  * HOST int32[4] receiving the flavour per class.  On error the mesh keeps
  * the flavours it had.  Allocates trial buffers and synchronises the context
  * stream (a set-up call, not for capture). */

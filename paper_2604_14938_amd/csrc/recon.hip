@@ -1461,6 +1461,10 @@ int candidates(vofpc_mesh M, int c, int out[8]) {
   return n;
 }
 
+// Revision of the reconstruction kernels in the cache's lines: raised when a
+// change may move the fastest flavour, so lines timed with others are ignored.
+constexpr int kTuneRevision = 2;
+
 std::string tune_key(vofpc_ctx ctx, vofpc_mesh M, const vofpc_recon_opts &o) {
   hipDeviceProp_t prop;
   std::string arch = "gpu";
@@ -1468,8 +1472,8 @@ std::string tune_key(vofpc_ctx ctx, vofpc_mesh M, const vofpc_recon_opts &o) {
   for (char &ch : arch)
     if (ch == ' ' || ch == ':') ch = '_';
   char buf[384];
-  snprintf(buf, sizeof buf, "%s cu%d n%lld f%lld v%lld c%lld,%lld,%lld,%lld o%d,%d,%d,%d,%.3g", arch.c_str(),
-           ctx->n_cu, (long long)M->d.n_cells, (long long)M->d.n_faces, (long long)M->d.n_verts,
+  snprintf(buf, sizeof buf, "%s r%d cu%d n%lld f%lld v%lld c%lld,%lld,%lld,%lld o%d,%d,%d,%d,%.3g", arch.c_str(),
+           kTuneRevision, ctx->n_cu, (long long)M->d.n_cells, (long long)M->d.n_faces, (long long)M->d.n_verts,
            (long long)M->class_cells[0], (long long)M->class_cells[1], (long long)M->class_cells[2],
            (long long)M->class_cells[3], o.vertex_mode, o.fixed_iso, o.bracket, o.max_iter, o.tol_rel);
   return buf;
