@@ -99,14 +99,6 @@ __device__ __forceinline__ double tsum(double v) {
   return v;
 }
 template <int G>
-__device__ __forceinline__ int tsum_i(int v) {
-  if constexpr (G >= 2) v += dpp_i<kQuadXor1>(v);
-  if constexpr (G >= 4) v += dpp_i<kQuadXor2>(v);
-  if constexpr (G >= 8) v += dpp_i<kHalfMirror>(v);
-  if constexpr (G >= 16) v += dpp_i<kRowMirror>(v);
-  return v;
-}
-template <int G>
 __device__ __forceinline__ int tmin_i(int v) {
   if constexpr (G >= 2) v = min(v, dpp_i<kQuadXor1>(v));
   if constexpr (G >= 4) v = min(v, dpp_i<kQuadXor2>(v));
@@ -198,18 +190,6 @@ __device__ __forceinline__ double items_sum(const double (&v)[K]) {
   }
   return a;
 }
-__device__ __forceinline__ float quad_sum_f(float v) {
-  v += __builtin_bit_cast(float, dpp_i<kQuadXor1>(__builtin_bit_cast(int, v)));
-  v += __builtin_bit_cast(float, dpp_i<kQuadXor2>(__builtin_bit_cast(int, v)));
-  return v;
-}
-__device__ __forceinline__ float row_sum_f(float v) {
-  v = quad_sum_f(v);
-  v += __builtin_bit_cast(float, dpp_i<kHalfMirror>(__builtin_bit_cast(int, v)));
-  v += __builtin_bit_cast(float, dpp_i<kRowMirror>(__builtin_bit_cast(int, v)));
-  return v;
-}
-
 // The group's bits of a wavefront ballot, the group's first lane in bit 0.
 template <int G>
 __device__ __forceinline__ uint32_t group_bits(bool b, int base) {
