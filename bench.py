@@ -12,9 +12,9 @@ pair alone, the pipe alone and the multi-instance time-step batch.
 
 Both forms are timed on the same inputs: plain (search from the cell's full
 vertex-value range) and learned (the bracket network inside the
-reconstruction kernel gives the first guess, checked with a cut at each
-end).  The headline value is the learned form when trained weights are
-present, else the plain one.
+reconstruction kernel gives the first guess and a bracket around it).  The
+headline value is the learned form when trained weights are present, else the
+plain one.
 
 Prints one JSON line: the metric and its value (mixed cells per second of
 the headline form), the step time, `config` (the workload, both forms'
@@ -118,6 +118,14 @@ def cell_classes(mesh, cells: np.ndarray, hex0: bool | None = None) -> np.ndarra
     if hex0:
         out[(out == 0) & ~hexfit] = 1
     return out
+
+
+def kernel_classes(cls: dict, class_ms, kc: int) -> list:
+    """The classes whose cells the kernel of class `kc` runs: its own and, for
+    the usual Voronoi class, those that have cells but no kernel of their own
+    (negative times): they ride in its launch."""
+    riders = [c for c in range(len(class_ms)) if cls["cells"][c] > 0 and class_ms[c] < 0]
+    return sorted([kc] + (riders if kc == 1 and cls["bucketed"] else []))
 
 
 def recon_bytes(mesh, mixed: np.ndarray, learned: bool = False) -> int:
@@ -525,17 +533,14 @@ def main() -> int:
         # (the timed step runs them side by side)
         run.ctx.overlap_classes(False)
         run.ctx.time_classes(True)
+        # (-1: no kernel of its own)
         cls_ms = np.zeros(4)
-        pass_ms = np.zeros(4)
         for _ in range(reps):
             rec()
-            km, pm = run.ctx.class_ms()
-            cls_ms += np.array(km)
-            pass_ms += np.array(pm)
+            cls_ms += np.array(run.ctx.class_ms()[0])
         run.ctx.time_classes(False)
         run.ctx.overlap_classes(True)
         res["class_ms"] = (cls_ms / reps).tolist()
-        res["pass_ms"] = (pass_ms / reps).tolist()
         res["tune"] = tune if tune is not None else res["classes"]["tune"]
         run.close()
         return res, ms, statistics.median(per), wall, recon_ms
@@ -552,8 +557,7 @@ def main() -> int:
         mlp.set_params(params)
         learned, ms_l, med_l, wall_l, rms_l = time_form(mlp, dscale)
         log(f"learned step: {ms_l * 1e3:.1f} us mean, {med_l * 1e3:.1f} us median (wall {wall_l:.3f} s); "
-            f"reconstruction {rms_l * 1e3:.1f} us, class kernels {learned['class_ms']} ms, bracket passes "
-            f"{learned['pass_ms']} ms")
+            f"reconstruction {rms_l * 1e3:.1f} us, class kernels {learned['class_ms']} ms")
     two = follow_on(args, wl, parts, runner, V, torch) if args.workload == "voronoi_bubble" else None
     if plain is None and learned is None:
         print(json.dumps({"error": "no trained weights for the learned form"}))
@@ -570,21 +574,17 @@ def main() -> int:
     cls = head["classes"]
     cms = np.array(head["class_ms"])
     kc = int(np.argmax(cms))
+    kcls = kernel_classes(cls, cms, kc)
     if cls["bucketed"]:
-        kcells = mixed[cell_classes(wl.mesh, mixed) == kc]
+        kcells = mixed[np.isin(cell_classes(wl.mesh, mixed), kcls)]
     else:
         kcells = mixed
     k_ms = float(cms[kc])
-    kp_ms = float(head["pass_ms"][kc])
-    # the learned class kernel reads its brackets (16 bytes per cell) when a
-    # bracket pass made them, else its network's inputs
-    rb_k = recon_bytes(wl.mesh, kcells, learned=form == "learned" and kp_ms < 0)
-    if form == "learned" and kp_ms >= 0:
-        rb_k += 16 * len(kcells)
+    rb_k = recon_bytes(wl.mesh, kcells, learned=form == "learned")
     rf_k = recon_flops(wl.mesh, kcells)
     tflops = rf_k / (k_ms * 1e-3) / 1e12
     achieved = rb_k / (k_ms * 1e-3) / 1e9
-    log(f"{form} dominant reconstruction kernel (class {kc}, flavour {head['tune'][kc]}): {k_ms * 1e3:.1f} us over "
+    log(f"{form} dominant reconstruction kernel (classes {kcls}, flavour {head['tune'][kc]}): {k_ms * 1e3:.1f} us over "
         f"{len(kcells)} cells, {rf_k / 1e6:.1f} MFLOP and {rb_k / 1e6:.2f} MB algorithmic -> {tflops:.3f} TFLOP/s, "
         f"{achieved:.1f} GB/s")
     rb = recon_bytes(wl.mesh, mixed, learned=form == "learned")
@@ -596,6 +596,10 @@ def main() -> int:
         n = max(len(st), 1)
         return {name: float(np.count_nonzero(st == i)) / n for i, name in enumerate(STATUS_NAMES)
                 if i != V.CELL_NOT_MIXED}
+
+    def class_us(r):
+        """Each class kernel's time, None for a class without one of its own."""
+        return [x * 1e3 if x >= 0 else None for x in r["class_ms"]]
 
     cfg = {
         "workload": wl_desc,
@@ -618,7 +622,7 @@ def main() -> int:
         cfg["follow_on"] = two
     if plain is not None:
         cfg["plain"] = {"cells_per_s": plain["mixed_per_step"] / (ms_p * 1e-3), "ms_per_step": ms_p,
-                        "recon_us": rms_p * 1e3, "class_kernel_us": [x * 1e3 for x in plain["class_ms"]],
+                        "recon_us": rms_p * 1e3, "class_kernel_us": class_us(plain),
                         "kernel_flavours": plain["tune"],
                         "evals_per_cell_mean": float(plain["iters"].mean()),
                         "evals_per_cell_p99": float(np.percentile(plain["iters"], 99)),
@@ -626,8 +630,7 @@ def main() -> int:
     if learned is not None:
         cfg["learned"] = {
             "cells_per_s": learned["mixed_per_step"] / (ms_l * 1e-3), "ms_per_step": ms_l, "recon_us": rms_l * 1e3,
-            "class_kernel_us": [x * 1e3 for x in learned["class_ms"]],
-            "bracket_pass_us": [x * 1e3 for x in learned["pass_ms"]],
+            "class_kernel_us": class_us(learned),
             "kernel_flavours": learned["tune"],
             "evals_per_cell_mean": float(learned["iters"].mean()),
             "evals_per_cell_p99": float(np.percentile(learned["iters"], 99)),
@@ -672,7 +675,7 @@ def main() -> int:
             "frac": tflops / FP64_PEAK_TFLOPS,
             "traffic": measured_traffic(args.workload, form, kc),
             "kernel_us": k_ms * 1e3,
-            "bracket_pass_us": kp_ms * 1e3 if kp_ms >= 0 else None,
+            "classes": kcls,
             "cells": int(len(kcells)),
             "algorithmic_flops": rf_k,
             "algorithmic_bytes": rb_k,
@@ -687,7 +690,7 @@ def main() -> int:
 
 
 def extrap_sweep_bytes(mesh, dom, us) -> dict:
-    """Algorithmic bytes of one busy extrapolation sweep over the domain
+    """Algorithmic bytes of one extrapolation sweep over the domain
     cells `dom` (boolean per cell): per domain cell its list entry (4), its
     packed-stencil range (8), theta (8), its advanced components read (24)
     and written (24), and its record as a neighbour (24); per upwind face
@@ -758,12 +761,11 @@ def follow_on(args, wl, parts, runner, V, torch) -> dict:
         log(f"two-sided mass transfer, {name}: eager {tsm[name]['us_eager']:.1f} us, graph replay "
             f"{tsm[name]['us_graph_replay']:.1f} us ({tsm['sweeps']} sweeps over {dom} cells)")
         del graph
-    # the sweep kernel alone: graph replays with no sweeps (set-up and
-    # finish), with exactly the sweeps convergence needs (all busy) and with
-    # the cap of 120 (the rest idle)
+    # a sweep alone: graph replays with no sweeps (set-up and outputs) and with
+    # exactly the sweeps convergence needs
     sw = tsm["sweeps"]
     t_cap = {}
-    for cap in (0, sw, 120):
+    for cap in (0, sw):
         graph = torch.cuda.CUDAGraph()
         with torch.cuda.graph(graph, stream=run.ctx.stream):
             two_sided(cap)
@@ -771,12 +773,11 @@ def follow_on(args, wl, parts, runner, V, torch) -> dict:
         torch.cuda.synchronize()
         t_cap[cap] = timed(graph.replay)
         del graph
-    busy = (t_cap[sw] - t_cap[0]) / max(sw, 1)
-    idle = (t_cap[120] - t_cap[sw]) / max(120 - sw, 1)
-    tsm["sweep_kernel"] = extrap_sweep_bytes(wl.mesh, (~torch.isnan(gl[0])).cpu().numpy(), busy)
-    tsm["sweep_kernel"].update(busy_us=busy, idle_us=idle, setup_and_finish_us=t_cap[0])
+    sweep = (t_cap[sw] - t_cap[0]) / max(sw, 1)
+    tsm["sweep_kernel"] = extrap_sweep_bytes(wl.mesh, (~torch.isnan(gl[0])).cpu().numpy(), sweep)
+    tsm["sweep_kernel"].update(sweep_us=sweep, setup_and_finish_us=t_cap[0])
     sk = tsm["sweep_kernel"]
-    log(f"extrapolation sweep: busy {busy:.2f} us, idle {idle:.2f} us, set-up and finish {t_cap[0]:.1f} us; "
+    log(f"extrapolation sweep: {sweep:.2f} us, set-up and finish {t_cap[0]:.1f} us; "
         f"{sk['algorithmic_bytes'] / 1e6:.2f} MB algorithmic per sweep -> {sk['GBps']:.0f} GB/s "
         f"({100 * sk['hbm_frac']:.1f} % of HBM)")
     nf_cap = wl.mesh.n_faces
