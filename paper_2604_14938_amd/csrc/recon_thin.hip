@@ -1343,8 +1343,8 @@ __device__ __forceinline__ void solve_cells(const ReconParams &p, typename Caps:
 // the groups it joins had no cells of their own.  Builds of 16 lanes a cell:
 // two rounds of teams of four; of four lanes a cell: one round of teams of
 // sixteen, then one of teams of four.  Whole label passes on 2,048 wavefronts:
-// 3,342 Voronoi cells 105 us in two rounds of teams, 134 us without teams; 2,832
-// with the network 120 and 135; 226 hexahedra in teams of sixteen 38 us, 53 us
+// 3,342 Voronoi cells 92 us in two rounds of teams, 99 us without teams; 2,832
+// with the network 117 and 116; 226 hexahedra in teams of sixteen 38 us, 53 us
 // without; 3,200 hexahedra in teams of four 60 us, of sixteen (two rounds)
 // 73 us; 10,251 without teams 83 us, in two rounds of teams of four 102 us.
 template <int C>
